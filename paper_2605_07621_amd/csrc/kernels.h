@@ -49,6 +49,7 @@ constexpr int HUBD_BATCH_SLOTS = 16;         // the same in the batched launch (
 constexpr int HUBD_ROWS = 4;                 // default rows per right-operator item
 constexpr int VEC_THREADS = 256;
 constexpr int64_t VEC_CHUNK = 8192;          // elements per reduction partial
+constexpr int64_t CGS_CHUNK_MIN = 1024;      // shortest chunk of the reorthogonalisation kernels
 constexpr int64_t STREAM_STORE_MIN = (int64_t)32 << 20;   // elements: results of vectors this long bypass the cache
 constexpr int MAX_BASIS = 1024;              // reorthogonalisation: vectors per projection call
 
@@ -145,13 +146,17 @@ hipError_t launch_axpy_norm(const VecJob *jobs_d, const int32_t *chunk_job_d, co
 // gate (nullable, device): when *gate == 0.0 the launch does nothing
 hipError_t launch_multidot(const double *basis, int64_t ld, int nvec, const double *y, int64_t n, double *partials,
                            int n_chunks, hipStream_t st, const double *gate = nullptr);
+// norm_part (nullable): also *norm_out = the sum of its n_chunks partials
 hipError_t launch_multidot_reduce(const double *partials, int n_chunks, int nvec, const double *scale, double *coef,
-                                  hipStream_t st, const double *gate = nullptr);
+                                  const double *norm_part, double *norm_out, hipStream_t st, const double *gate = nullptr);
 hipError_t launch_multiaxpy(const double *basis, int64_t ld, int nvec, const double *coef, const double *scale,
                             double *y, int64_t n, double *partials, int n_chunks, double sign, hipStream_t st,
                             const double *gate = nullptr);
-// scal[4] = 1 if scal[3] < scal[2] / 2 else 0 (second reorthogonalisation pass needed)
-hipError_t launch_dgks_gate(double *scal, hipStream_t st);
+// scal[3] = the sum of the partials, scal[4] = 1 if scal[3] < scal[2] / 2 else 0
+// (second reorthogonalisation pass needed)
+hipError_t launch_dgks_gate(double *scal, const double *partials, int n_chunks, hipStream_t st);
+// elements per chunk (partial sum) of the reorthogonalisation kernels
+int64_t cgs_chunk(int64_t n);
 hipError_t launch_scale_copy(const double *x, double *y, int64_t n, double a, hipStream_t st);
 hipError_t launch_fill_normal(double *y, int64_t n, uint64_t seed, hipStream_t st);
 

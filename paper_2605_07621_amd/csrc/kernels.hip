@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "ecut_internal.h"
 #include "kernels.h"
@@ -2394,19 +2395,24 @@ __global__ __launch_bounds__(VEC_THREADS) void k_axpy_norm(const VecJob *__restr
     }
 }
 
-// Reorthogonalisation kernels.  One work group per chunk of VEC_CHUNK
-// elements (512 threads x 16 elements); a thread's chunk of y stays in
+// Reorthogonalisation kernels.  One work group per chunk of 1024 x PAIRS
+// elements (512 threads x PAIRS element pairs); a thread's chunk of y stays in
 // registers while the basis vectors stream past it.  Element pair t of a
 // thread is (i0 + 2 (tid + 512 t), i0 + 2 (tid + 512 t) + 1); with V2 (every
 // vector 16-byte aligned, even ld) a pair is one 16-byte load.
+// Both kernels are bound by the basis stream, so the chunk follows the vector
+// length (cgs_chunk): long vectors take 8 pairs per thread, short ones fewer,
+// down to one, because 8,192-element chunks of a vector of 853,776 elements
+// are 105 groups on 256 compute units: there both kernels streamed the basis
+// at 2.0 TB/s, with 1,024-element chunks at 5.4-5.5 TB/s (100 steps of full
+// reorthogonalisation, 45.6 -> 20.6 ms).
 constexpr int CGS_THREADS = 512;
-constexpr int CGS_PAIRS = (int)(VEC_CHUNK / (2 * CGS_THREADS));
-static_assert(2 * CGS_THREADS * CGS_PAIRS == VEC_CHUNK, "one chunk per work group");
+static_assert(2 * CGS_THREADS * 8 == VEC_CHUNK && 2 * CGS_THREADS == CGS_CHUNK_MIN, "1 to 8 pairs per thread");
 
-template <bool V2>
-__device__ __forceinline__ void cgs_load(const double *__restrict__ p, int64_t i0, int64_t i1, double2 (&v)[CGS_PAIRS]) {
+template <bool V2, int PAIRS>
+__device__ __forceinline__ void cgs_load(const double *__restrict__ p, int64_t i0, int64_t i1, double2 (&v)[PAIRS]) {
 #pragma unroll
-    for (int t = 0; t < CGS_PAIRS; ++t) {
+    for (int t = 0; t < PAIRS; ++t) {
         const int64_t e = i0 + 2 * (int64_t)(threadIdx.x + CGS_THREADS * t);
         if (e + 1 < i1)
             v[t] = V2 ? *(const double2 *)(p + e) : make_double2(p[e], p[e + 1]);
@@ -2415,24 +2421,47 @@ __device__ __forceinline__ void cgs_load(const double *__restrict__ p, int64_t i
     }
 }
 
+// Wave sums of eight values together: each step exchanges the half of the
+// values the other half of the lanes keeps, so 10 exchanges instead of 48.
+// The lane's return value is the sum of value lane >> 3.
+__device__ __forceinline__ double wave_sum8(const double (&s)[8]) {
+    const int lane = threadIdx.x & 63;
+    double a[4], b[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const double keep = lane & 32 ? s[i + 4] : s[i], give = lane & 32 ? s[i] : s[i + 4];
+        a[i] = keep + __shfl_xor(give, 32, 64);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double keep = lane & 16 ? a[i + 2] : a[i], give = lane & 16 ? a[i] : a[i + 2];
+        b[i] = keep + __shfl_xor(give, 16, 64);
+    }
+    double r = (lane & 8 ? b[1] : b[0]) + __shfl_xor(lane & 8 ? b[0] : b[1], 8, 64);
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
+    return r;
+}
+
 // Classical Gram-Schmidt, dot phase: partials[k * n_chunks + chunk] = <w_k, y> over the chunk.
 // gate (nullable): when it points to 0.0 the kernel does nothing (the
 // conditional second pass of the reorthogonalisation).  The per-wave sums of
 // eight vectors are reduced across the group together, behind one barrier.
-template <bool V2>
+template <bool V2, int PAIRS>
 __global__ __launch_bounds__(CGS_THREADS) void k_multidot(const double *__restrict__ basis, int64_t ld, int nvec,
                                                           const double *__restrict__ y, int64_t n,
                                                           double *__restrict__ partials, int n_chunks,
                                                           const double *__restrict__ gate) {
     if (gate && *gate == 0.0) return;
     constexpr int NW = CGS_THREADS / 64;
+    constexpr int64_t CHUNK = 2 * CGS_THREADS * PAIRS;
     __shared__ double red[2][8][NW];   // two buffers: a group writes one while the other is read
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const int64_t i0 = (int64_t)c * VEC_CHUNK;
-        const int64_t i1 = i0 + VEC_CHUNK < n ? i0 + VEC_CHUNK : n;
-        double2 yv[CGS_PAIRS];
-        cgs_load<V2>(y, i0, i1, yv);
+        const int64_t i0 = (int64_t)c * CHUNK;
+        const int64_t i1 = i0 + CHUNK < n ? i0 + CHUNK : n;
+        double2 yv[PAIRS];
+        cgs_load<V2, PAIRS>(y, i0, i1, yv);
         int g = 0;
         for (int k0 = 0; k0 < nvec; k0 += 8, g ^= 1) {
             double s[8];
@@ -2440,21 +2469,17 @@ __global__ __launch_bounds__(CGS_THREADS) void k_multidot(const double *__restri
             for (int q = 0; q < 8; ++q) {
                 s[q] = 0.0;
                 if (k0 + q < nvec) {
-                    double2 b[CGS_PAIRS];
-                    cgs_load<V2>(basis + (int64_t)(k0 + q) * ld, i0, i1, b);
+                    double2 b[PAIRS];
+                    cgs_load<V2, PAIRS>(basis + (int64_t)(k0 + q) * ld, i0, i1, b);
 #pragma unroll
-                    for (int t = 0; t < CGS_PAIRS; ++t) {
+                    for (int t = 0; t < PAIRS; ++t) {
                         s[q] += b[t].x * yv[t].x;
                         s[q] += b[t].y * yv[t].y;
                     }
                 }
             }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) s[q] = wave_sum(s[q]);
-            if (lane == 0) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) red[g][q][wid] = s[q];
-            }
+            const double w8 = wave_sum8(s);
+            if ((lane & 7) == 0) red[g][lane >> 3][wid] = w8;
             __syncthreads();
             if (threadIdx.x < 8 && k0 + (int)threadIdx.x < nvec) {
                 double r = 0.0;
@@ -2467,17 +2492,25 @@ __global__ __launch_bounds__(CGS_THREADS) void k_multidot(const double *__restri
     }
 }
 
-// coef[k] = scale_k * sum_chunks partials[k][*]  (fixed order)
-__global__ __launch_bounds__(VEC_THREADS) void k_multidot_reduce(const double *__restrict__ partials, int n_chunks,
+// coef[k] = scale_k * sum_chunks partials[k][*]  (fixed order); with
+// norm_part, group nvec sums the norm partials of y before the projection
+// into *norm_out (k_reduce's order), in the same launch.
+__global__ __launch_bounds__(VEC_THREADS) void k_multidot_reduce(const double *__restrict__ partials, int n_chunks, int nvec,
                                                                  const double *__restrict__ scale, double *__restrict__ coef,
+                                                                 const double *__restrict__ norm_part,
+                                                                 double *__restrict__ norm_out,
                                                                  const double *__restrict__ gate) {
     if (gate && *gate == 0.0) return;
     __shared__ double red[VEC_THREADS / 64];
     const int k = blockIdx.x;
+    const double *__restrict__ p = k < nvec ? partials + (int64_t)k * n_chunks : norm_part;
     double s = 0.0;
-    for (int i = threadIdx.x; i < n_chunks; i += blockDim.x) s += partials[(int64_t)k * n_chunks + i];
+    for (int i = threadIdx.x; i < n_chunks; i += blockDim.x) s += p[i];
     s = block_sum(s, red);
-    if (threadIdx.x == 0) coef[k] = s * scale[k];
+    if (threadIdx.x == 0) {
+        if (k < nvec) coef[k] = s * scale[k];
+        else *norm_out = s;
+    }
 }
 
 // y <- y - sum_k coef[k] * scale_k * w_k (sign != 0), or y <- sum_k ... (sign
@@ -2485,44 +2518,45 @@ __global__ __launch_bounds__(VEC_THREADS) void k_multidot_reduce(const double *_
 // its terms in order k = 0, 1, ...  Capped at four waves per SIMD (at most
 // 128 registers): the uncapped build holds more loads in flight but runs one
 // group per compute unit, and streams the basis about 25% slower.
-template <bool V2>
+template <bool V2, int PAIRS>
 __global__ __launch_bounds__(CGS_THREADS, 4) void k_multiaxpy(const double *__restrict__ basis, int64_t ld, int nvec,
                                                            const double *__restrict__ coef, const double *__restrict__ scale,
                                                            double *__restrict__ y, int64_t n, double *__restrict__ partials,
                                                            int n_chunks, double sign, const double *__restrict__ gate) {
     if (gate && *gate == 0.0) return;
+    constexpr int64_t CHUNK = 2 * CGS_THREADS * PAIRS;
     __shared__ double red[CGS_THREADS / 64];
     __shared__ double cs[MAX_BASIS];
     for (int k = threadIdx.x; k < nvec; k += blockDim.x) cs[k] = coef[k] * scale[k];
     __syncthreads();
     for (int c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const int64_t i0 = (int64_t)c * VEC_CHUNK;
-        const int64_t i1 = i0 + VEC_CHUNK < n ? i0 + VEC_CHUNK : n;
-        double2 v[CGS_PAIRS];
+        const int64_t i0 = (int64_t)c * CHUNK;
+        const int64_t i1 = i0 + CHUNK < n ? i0 + CHUNK : n;
+        double2 v[PAIRS];
 #pragma unroll
-        for (int t = 0; t < CGS_PAIRS; ++t) v[t] = make_double2(0.0, 0.0);
+        for (int t = 0; t < PAIRS; ++t) v[t] = make_double2(0.0, 0.0);
         // eight vectors per unrolled group, as in the dot kernel, so that
         // loads of later vectors can go out early
         for (int k0 = 0; k0 < nvec; k0 += 8) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 if (k0 + q < nvec) {
-                    double2 b[CGS_PAIRS];
-                    cgs_load<V2>(basis + (int64_t)(k0 + q) * ld, i0, i1, b);
+                    double2 b[PAIRS];
+                    cgs_load<V2, PAIRS>(basis + (int64_t)(k0 + q) * ld, i0, i1, b);
                     const double ck = cs[k0 + q];
 #pragma unroll
-                    for (int t = 0; t < CGS_PAIRS; ++t) {
+                    for (int t = 0; t < PAIRS; ++t) {
                         v[t].x += ck * b[t].x;
                         v[t].y += ck * b[t].y;
                     }
                 }
             }
         }
-        double2 yo[CGS_PAIRS];
-        if (sign != 0.0) cgs_load<V2>(y, i0, i1, yo);
+        double2 yo[PAIRS];
+        if (sign != 0.0) cgs_load<V2, PAIRS>(y, i0, i1, yo);
         double s = 0.0;
 #pragma unroll
-        for (int t = 0; t < CGS_PAIRS; ++t) {
+        for (int t = 0; t < PAIRS; ++t) {
             const int64_t e = i0 + 2 * (int64_t)(threadIdx.x + CGS_THREADS * t);
             const double2 r = sign != 0.0 ? make_double2(yo[t].x - v[t].x, yo[t].y - v[t].y) : v[t];
             if (e + 1 < i1) {
@@ -2549,13 +2583,22 @@ __global__ __launch_bounds__(CGS_THREADS, 4) void k_multiaxpy(const double *__re
 // Second-pass test of the reorthogonalisation (Daniel, Gragg, Kaufman and
 // Stewart, 1976): project again only when the first projection removed more
 // than half of the squared norm, ||w'||^2 < ||w||^2 / 2.
-// s[2] = ||w||^2 before, s[3] = ||w'||^2 after the first pass; s[4] = gate.
-__global__ void k_dgks_gate(double *s) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) s[4] = (s[3] < 0.5 * s[2]) ? 1.0 : 0.0;
+// s[2] = ||w||^2 before; s[3] = ||w'||^2 after the first pass, summed here
+// from its partials (k_reduce's order); s[4] = gate.
+__global__ __launch_bounds__(VEC_THREADS) void k_dgks_gate(double *__restrict__ s, const double *__restrict__ partials,
+                                                           int n_chunks) {
+    __shared__ double red[VEC_THREADS / 64];
+    double t = 0.0;
+    for (int i = threadIdx.x; i < n_chunks; i += blockDim.x) t += partials[i];
+    t = block_sum(t, red);
+    if (threadIdx.x == 0) {
+        s[3] = t;
+        s[4] = (t < 0.5 * s[2]) ? 1.0 : 0.0;
+    }
 }
 
-hipError_t launch_dgks_gate(double *scal, hipStream_t st) {
-    hipLaunchKernelGGL(k_dgks_gate, dim3(1), dim3(64), 0, st, scal);
+hipError_t launch_dgks_gate(double *scal, const double *partials, int n_chunks, hipStream_t st) {
+    hipLaunchKernelGGL(k_dgks_gate, dim3(1), dim3(VEC_THREADS), 0, st, scal, partials, n_chunks);
     return hipGetLastError();
 }
 
@@ -2760,21 +2803,42 @@ static bool cgs_aligned(const double *basis, int64_t ld, const double *y) {
     return ((((uintptr_t)basis | (uintptr_t)y) & 15) == 0) && (ld & 1) == 0;
 }
 
+// The chunk of the reorthogonalisation kernels for vectors of n elements: the
+// longest of 8192, 4096, 2048 and 1024 that still gives four groups per
+// compute unit (1,024 chunks), else the shortest.
+int64_t cgs_chunk(int64_t n) {
+    int64_t c = VEC_CHUNK;
+    while (c > CGS_CHUNK_MIN && n < c * 1024) c /= 2;
+    return c;
+}
+
+// calls f with the kernel variant's alignment and pairs per thread as constants
+template <class F>
+static void cgs_variant(bool v2, int64_t chunk, F f) {
+    auto pairs = [&](auto v) {
+        if (chunk == VEC_CHUNK) f(v, std::integral_constant<int, 8>{});
+        else if (chunk == VEC_CHUNK / 2) f(v, std::integral_constant<int, 4>{});
+        else if (chunk == VEC_CHUNK / 4) f(v, std::integral_constant<int, 2>{});
+        else f(v, std::integral_constant<int, 1>{});
+    };
+    if (v2) pairs(std::true_type{});
+    else pairs(std::false_type{});
+}
+
 hipError_t launch_multidot(const double *basis, int64_t ld, int nvec, const double *y, int64_t n, double *partials,
                            int n_chunks, hipStream_t st, const double *gate) {
     const int grid = n_chunks < 1 ? 1 : (n_chunks < 65536 ? n_chunks : 65536);
-    if (cgs_aligned(basis, ld, y))
-        hipLaunchKernelGGL(k_multidot<true>, dim3(grid), dim3(CGS_THREADS), 0, st, basis, ld, nvec, y, n, partials,
-                           n_chunks, gate);
-    else
-        hipLaunchKernelGGL(k_multidot<false>, dim3(grid), dim3(CGS_THREADS), 0, st, basis, ld, nvec, y, n, partials,
-                           n_chunks, gate);
+    cgs_variant(cgs_aligned(basis, ld, y), cgs_chunk(n), [&](auto v2, auto pairs) {
+        hipLaunchKernelGGL((k_multidot<decltype(v2)::value, decltype(pairs)::value>), dim3(grid), dim3(CGS_THREADS), 0, st,
+                           basis, ld, nvec, y, n, partials, n_chunks, gate);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_multidot_reduce(const double *partials, int n_chunks, int nvec, const double *scale, double *coef,
-                                  hipStream_t st, const double *gate) {
-    hipLaunchKernelGGL(k_multidot_reduce, dim3(nvec), dim3(VEC_THREADS), 0, st, partials, n_chunks, scale, coef, gate);
+                                  const double *norm_part, double *norm_out, hipStream_t st, const double *gate) {
+    hipLaunchKernelGGL(k_multidot_reduce, dim3(nvec + (norm_part ? 1 : 0)), dim3(VEC_THREADS), 0, st, partials, n_chunks,
+                       nvec, scale, coef, norm_part, norm_out, gate);
     return hipGetLastError();
 }
 
@@ -2782,12 +2846,10 @@ hipError_t launch_multiaxpy(const double *basis, int64_t ld, int nvec, const dou
                             double *y, int64_t n, double *partials, int n_chunks, double sign, hipStream_t st,
                             const double *gate) {
     const int grid = n_chunks < 1 ? 1 : (n_chunks < 65536 ? n_chunks : 65536);
-    if (cgs_aligned(basis, ld, y))
-        hipLaunchKernelGGL(k_multiaxpy<true>, dim3(grid), dim3(CGS_THREADS), 0, st, basis, ld, nvec, coef, scale, y, n,
-                           partials, n_chunks, sign, gate);
-    else
-        hipLaunchKernelGGL(k_multiaxpy<false>, dim3(grid), dim3(CGS_THREADS), 0, st, basis, ld, nvec, coef, scale, y,
-                           n, partials, n_chunks, sign, gate);
+    cgs_variant(cgs_aligned(basis, ld, y), cgs_chunk(n), [&](auto v2, auto pairs) {
+        hipLaunchKernelGGL((k_multiaxpy<decltype(v2)::value, decltype(pairs)::value>), dim3(grid), dim3(CGS_THREADS), 0, st,
+                           basis, ld, nvec, coef, scale, y, n, partials, n_chunks, sign, gate);
+    });
     return hipGetLastError();
 }
 

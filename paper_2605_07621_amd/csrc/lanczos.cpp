@@ -27,11 +27,11 @@
 
 namespace ecut {
 
-// Elements per norm partial: VEC_CHUNK with reorthogonalisation (its kernels
-// share that layout); for three-term solves smaller, down to 1024, so a
+// Elements per norm partial: the reorthogonalisation kernels' chunk when they
+// run (they share that layout); for three-term solves smaller, down to 1024, so a
 // short vector's update pass still spreads over many work groups.
 static int64_t chunk_of(int64_t n, bool reorth) {
-    if (reorth) return VEC_CHUNK;
+    if (reorth) return cgs_chunk(n);
     int64_t c = 1024;
     while (c < VEC_CHUNK && c * 2048 < n) c *= 2;
     return c;
@@ -270,7 +270,7 @@ struct StepPlan {
     HubBatchLayout hub_l;
     bool fuse_alpha = false;                  // alpha formed inside the update pass
     Pack P;
-    size_t o_rows = 0, o_ja = 0, o_jx = 0, o_jb = 0, o_cj = 0, o_ci = 0, o_n0 = 0, o_n1 = 0;
+    size_t o_rows = 0, o_ja = 0, o_jx = 0, o_jb = 0, o_cj = 0, o_ci = 0;
     int n_ja = 0, n_cj = 0;
     LzSolve *R = nullptr;                     // the one solve with reorthogonalisation, if any
 };
@@ -372,19 +372,6 @@ static void build_plan(const std::vector<LzSolve *> &act, double *out2, StepPlan
     pl.n_ja = (int)ja.size();
     pl.n_cj = (int)cj.size();
     pl.R = (act.size() == 1 && act[0]->reorth) ? act[0] : nullptr;
-    if (pl.R) {
-        // squared norm of w before (scal[2]) and after (scal[3]) the first projection
-        std::vector<VecJob> n0(1), n1(1);
-        n0[0].partials = pl.R->part_norm;
-        n0[0].n_partials = pl.R->n_chunks;
-        n0[0].mode = 1;
-        n0[0].scalars = pl.R->scal;
-        n0[0].out = 2;
-        n1[0] = n0[0];
-        n1[0].out = 3;
-        pl.o_n0 = pl.P.put(n0);
-        pl.o_n1 = pl.P.put(n1);
-    }
 }
 
 // launches of a step; dev: a device copy of pl.P.buf
@@ -411,17 +398,18 @@ static ecut_status enqueue_plan(const StepPlan &pl, const void *dev, hipStream_t
         // part_norm, so beta^2 below is the norm of the vector actually kept.
         const int nv = R->j + 1;
         if (nv > MAX_BASIS) return fail(ECUT_EUNSUPPORTED, "too many basis vectors");
-        e = launch_reduce((const VecJob *)(d + pl.o_n0), 1, st);
         const double *gate = R->scal + 4;
         for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
             const double *g = pass == 1 ? gate : nullptr;
             e = launch_multidot(R->basis, basis_ld(*R), nv, yvec(*R), R->n, R->part_cgs, R->n_chunks, st, g);
-            if (e == hipSuccess) e = launch_multidot_reduce(R->part_cgs, R->n_chunks, nv, R->dscale, R->dcoef, st, g);
+            // the first pass also sums |w|^2 before the projection (scal[2])
+            if (e == hipSuccess)
+                e = launch_multidot_reduce(R->part_cgs, R->n_chunks, nv, R->dscale, R->dcoef,
+                                           pass == 0 ? R->part_norm : nullptr, R->scal + 2, st, g);
             if (e == hipSuccess)
                 e = launch_multiaxpy(R->basis, basis_ld(*R), nv, R->dcoef, R->dscale, yvec(*R), R->n, R->part_norm,
                                      R->n_chunks, 1.0, st, g);
-            if (e == hipSuccess && pass == 0) e = launch_reduce((const VecJob *)(d + pl.o_n1), 1, st);
-            if (e == hipSuccess && pass == 0) e = launch_dgks_gate(R->scal, st);
+            if (e == hipSuccess && pass == 0) e = launch_dgks_gate(R->scal, R->part_norm, R->n_chunks, st);
         }
         if (e != hipSuccess) return hip_fail(e, "reorthogonalisation");
     }
