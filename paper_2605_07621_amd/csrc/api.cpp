@@ -312,6 +312,7 @@ ecut_status upload(ecut_sectors *s) {
     P.maps = (const int32_t *)(b + o_maps);
     P.dim = s->dim;
     P.xscale = 1.0;
+    P.rows_split = rows_split_of(s);
     if (s->spin_ok || s->sp2_ok) {
         P.spin_ok = (s->spin_ok && s->tune.variant == 0) ? 1 : 0;
         P.n_rflip = (int32_t)s->spin_fmask.size();
@@ -454,6 +455,22 @@ int32_t max_tile_elems(const ecut_sectors *s) {
     return (int32_t)m;
 }
 
+// The generic kernel's items are row tiles of about 2,048 amplitudes, and at
+// least one row: a problem of few or long rows has too few of them to fill the
+// device.  Such a problem's items are cut into slices of at least one pass of
+// a work group until the launch has about ROWS_MIN_GROUPS groups.  Problems the
+// spin kernel can take keep whole items (the generic kernel is their fallback
+// tuning, with rows staged in LDS).
+int32_t rows_split_of(const ecut_sectors *s) {
+    if (s->kernel == 1 || s->spin_ok || s->item_slots <= 0) return 1;
+    int64_t tile = 0;
+    for (const ItemDev &it : s->hub_spatial ? s->generic_items : s->items)
+        tile = std::max<int64_t>(tile, (int64_t)(it.row1 - it.row0) * s->blocks[it.block].d_r);
+    const int64_t n = s->hub_spatial ? (int64_t)s->generic_items.size() : s->item_slots;
+    const int64_t most = (tile + ROWS_THREADS - 1) / ROWS_THREADS;
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(most, std::min<int64_t>(ROWS_MIN_GROUPS / n, 65535)));
+}
+
 // Item counts of the two-pass kernels for the current tuning: the left pass
 // takes `grid` rows of the level order (0 = HUBU_ROWS) per item over slabs of
 // 64 lanes x 1 or 2 columns; the right pass `tile` rows (0 = HUBD_ROWS) x
@@ -583,7 +600,7 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
         if (s->tune.order == 1) grid = std::max(8, ((grid > 0 ? grid : 2048) / 8) * 8);   // keeps chunk c on XCD c
         e = launch_spin(nullptr, P, s->dev_items, (int)s->items.size(), max_tile_elems(s), s->max_d_r, grid, st);
     } else {
-        e = launch_rows(nullptr, P, s->dev_items, (int)s->items.size(), max_tile_elems(s), st);
+        e = launch_rows(nullptr, P, s->dev_items, (int)s->items.size(), max_tile_elems(s), P.rows_split, st);
     }
     if (e != hipSuccess) return hip_fail(e, "kernel launch (apply_H)");
     return ECUT_OK;
@@ -639,7 +656,7 @@ hipError_t hub6_batch_launch(const HubBatch &b, const HubBatchLayout &l, const v
 
 // number of partial slots the apply kernel writes
 int32_t apply_partial_slots(const ecut_sectors *s) {
-    if (s->kernel != 1) return s->item_slots;
+    if (s->kernel != 1) return s->item_slots * ((s->spin_ok || s->tune.variant == 2) ? 1 : s->prob.rows_split);
     if (s->tune.variant == 5 && s->hubseg_ok) return s->hs_n_slots;
     if (s->tune.variant == 7 && s->hub3_ok) return (int32_t)s->hub_items.size();
     if (s->tune.variant == 6 && s->hub6_ok) {
@@ -661,7 +678,7 @@ int32_t apply_partial_slots_max(const ecut_sectors *s) {
                                                                                     (int32_t)s->hub_items.size()),
                                                                   s->hubseg_ok ? s->hs_n_slots : 0),
                                               h6)
-                          : std::max(s->item_slots_cap, s->item_slots);
+                          : std::max(s->item_slots_cap, s->item_slots) * std::max(1, s->prob.rows_split);
 }
 
 // ---------------------------------------------------------------- staging buffers
@@ -743,6 +760,7 @@ void make_rows_batch(const std::vector<ProblemDev> &probs, const std::vector<Ite
         if (!probs[it.prob].spin_ok) {
             items.push_back(it);
             b.rows_tile = std::max(b.rows_tile, tiles[it.prob]);
+            b.rows_split = std::max(b.rows_split, probs[it.prob].rows_split);
         }
     b.n_items = (int)items.size();
     b.pb = (probs.size() * sizeof(ProblemDev) + 255) & ~(size_t)255;
@@ -759,7 +777,7 @@ hipError_t launch_rows_batch(const RowsBatch &b, const void *dev, hipStream_t st
     hipError_t e = hipSuccess;
     if (b.n_spin > 0) e = launch_spin(probs_d, b.spin_single, items_d, b.n_spin, b.spin_tile, b.spin_src, 0, st);
     if (e == hipSuccess && b.n_spin < b.n_items)
-        e = launch_rows(probs_d, b.rows_single, items_d + b.n_spin, b.n_items - b.n_spin, b.rows_tile, st);
+        e = launch_rows(probs_d, b.rows_single, items_d + b.n_spin, b.n_items - b.n_spin, b.rows_tile, b.rows_split, st);
     return e;
 }
 

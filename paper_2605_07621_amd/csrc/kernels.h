@@ -10,6 +10,7 @@
 namespace ecut {
 
 constexpr int ROWS_THREADS = 256;
+constexpr int ROWS_MIN_GROUPS = 4096;        // generic kernel: items are sliced until a launch has about this many groups
 constexpr size_t ROWS_MAX_LDS = 64 * 1024;   // generic kernel stages tiles up to this size
 constexpr int HUB_THREADS = 1024;
 constexpr int HUB_MAXC = 16;                 // columns per thread: d_R <= HUB_THREADS * HUB_MAXC
@@ -93,8 +94,9 @@ struct VecJob {
 
 size_t hub_lds_bytes(const ecut_sectors *s);
 hipError_t set_hub_lds_limits(size_t bytes);
+// max_split: the largest rows_split of the launch's problems
 hipError_t launch_rows(const ProblemDev *probs_d, const ProblemDev &single, const ItemDev *items_d, int n_items,
-                       int max_tile_elems, hipStream_t st);
+                       int max_tile_elems, int max_split, hipStream_t st);
 // spin kernel with ranking tables; every problem of the launch must have
 // spin_ok.  max_src: largest d_r of any block of the launch's problems.
 // grid: work groups of each of the two launches (0 = min(n_items, 2048)).

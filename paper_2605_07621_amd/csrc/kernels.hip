@@ -67,10 +67,40 @@ __device__ __forceinline__ double2 epi_factors(const double *dscale, double xsca
     return dscale ? make_double2(dscale[0], dscale[1]) : make_double2(xscale, zcoef);
 }
 
+// sum of the CSR row [k0, k1) over the gathered values src(column), added to
+// acc in entry order; four entries' indices, then four values, in flight
+template <class Src>
+__device__ __forceinline__ double csr_add(double acc, int k0, int k1, const int32_t *__restrict__ col,
+                                          const double *__restrict__ val, Src src) {
+    for (int k = k0; k < k1; k += 4) {
+        int c[4];
+        double h[4], v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = k + u < k1 ? k + u : k;
+            c[u] = col[q];
+            h[u] = val[q];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = src(c[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k + u < k1) acc += h[u] * v[u];
+    }
+    return acc;
+}
+
 // ------------------------------------------------------------------------
 // Generic row-tile kernel: any cut, sector-changing cross terms, batches of
 // problems.  One work item = rows [row0,row1) of one block, staged in LDS
-// (STAGE) so the right-operator gathers hit LDS.
+// (STAGE) so the right-operator gathers hit LDS.  A problem of few items
+// (P.rows_split > 1) has every item cut into that many slices of elements,
+// one work group each (blockIdx.y), which gather from global memory: an
+// amplitude is a chain of dependent index, value and amplitude loads, so a
+// problem is latency bound until every compute unit holds several groups.
+// The 36-site ring with 5 magnons (376,992 amplitudes, rows of up to 11,628
+// in about 50 items): 364 us with whole items and one entry at a time, 15.7 us
+// in slices of 256.
 // ------------------------------------------------------------------------
 template <bool STAGE>
 __global__ __launch_bounds__(ROWS_THREADS) void k_rows(const ProblemDev *__restrict__ probs, const ProblemDev single,
@@ -81,26 +111,32 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_rows(const ProblemDev *__restr
         const ItemDev W = items[it];
         if (W.row1 <= W.row0) continue;   // padding of an XCD-dealt list
         const ProblemDev &P = probs ? probs[W.prob] : single;
+        const int split = P.rows_split, part_no = blockIdx.y;
+        if (part_no >= split) continue;   // uniform over the group
         const double2 ef = epi_factors(P.dscale, P.xscale, P.zcoef);
         const BlockDev B = P.blocks[W.block];
         const int dR = B.d_r;
         const int nrows = W.row1 - W.row0;
         const int n = nrows * dR;
+        // this group's slice of the item's elements, in whole passes of the group
+        const int slice = split > 1 ? ((n + split - 1) / split + ROWS_THREADS - 1) / ROWS_THREADS * ROWS_THREADS : n;
+        const int e0 = (int)min((int64_t)part_no * slice, (int64_t)n), e1 = (int)min((int64_t)e0 + slice, (int64_t)n);
+        const bool stage = STAGE && split == 1;
         const double *__restrict__ xblk = P.x + B.offset;
         const double *__restrict__ xt = xblk + (int64_t)W.row0 * dR;
-        if (STAGE) {
+        if (stage) {
             for (int e = threadIdx.x; e < n; e += blockDim.x) lds[e] = xt[e];
             __syncthreads();
         }
         double part = 0.0;
-        for (int e = threadIdx.x; e < n; e += blockDim.x) {
+        for (int e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
             const int lr = e / dR;
             const int r = e - lr * dR;
             const int l = W.row0 + lr;
             const int gl = B.lbase + l, gr = B.rbase + r;
             const uint32_t lw = P.lwords[gl], rw = P.rwords[gr];
-            const double *xrow = STAGE ? (lds + lr * dR) : (xt + (int64_t)lr * dR);
-            const double xv = xrow[r];
+            const int kr0 = P.hr_ptr[gr], kr1 = P.hr_ptr[gr + 1], kl0 = P.hl_ptr[gl], kl1 = P.hl_ptr[gl + 1];
+            const double xv = stage ? lds[e] : xt[e];
             double dg = P.diag_l[gl] + P.diag_r[gr];
             for (int k = 0; k < P.n_xdiag; ++k) {
                 const XDiagDev X = P.xdiag[k];
@@ -111,9 +147,15 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_rows(const ProblemDev *__restr
                 dg += X.coef * fl * fr;
             }
             double acc = dg * xv;
-            for (int k = P.hr_ptr[gr]; k < P.hr_ptr[gr + 1]; ++k) acc += P.hr_val[k] * xrow[P.hr_col[k]];
-            for (int k = P.hl_ptr[gl]; k < P.hl_ptr[gl + 1]; ++k)
-                acc += P.hl_val[k] * xblk[(int64_t)P.hl_col[k] * dR + r];
+            if (stage) {
+                const double *xrow = lds + lr * dR;
+                acc = csr_add(acc, kr0, kr1, P.hr_col, P.hr_val, [&](int c) { return xrow[c]; });
+            } else {
+                const double *xrow = xt + (int64_t)lr * dR;
+                acc = csr_add(acc, kr0, kr1, P.hr_col, P.hr_val, [&](int c) { return xrow[c]; });
+            }
+            const double *xcol = xblk + r;
+            acc = csr_add(acc, kl0, kl1, P.hl_col, P.hl_val, [&](int c) { return xcol[(int64_t)c * dR]; });
             for (int k = 0; k < P.n_xbond; ++k) {
                 const XBondDev X = P.xbond[k];
                 int src, lp, rp;
@@ -145,8 +187,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_rows(const ProblemDev *__restr
         }
         if (P.partials) {
             const double s = block_sum(part, red);
-            if (threadIdx.x == 0) P.partials[W.slot] = s;
-        } else if (STAGE) {
+            if (threadIdx.x == 0) P.partials[(int64_t)W.slot * split + part_no] = s;
+        } else if (stage) {
             __syncthreads();
         }
     }
@@ -2630,15 +2672,15 @@ __global__ void k_fill_normal(double *__restrict__ y, int64_t n, uint64_t seed) 
 // host launchers
 // ------------------------------------------------------------------------
 hipError_t launch_rows(const ProblemDev *probs_d, const ProblemDev &single, const ItemDev *items_d, int n_items,
-                       int max_tile_elems, hipStream_t st) {
+                       int max_tile_elems, int max_split, hipStream_t st) {
     if (n_items <= 0) return hipSuccess;
     const bool stage = (size_t)max_tile_elems * 8 <= ROWS_MAX_LDS;
-    int grid = n_items < 65536 ? n_items : 65536;
+    const dim3 grid(n_items < 65536 ? n_items : 65536, max_split < 1 ? 1 : max_split);
     if (stage) {
         const size_t lds = (size_t)max_tile_elems * 8;
-        hipLaunchKernelGGL(k_rows<true>, dim3(grid), dim3(ROWS_THREADS), lds, st, probs_d, single, items_d, n_items);
+        hipLaunchKernelGGL(k_rows<true>, grid, dim3(ROWS_THREADS), lds, st, probs_d, single, items_d, n_items);
     } else {
-        hipLaunchKernelGGL(k_rows<false>, dim3(grid), dim3(ROWS_THREADS), 0, st, probs_d, single, items_d, n_items);
+        hipLaunchKernelGGL(k_rows<false>, grid, dim3(ROWS_THREADS), 0, st, probs_d, single, items_d, n_items);
     }
     return hipGetLastError();
 }

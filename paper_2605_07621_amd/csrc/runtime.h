@@ -16,6 +16,8 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
 int32_t apply_partial_slots(const ecut_sectors *s);        // slots the current launch writes
 int32_t apply_partial_slots_max(const ecut_sectors *s);    // slots any variant may write
 int32_t max_tile_elems(const ecut_sectors *s);
+// work groups per item of the generic row kernel for this problem
+int32_t rows_split_of(const ecut_sectors *s);
 // key of a problem's launch tuning: device architecture and problem shape
 std::string tune_shape_key(const ecut_sectors *s);
 
@@ -24,7 +26,7 @@ std::string tune_shape_key(const ecut_sectors *s);
 struct RowsBatch {
     std::vector<char> buf;
     size_t pb = 0;
-    int n_spin = 0, n_items = 0, spin_tile = 0, spin_src = 0, rows_tile = 0, first_spin = -1;
+    int n_spin = 0, n_items = 0, spin_tile = 0, spin_src = 0, rows_tile = 0, rows_split = 1, first_spin = -1;
     ProblemDev spin_single{}, rows_single{};
 };
 void make_rows_batch(const std::vector<ProblemDev> &probs, const std::vector<ItemDev> &items,

@@ -50,3 +50,31 @@ def test_reorth_chunk_lengths(dev, n, n_up):
     gs = gs / gs.norm()
     gs = gs if float(gs @ ref) > 0 else -gs
     assert float((gs - ref).norm()) <= 1e-10
+
+
+# the generic kernel's slices: fewer elements than one pass of a group, rows
+# longer than a slice, a last slice that is empty, and problems of different
+# slice counts in one batch
+_SLICED = [(33, 1, 16), (34, 3, 17), (36, 4, 17), (40, 3, 20)]
+
+
+def test_generic_kernel_slices_vs_oracle(dev):
+    """H psi of wide rings against the oracle (relative L2 1e-12, as every
+    H psi test), alone and in one batch (the same vectors bit for bit), and
+    alpha of the first Lanczos step, which sums the slices' partials:
+    <x, H x> / <x, x> to 1e-12 of |H x| / |x|."""
+    import oracle as O
+    probs = [I.Problem(I.xxz_chain(n, 1.0, 0.6, periodic=True), I.Cut("spatial", I.left_mask_first(cut)), k)
+             for n, k, cut in _SLICED]
+    S = [ecut.Sectors.from_problem(p) for p in probs]
+    xs = [_vec(s.dim, 40 + k, dev) for k, s in enumerate(S)]
+    ys = [torch.empty_like(x) for x in xs]
+    ecut.apply_batch(S, xs, ys)
+    for p, s, x, yb in zip(probs, S, xs, ys):
+        y = s.apply(x)
+        assert torch.equal(y, yb)
+        ref = O.Sector(p.model, p.n_up).apply(s.export(x).cpu().numpy())
+        got = s.export(y).cpu().numpy()
+        assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
+        a, _, n2 = ecut.lanczos_tridiag(s, x, 1)
+        assert abs(a[0] - float(x @ y) / n2) <= 1e-12 * float(y.norm()) / float(x.norm())
