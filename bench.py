@@ -281,6 +281,13 @@ def serving_bench(n_requests, budget_gb):
 def kernel_name(S):
     """Name of the kernel that carries the apply under the handle's tuning."""
     info, t = S.info, S.get_tuning()
+    if not any(t.values()):   # the default selects by size
+        if info.kernel == 1 and info.kernel_flags & 32:
+            if S.dim <= 1 << 18:
+                return "k_hubF"
+            return "k_hubU+k_hub3" if info.kernel_flags & 2 and S.dim >= 1 << 25 else "k_hubU+k_hubD"
+        if info.kernel_flags & 64:
+            return "k_flat" if S.dim <= 1 << 20 else "k_spinL+k_spinR"
     if info.kernel == 1:
         v = t["variant"]
         if v == 0:

@@ -221,12 +221,15 @@ ecut_status ecut_apply_H(const ecut_sectors *s, const double *psi_d, double *y_d
  * n independent applications y_k = H_k psi_k, the batched sector dispatch
  * over many Hamiltonians (the uneven symmetry sectors of the paper's
  * discussion of symmetry fragmentation, Eq. (3) blocks of every problem).
- * Spin and generic problems share one work queue over (problem, block, row
- * tile), largest tiles first (one launch of the spin kernel pair and/or one
- * of the generic row kernel); Hubbard up/down problems tuned to the two-pass
- * kernels (variant 6, at most 16 hopping bonds) share one launch per pass,
- * other Hubbard tunings run their own kernels.  Each output equals what
- * ecut_apply_H gives for that problem alone, bit for bit.
+ * The problems on the default's thread-per-amplitude kernel share one launch
+ * per kind (spin, spatial Hubbard); other one-pass spin and generic problems
+ * share one work queue over (problem, block, row tile), largest tiles first
+ * (one launch of the spin kernel pair and/or one of the generic row kernel);
+ * Hubbard up/down problems of at most 16 hopping bonds whose tuning selects
+ * the fused or the two-pass kernels (the default, or variant 6) share one
+ * launch for all fused ones and one per pass for the others; other tunings
+ * run their own kernels.  Each output equals what ecut_apply_H gives for that
+ * problem alone, bit for bit.
  * s, psi_d, y_d: host arrays of n entries.  The launch descriptors go
  * through device buffers the library allocates on first use and grows (a
  * ring of four per calling thread, with pinned staging): the call does not
@@ -257,8 +260,15 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
                                        double *const *y_d, void *stream);
 
 /*
- * Launch tuning of ecut_apply_H (used by the Hubbard up/down kernel, whose
- * work groups each own one row of Psi at a time):
+ * Launch tuning of ecut_apply_H.  All fields 0, the default, selects the
+ * kernels by the vector's size: Hubbard up/down problems of at most 32
+ * hopping bonds run one fused kernel up to 2^18 amplitudes, the two-pass
+ * kernels (variant 6) above, and variant 7 from 2^25 where it is available;
+ * spin problems and the spatial Hubbard cut, where kernel_flags bit 6 is set,
+ * run one kernel with a thread per amplitude up to 2^20 amplitudes and the
+ * two-pass kernels (variant 2) above; other problems run variant 0's kernel.
+ * Explicit tunings (used by the Hubbard up/down kernel, whose work groups
+ * each own one row of Psi at a time):
  *   grid:      work groups (0 = one per compute unit);
  *   n_xcd:     rows are split into n_xcd contiguous chunks of the row order,
  *              chunk k served by the work groups with blockIdx % n_xcd == k
@@ -293,7 +303,9 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
  *              down high-half hops find their source in L2 (needs
  *              kernel_flags bit 4; row_order ignored; n_xcd 1 = plain grid
  *              stride, else 8 XCD chunks),
- *              6 two passes of one work group per item (kernel_flags bit 5):
+ *              6 two passes of one work group per item (kernel_flags bit 5;
+ *              vectors of at most 2^18 amplitudes take the default's fused
+ *              kernel instead, and grid and tile are ignored):
  *              the left operator over column slabs in inversion-level row
  *              order (grid = rows per item, 0 = 4, at most 32), then the
  *              right operator, diagonal and epilogue with the source

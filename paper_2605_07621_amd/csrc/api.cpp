@@ -233,7 +233,7 @@ ecut_status upload(ecut_sectors *s) {
         o_hbb = A.add(s->hrow_bbetw);
         o_hbc = A.add(s->hrow_bcoef);
     }
-    size_t o_spr = 0, o_spb = 0, o_spp = 0, o_spc = 0, o_spv = 0, o_spt = 0, o_sptb = 0;
+    size_t o_spr = 0, o_spb = 0, o_spp = 0, o_spc = 0, o_spv = 0, o_spt = 0, o_sptb = 0, o_flat = 0;
     if (s->spin_ok || s->sp2_ok) {
         o_sfm = A.add(s->spin_fmask);
         o_sfc = A.add(s->spin_fcoef);
@@ -244,6 +244,7 @@ ecut_status upload(ecut_sectors *s) {
         o_spv = A.add(s->sp_pval);
         o_spt = A.add(s->sp_tab);
         o_sptb = A.add(s->sp_tbase);
+        o_flat = A.add(s->flat_base);
     }
     size_t o_3si = 0, o_3li = 0, o_3lo = 0, o_3hn = 0, o_3hc = 0;
     if (s->hub3_ok) {
@@ -328,6 +329,10 @@ ecut_status upload(ecut_sectors *s) {
         s->dev_sp_pval = (const double *)(b + o_spv);
         s->dev_sp_tab = (const uint16_t *)(b + o_spt);
         s->dev_sp_tbase = (const int64_t *)(b + o_sptb);
+        P.sp_tab = s->dev_sp_tab;
+        P.sp_tbase = s->dev_sp_tbase;
+        P.flat_base = (const int32_t *)(b + o_flat);
+        P.flat_groups = s->flat_base.empty() ? 0 : s->flat_base.back();
     }
     s->dev_items = (ItemDev *)(b + o_items);
     if (s->hub_ok) {
@@ -446,7 +451,41 @@ ecut_status upload(ecut_sectors *s) {
     s->dev_bytes = A.off;
     s->device = dev;
     s->on_device = true;
+    P.flat = flat_on(s) ? (s->hub_spatial ? 2 : 1) : 0;
     return ECUT_OK;
+}
+
+static bool default_tuning(const ApplyTuning &T) {
+    return T.grid == 0 && T.n_xcd == 0 && T.order == 0 && T.variant == 0 && T.tile == 0;
+}
+
+// The default tuning of a spin or spatial Hubbard cut whose tables the flat
+// kernel can read (flat_base is built for vectors it is the better kernel for)
+bool flat_on(const ecut_sectors *s) {
+    return s->on_device && s->kernel != 1 && !s->flat_base.empty() && default_tuning(s->tune);
+}
+
+// Variant 2 of a spin or spatial Hubbard cut, and the default tuning of the
+// vectors too long for the flat kernel
+bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T) {
+    return s->kernel != 1 && s->sp2_ok && (T.variant == 2 || (s->flat_base.empty() && default_tuning(T)));
+}
+
+// The default tuning, and the two-pass tuning, of a Hubbard up/down problem of
+// at most HUBF_MAX_DIM amplitudes
+bool hub_fused(const ecut_sectors *s) {
+    return s->kernel == 1 && s->hub6_ok && s->dim <= HUBF_MAX_DIM && (s->tune.variant == 6 || default_tuning(s->tune));
+}
+
+// The default tuning above HUBF_MAX_DIM: the two-pass kernels, which beat the
+// one-pass class tiles at every size measured (12-site chain 16.4 against 22.4
+// us, 14-site 180 against 325, 14-site ring 186 against 481); vectors past the
+// last-level cache take the class tiles for the right pass where they exist
+// (16-site chain: 2.2 against 2.8 ms).
+ApplyTuning hub_tuning(const ecut_sectors *s) {
+    if (s->kernel != 1 || !default_tuning(s->tune) || !s->hub6_ok) return s->tune;
+    if (s->hub3_ok && s->dim >= STREAM_STORE_MIN) return ApplyTuning{8, 8, 0, 7, 0};
+    return ApplyTuning{0, 8, 0, 6, 0};
 }
 
 int32_t max_tile_elems(const ecut_sectors *s) {
@@ -475,19 +514,40 @@ int32_t rows_split_of(const ecut_sectors *s) {
 // takes `grid` rows of the level order (0 = HUBU_ROWS) per item over slabs of
 // 64 lanes x 1 or 2 columns; the right pass `tile` rows (0 = HUBD_ROWS) x
 // HUBD_THREADS columns per item.
-static int32_t hub6_rows_d(const ecut_sectors *s) { return s->tune.tile > 0 ? s->tune.tile : HUBD_ROWS; }
+static int32_t hub6_rows_d(const ApplyTuning &T) { return T.tile > 0 ? T.tile : HUBD_ROWS; }
 
 void hub6_shape(const ecut_sectors *s, HubUArgs &U, HubDArgs &D) {
     const int32_t dR = s->blocks[0].d_r, nr = s->blocks[0].d_l;
     const int32_t cols = (dR % 2 == 0 ? 2 : 1) * 64;
-    U.rows_per_item = s->tune.grid > 0 ? s->tune.grid : HUBU_ROWS;
+    const ApplyTuning T = hub_tuning(s);
+    U.rows_per_item = T.grid > 0 ? T.grid : HUBU_ROWS;
     U.n_rgroups = (nr + U.rows_per_item - 1) / U.rows_per_item;
-    U.slab_ways = (s->tune.variant == 7 && s->tune.tile > 0) ? s->tune.tile : 1;
+    U.slab_ways = (T.variant == 7 && T.tile > 0) ? T.tile : 1;
     U.n_slabs = ((dR + cols - 1) / cols + U.slab_ways - 1) / U.slab_ways;
     U.n_items = U.n_slabs * U.n_rgroups;
-    D.rows_per_item = hub6_rows_d(s);
+    // the fused kernel takes single rows: the shorter the items, the more of
+    // them to fill the device
+    D.rows_per_item = hub_fused(s) ? 1 : hub6_rows_d(T);
     D.n_chunks = (dR + HUBD_THREADS - 1) / HUBD_THREADS;
     D.n_items = ((nr + D.rows_per_item - 1) / D.rows_per_item) * D.n_chunks;
+}
+
+static HubFArgs hub_fused_args(const ecut_sectors *s, const ProblemDev &P) {
+    HubUArgs U = s->h6u;
+    HubFArgs F{};
+    F.d = s->h6d;
+    hub6_shape(s, U, F.d);
+    F.d.x = P.x;
+    F.d.y = P.y;
+    F.d.z = P.z;
+    F.d.partials = P.partials;
+    F.d.xscale = P.xscale;
+    F.d.zcoef = P.zcoef;
+    F.d.dscale = P.dscale;
+    F.hl_ptr = P.hl_ptr;
+    F.hl_col = P.hl_col;
+    F.hl_val = P.hl_val;
+    return F;
 }
 
 // One application on a stream, with the Lanczos epilogue fields of `P`
@@ -497,8 +557,10 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
     ecut_status rs = device_res(&dev, nullptr, &n_cu);
     if (rs != ECUT_OK) return rs;
     hipError_t e;
-    if (s->kernel == 1) {
-        const ApplyTuning &T = s->tune;
+    if (hub_fused(s)) {
+        e = launch_hubF(hub_fused_args(s, P), st);
+    } else if (s->kernel == 1) {
+        const ApplyTuning T = hub_tuning(s);
         const int n_xcd = T.n_xcd > 0 ? T.n_xcd : 8;
         if ((T.variant == 0 || T.variant == 3) && s->hub3_ok) {
             const size_t lds = hub3_lds_bytes(s);
@@ -579,7 +641,7 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
             const int grid = T.grid > 0 ? T.grid : n_cu;
             e = launch_hub(s, P, s->dev_row_order, s->blocks[0].d_l, grid, n_xcd, st);
         }
-    } else if (s->sp2_ok && s->tune.variant == 2) {
+    } else if (two_pass_rows(s, s->tune)) {
         SpinLArgs L{};
         L.x = P.x;
         L.y = P.y;
@@ -595,6 +657,8 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
         L.rows_per_item = s->tune.grid > 0 ? s->tune.grid : HUBU_ROWS;
         e = launch_spin2(L, P, s->dev_sp_tab, s->dev_sp_tbase, s->dev_items, s->sp_n_one, (int)s->items.size(),
                          s->max_d_r, s->tune.n_xcd == 1 ? 1 : 8, s->hub_spatial, st);
+    } else if (P.flat) {
+        e = launch_flat(P, st);
     } else if (P.spin_ok) {
         int grid = s->tune.grid;
         if (s->tune.order == 1) grid = std::max(8, ((grid > 0 ? grid : 2048) / 8) * 8);   // keeps chunk c on XCD c
@@ -606,13 +670,18 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
     return ECUT_OK;
 }
 
-bool own_launch(const ecut_sectors *s) { return s->kernel == 1 || (s->sp2_ok && s->tune.variant == 2); }
+bool own_launch(const ecut_sectors *s) { return s->kernel == 1 || two_pass_rows(s, s->tune); }
 
 bool hub6_batchable(const ecut_sectors *s) {
-    return s->kernel == 1 && s->hub6_ok && s->tune.variant == 6 && s->h6_maxq <= HUBD_BATCH_SLOTS;
+    return s->kernel == 1 && s->hub6_ok && hub_tuning(s).variant == 6 && s->h6_maxq <= HUBD_BATCH_SLOTS;
 }
 
 void hub6_batch_add(HubBatch &b, const ecut_sectors *s, const ProblemDev &P) {
+    if (hub_fused(s)) {
+        b.f.push_back(hub_fused_args(s, P));
+        b.off_f.push_back(b.off_f.back() + b.f.back().d.n_items);
+        return;
+    }
     HubUArgs U = s->h6u;
     HubDArgs D = s->h6d;
     hub6_shape(s, U, D);
@@ -636,7 +705,9 @@ HubBatchLayout hub6_batch_layout(const HubBatch &b, size_t base) {
     l.d = al(l.u + b.u.size() * sizeof(HubUArgs));
     l.off_u = al(l.d + b.d.size() * sizeof(HubDArgs));
     l.off_d = al(l.off_u + b.off_u.size() * sizeof(int32_t));
-    l.bytes = l.off_d + b.off_d.size() * sizeof(int32_t);
+    l.f = al(l.off_d + b.off_d.size() * sizeof(int32_t));
+    l.off_f = al(l.f + b.f.size() * sizeof(HubFArgs));
+    l.bytes = l.off_f + b.off_f.size() * sizeof(int32_t);
     return l;
 }
 
@@ -645,28 +716,35 @@ void hub6_batch_pack(const HubBatch &b, const HubBatchLayout &l, char *buf) {
     std::memcpy(buf + l.d, b.d.data(), b.d.size() * sizeof(HubDArgs));
     std::memcpy(buf + l.off_u, b.off_u.data(), b.off_u.size() * sizeof(int32_t));
     std::memcpy(buf + l.off_d, b.off_d.data(), b.off_d.size() * sizeof(int32_t));
+    std::memcpy(buf + l.f, b.f.data(), b.f.size() * sizeof(HubFArgs));
+    std::memcpy(buf + l.off_f, b.off_f.data(), b.off_f.size() * sizeof(int32_t));
 }
 
 hipError_t hub6_batch_launch(const HubBatch &b, const HubBatchLayout &l, const void *dev, hipStream_t st) {
     if (b.empty()) return hipSuccess;
     const char *d = (const char *)dev;
+    const hipError_t e = launch_hubF_batch((const HubFArgs *)(d + l.f), (const int32_t *)(d + l.off_f), (int)b.f.size(),
+                                           b.off_f.back(), st);
+    if (e != hipSuccess) return e;
     return launch_hub6_batch((const HubUArgs *)(d + l.u), (const HubDArgs *)(d + l.d), (const int32_t *)(d + l.off_u),
                              (const int32_t *)(d + l.off_d), (int)b.u.size(), b.off_u.back(), b.off_d.back(), st);
 }
 
 // number of partial slots the apply kernel writes
 int32_t apply_partial_slots(const ecut_sectors *s) {
-    if (s->kernel != 1) return s->item_slots * ((s->spin_ok || s->tune.variant == 2) ? 1 : s->prob.rows_split);
-    if (s->tune.variant == 5 && s->hubseg_ok) return s->hs_n_slots;
-    if (s->tune.variant == 7 && s->hub3_ok) return (int32_t)s->hub_items.size();
-    if (s->tune.variant == 6 && s->hub6_ok) {
+    if (flat_on(s)) return s->prob.flat_groups;
+    if (s->kernel != 1) return s->item_slots * ((s->spin_ok || two_pass_rows(s, s->tune)) ? 1 : s->prob.rows_split);
+    const ApplyTuning T = hub_tuning(s);
+    if (T.variant == 5 && s->hubseg_ok) return s->hs_n_slots;
+    if (T.variant == 7 && s->hub3_ok) return (int32_t)s->hub_items.size();
+    if (T.variant == 6 && s->hub6_ok) {
         HubUArgs U{};
         HubDArgs D{};
         hub6_shape(s, U, D);
         return D.n_items;
     }
-    const bool tiles = ((s->tune.variant == 0 || s->tune.variant == 3) && (s->hub3_ok || s->hub2_ok)) ||
-                       (s->tune.variant == 2 && s->hub2_ok);   // variants 1 and 4: one slot per row
+    const bool tiles = ((T.variant == 0 || T.variant == 3) && (s->hub3_ok || s->hub2_ok)) ||
+                       (T.variant == 2 && s->hub2_ok);   // variants 1 and 4: one slot per row
     return tiles ? (int32_t)s->hub_items.size() : s->blocks[0].d_l;
 }
 
@@ -678,7 +756,8 @@ int32_t apply_partial_slots_max(const ecut_sectors *s) {
                                                                                     (int32_t)s->hub_items.size()),
                                                                   s->hubseg_ok ? s->hs_n_slots : 0),
                                               h6)
-                          : std::max(s->item_slots_cap, s->item_slots) * std::max(1, s->prob.rows_split);
+                          : std::max(std::max(s->item_slots_cap, s->item_slots) * std::max(1, s->prob.rows_split),
+                                     s->flat_base.empty() ? 0 : s->flat_base.back());
 }
 
 // ---------------------------------------------------------------- staging buffers
@@ -741,7 +820,7 @@ void Staging::release() {
 }
 
 void make_rows_batch(const std::vector<ProblemDev> &probs, const std::vector<ItemDev> &items_in,
-                     const std::vector<int32_t> &tiles, RowsBatch &b) {
+                     const std::vector<int32_t> &tiles, const std::vector<char> &flat, RowsBatch &b) {
     // the spin kernel takes the problems whose tuning selects it (as their
     // own ecut_apply_H does), the generic row kernel the others; the order
     // of the queue is kept within each group
@@ -763,10 +842,27 @@ void make_rows_batch(const std::vector<ProblemDev> &probs, const std::vector<Ite
             b.rows_split = std::max(b.rows_split, probs[it.prob].rows_split);
         }
     b.n_items = (int)items.size();
+    for (size_t k = 0; k < flat.size(); ++k) {
+        if (!flat[k] || probs[k].flat_groups <= 0) continue;
+        const int t = probs[k].flat == 2;
+        if (b.flat_off[t].empty()) b.flat_off[t].push_back(0);
+        b.flat_idx[t].push_back((int32_t)k);
+        b.flat_off[t].push_back(b.flat_off[t].back() + probs[k].flat_groups);
+    }
     b.pb = (probs.size() * sizeof(ProblemDev) + 255) & ~(size_t)255;
-    b.buf.assign(b.pb + items.size() * sizeof(ItemDev), 0);
+    size_t bytes = b.pb + items.size() * sizeof(ItemDev);
+    for (int t = 0; t < 2; ++t) {
+        b.o_flat[t] = bytes = (bytes + 15) & ~(size_t)15;
+        bytes += (b.flat_idx[t].size() + b.flat_off[t].size()) * sizeof(int32_t);
+    }
+    b.buf.assign(bytes, 0);
     std::memcpy(b.buf.data(), probs.data(), probs.size() * sizeof(ProblemDev));
     std::memcpy(b.buf.data() + b.pb, items.data(), items.size() * sizeof(ItemDev));
+    for (int t = 0; t < 2; ++t) {
+        char *o = b.buf.data() + b.o_flat[t];
+        std::memcpy(o, b.flat_idx[t].data(), b.flat_idx[t].size() * sizeof(int32_t));
+        std::memcpy(o + b.flat_idx[t].size() * sizeof(int32_t), b.flat_off[t].data(), b.flat_off[t].size() * sizeof(int32_t));
+    }
     if (b.first_spin >= 0) b.spin_single = probs[b.first_spin];
     if (!probs.empty()) b.rows_single = probs[0];
 }
@@ -778,27 +874,12 @@ hipError_t launch_rows_batch(const RowsBatch &b, const void *dev, hipStream_t st
     if (b.n_spin > 0) e = launch_spin(probs_d, b.spin_single, items_d, b.n_spin, b.spin_tile, b.spin_src, 0, st);
     if (e == hipSuccess && b.n_spin < b.n_items)
         e = launch_rows(probs_d, b.rows_single, items_d + b.n_spin, b.n_items - b.n_spin, b.rows_tile, b.rows_split, st);
+    for (int t = 0; t < 2 && e == hipSuccess; ++t) {
+        const int n = (int)b.flat_idx[t].size();
+        const int32_t *idx = (const int32_t *)((const char *)dev + b.o_flat[t]);
+        if (n > 0) e = launch_flat_batch(probs_d, idx, idx + n, n, b.flat_off[t].back(), t == 1, st);
+    }
     return e;
-}
-
-ecut_status batch_launch_rows(const std::vector<ProblemDev> &probs, const std::vector<ItemDev> &items_in,
-                              const std::vector<int32_t> &tiles, hipStream_t st) {
-    static thread_local Staging S;
-    RowsBatch b;
-    make_rows_batch(probs, items_in, tiles, b);
-    ecut_status rs = S.reserve(b.buf.size());
-    if (rs != ECUT_OK) return rs;
-    rs = S.wait();
-    if (rs != ECUT_OK) return rs;
-    std::memcpy(S.host, b.buf.data(), b.buf.size());
-    hipError_t e = hipMemcpyAsync(S.dev, S.host, b.buf.size(), hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(batch descriptors)");
-    e = launch_rows_batch(b, S.dev, st);
-    if (e != hipSuccess) return hip_fail(e, "kernel launch (batched apply_H)");
-    e = hipEventRecord(S.ev, st);
-    if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
-    S.pending = true;
-    return ECUT_OK;
 }
 
 ecut_status make_batch_plan(int32_t n, const ecut_sectors *const *s, const double *const *psi_d,
@@ -808,7 +889,9 @@ ecut_status make_batch_plan(int32_t n, const ecut_sectors *const *s, const doubl
     if (n == 0) return ECUT_OK;
     std::vector<ProblemDev> probs(n);
     std::vector<ItemDev> items;
-    std::vector<int32_t> tiles(n);
+    std::vector<int32_t> tiles(n, 0);
+    std::vector<char> flat(n, 0);   // problems on the flat kernel
+    bool any_flat = false;
     for (int32_t k = 0; k < n; ++k) {
         ecut_status st = check_dev(s[k]);
         if (st != ECUT_OK) return st;
@@ -822,6 +905,11 @@ ecut_status make_batch_plan(int32_t n, const ecut_sectors *const *s, const doubl
         probs[k].xscale = 1.0;
         probs[k].zcoef = 0.0;
         probs[k].partials = nullptr;
+        if (probs[k].flat) {
+            flat[k] = 1;
+            any_flat = true;
+            continue;
+        }
         tiles[k] = max_tile_elems(s[k]);
         if (hub6_batchable(s[k])) {
             hub6_batch_add(pl.hub, s[k], probs[k]);   // one merged launch per pass for all of them
@@ -832,14 +920,14 @@ ecut_status make_batch_plan(int32_t n, const ecut_sectors *const *s, const doubl
             for (const ItemDev &it : s[k]->items) items.push_back(ItemDev{k, it.block, it.row0, it.row1, it.slot, 0});
         }
     }
-    if (!items.empty()) {
+    if (!items.empty() || any_flat) {
         // one queue over all problems, largest tiles first (stable: problem order breaks ties)
         std::stable_sort(items.begin(), items.end(), [&](const ItemDev &a, const ItemDev &b) {
             const int64_t wa = (int64_t)(a.row1 - a.row0) * s[a.prob]->blocks[a.block].d_r;
             const int64_t wb = (int64_t)(b.row1 - b.row0) * s[b.prob]->blocks[b.block].d_r;
             return wa > wb;
         });
-        make_rows_batch(probs, items, tiles, pl.rows);
+        make_rows_batch(probs, items, tiles, flat, pl.rows);
         pl.has_rows = true;
         pl.buf = pl.rows.buf;
     }

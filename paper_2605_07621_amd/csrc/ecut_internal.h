@@ -226,6 +226,15 @@ struct HubDArgs {
     int32_t n_chunks, n_items, n_slots, pad_;
 };
 
+// Both operators of a Hubbard problem in one pass (the fused kernel of short
+// vectors): the right pass's arguments and the left operator's CSR, rows in
+// the block's own order (at most 32 entries each).
+struct HubFArgs {
+    HubDArgs d;
+    const int32_t *hl_ptr, *hl_col;
+    const double *hl_val;
+};
+
 // c+ / c of one (site, spin) mode between two Hubbard up/down sectors: each
 // destination element (a', c') reads its source element, or is 0.
 struct CdagArgs {
@@ -314,6 +323,14 @@ struct ProblemDev {
     const double *xdl;
     int32_t n_xr;
     int32_t xr_site[XR_MAX];
+    // flat row kernel (0 = another kernel runs this problem, 1 = spin cut,
+    // 2 = spatial Hubbard cut): thread per amplitude, source columns from the
+    // two-pass kernels' tables
+    int32_t flat;
+    int32_t flat_groups;         // work groups (and partial-sum slots)
+    const int32_t *flat_base;    // [n_blocks + 1] first group of each block
+    const uint16_t *sp_tab;      // source-column tables (ecut_sectors::sp_tab)
+    const int64_t *sp_tbase;
     int32_t rows_split;          // generic row kernel: work groups per item (slices of its elements)
     int32_t xr_lo, xr_contig;    // xr_contig: the sites are xr_lo, xr_lo + 1, ... (one bit field of r)
     int64_t dim;
@@ -433,6 +450,7 @@ struct ecut_sectors {
     std::vector<int64_t> sp_tbase;
     const uint16_t *dev_sp_tab = nullptr;
     const int64_t *dev_sp_tbase = nullptr;
+    std::vector<int32_t> flat_base;          // ProblemDev::flat_base (empty: the flat kernel never runs this problem)
     std::vector<ecut::SpinLBlock> sp_lblocks;
     int32_t sp_n_one = 0;
     int32_t *dev_sp_rows = nullptr;
@@ -477,6 +495,14 @@ int32_t processing_csr(const ecut_sectors *s, const std::vector<int32_t> &order,
 // left-pass block table of the two-pass spin kernels
 void spin_left_blocks(const ecut_sectors *s, int32_t rows_per_item, std::vector<SpinLBlock> &out);
 void release_device(ecut_sectors *s);
+// the problem runs the flat row kernel (spin, spatial Hubbard) under its tuning
+bool flat_on(const ecut_sectors *s);
+// a spin or spatial Hubbard problem runs the two-pass row kernels under T
+bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T);
+// the Hubbard up/down problem runs the fused one-pass kernel under its tuning
+bool hub_fused(const ecut_sectors *s);
+// the tuning the Hubbard launches follow: the handle's, or what its default selects by size
+ApplyTuning hub_tuning(const ecut_sectors *s);
 // item counts of the two-pass kernels (variant 6) for the handle's tuning
 void hub6_shape(const ecut_sectors *s, HubUArgs &U, HubDArgs &D);
 }  // namespace ecut

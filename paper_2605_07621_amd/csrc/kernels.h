@@ -48,6 +48,9 @@ constexpr int HUBD_NB = 8;                   // in-row gathers issued together p
 constexpr int HUBD_MAX_SLOTS = 32;           // bonds of the down-spin hop table (held in registers)
 constexpr int HUBD_BATCH_SLOTS = 16;         // the same in the batched launch (problems with more launch alone)
 constexpr int HUBD_ROWS = 4;                 // default rows per right-operator item
+constexpr int FLAT_THREADS = 256;            // flat row kernel: one amplitude per thread
+constexpr int64_t FLAT_MAX_DIM = (int64_t)1 << 20;        // longest vectors it takes: the two-pass kernels beat it above
+constexpr int64_t HUBF_MAX_DIM = (int64_t)1 << 18;        // the same for the fused Hubbard kernel
 constexpr int VEC_THREADS = 256;
 constexpr int64_t VEC_CHUNK = 8192;          // elements per reduction partial
 constexpr int64_t CGS_CHUNK_MIN = 1024;      // shortest chunk of the reorthogonalisation kernels
@@ -135,6 +138,15 @@ hipError_t launch_perm_cols(const int32_t *col_d, int64_t n_rows, int dR, const 
 hipError_t launch_perm(const ecut_sectors *s, const uint64_t *binom_d, const BlockDev *blocks_d, const double *in,
                        double *out, bool to_bip, hipStream_t st);
 hipError_t launch_cdag(const CdagArgs &A, hipStream_t st);
+// flat row kernel: one problem, or the problems idx[0 .. n_probs) of probs_d
+// (fermion: all of them spatial Hubbard cuts, else spin cuts), off[k] the first
+// group of problem k, off[n_probs] = n_groups
+hipError_t launch_flat(const ProblemDev &P, hipStream_t st);
+hipError_t launch_flat_batch(const ProblemDev *probs_d, const int32_t *idx, const int32_t *off, int n_probs,
+                             int n_groups, bool fermion, hipStream_t st);
+// fused one-pass Hubbard kernel, alone and over the items of several problems
+hipError_t launch_hubF(const HubFArgs &F, hipStream_t st);
+hipError_t launch_hubF_batch(const HubFArgs *probs, const int32_t *off, int n_probs, int n_items, hipStream_t st);
 // two-pass spin kernels: left pass over slab items, then the one-row items
 // [0, n_one) and the several-row items [n_one, n_items) without the left operator
 hipError_t launch_spin2(const SpinLArgs &L, const ProblemDev &P, const uint16_t *tab, const int64_t *tbase,

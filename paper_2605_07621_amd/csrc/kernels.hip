@@ -1316,6 +1316,179 @@ __global__ __launch_bounds__(ONE ? NT1 : SPIN_MANY_THREADS, (ONE && NT1 == SPIN_
 }
 
 // ------------------------------------------------------------------------
+// Flat row kernel of spin cuts (FERM: of spatial Hubbard cuts): one amplitude
+// per thread, everything gathered from global memory (L1 and L2 hold the rows
+// of a group), no LDS, no barrier but the partial sum's.  Work groups take
+// FLAT_THREADS consecutive amplitudes of one block, the groups of an XCD a
+// contiguous run.
+// The one-pass spin kernel stages whole rows or row tiles for 512 or 256
+// threads: on short rows most of its threads idle, on short vectors it has too
+// few groups, and each group first loads the ranking tables and waits at
+// several barriers.  Here every load of an amplitude depends on at most three
+// others.  The sums run in the same order (left operator, cross terms; the
+// right operator apart; then the diagonal), so the vector is the same bit for
+// bit.  XXZ chains, one-pass spin kernel -> this one: 16 sites 17.9 -> 7.6 us
+// (the host's call rate), 20 sites 22.4 -> 8.1, 22 sites 60 -> 22.5.  Past
+// about 2^20 amplitudes the left operator's rows no longer come from L2 and
+// the two-pass kernels' slab order wins: 22 sites 22.5 against 27 us, 23 sites
+// (1.35M) 41 against 35.5, 24 sites 76 against 53; spatial Hubbard cut, 12
+// sites 29.5 against 44.6, 13 sites (2.9M) 87 against 74.
+// ------------------------------------------------------------------------
+template <bool FERM>
+__device__ __forceinline__ void flat_group(const ProblemDev &P, int g, double *red) {
+    const double2 ef = epi_factors(P.dscale, P.xscale, P.zcoef);
+    int lo = 0, hi = P.n_blocks - 1;   // the last block with flat_base <= g (empty blocks own no group)
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (P.flat_base[mid] <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    const BlockDev B = P.blocks[lo];
+    const uint16_t *__restrict__ tabR = P.sp_tab + P.sp_tbase[2 * lo];
+    const uint16_t *__restrict__ tabX = P.sp_tab + P.sp_tbase[2 * lo + 1];
+    const int dR = B.d_r, n_flip = P.n_rflip;
+    const double inv_d = 1.0 / (double)dR;
+    const double *__restrict__ xblk = P.x + B.offset;
+    const int E = (g - P.flat_base[lo]) * FLAT_THREADS + (int)threadIdx.x;
+    double part = 0.0;
+    if (E < B.d_l * B.d_r) {
+        const int l = (int)(((double)E + 0.5) * inv_d);   // exact: E < 2^31, the quotient's error far below 1 / d_r
+        const int r = E - l * dR;
+        const int gl = B.lbase + l, gr = B.rbase + r;
+        const double *__restrict__ xrow = xblk + (int64_t)l * dR;
+        const uint64_t *__restrict__ tw = (const uint64_t *)tabR + r;
+        // the first eight right terms' entries go out with the row's own loads
+        uint64_t t0 = n_flip > 0 ? tw[0] : 0, t1 = n_flip > 4 ? tw[dR] : 0;
+        const uint32_t lw = P.lwords[gl], w = P.rwords[gr];
+        const int q0 = P.hl_ptr[gl], q1 = P.hl_ptr[gl + 1];
+        const double x0 = xrow[r];
+        double dg = P.diag_l[gl] + P.diag_r[gr];
+        // right operator: four terms' source columns per table word, in term order
+        double ra = 0.0;
+        for (int f0 = 0; f0 < n_flip; f0 += 8) {
+            double v[8];
+            bool on[8], neg[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t s = (uint32_t)((u < 4 ? t0 : t1) >> (16 * (u & 3))) & 0xffffu;
+                on[u] = f0 + u < n_flip && s != (FERM ? 0xffffu : 8u * (uint32_t)dR);
+                neg[u] = FERM && (s & 0x8000u);
+                const uint32_t off = FERM ? 8u * (s & 0x7fffu) : s;   // a spin cut's entry is a byte offset
+                v[u] = on[u] ? *(const double *)((const char *)xrow + off) : 0.0;
+            }
+            if (f0 + 8 < n_flip) t0 = tw[(int64_t)(f0 / 4 + 2) * dR];
+            if (f0 + 12 < n_flip) t1 = tw[(int64_t)(f0 / 4 + 3) * dR];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (on[u]) ra += (neg[u] ? -P.rflip_coef[f0 + u] : P.rflip_coef[f0 + u]) * v[u];
+        }
+        // left operator: the same column of the block's neighbour rows
+        const double *__restrict__ xcol = xblk + r;
+        double acc = csr_add(0.0, q0, q1, P.hl_col, P.hl_val, [&](int c) { return xcol[(int64_t)c * dR]; });
+        // cross terms: one element of a row of the neighbouring block
+        for (int k = 0; k < P.n_xbond; ++k) {
+            const XBondDev X = P.xbond[k];
+            const uint32_t bl = (lw >> X.li) & 1u;
+            if (((w >> X.rj) & 1u) == bl) continue;
+            const int src = FERM && X.label ? (bl ? B.blk_l2minus : B.blk_l2plus) : (bl ? B.blk_lminus : B.blk_lplus);
+            if (src < 0) continue;
+            int lp = P.maps[(bl ? X.lmap_del : X.lmap_ins) + gl];
+            if (lp < 0) continue;
+            const uint32_t e = tabX[(int64_t)k * dR + r];
+            const BlockDev *__restrict__ S = P.blocks + src;
+            const int sd = S->d_r;
+            double c = X.coef;
+            if constexpr (FERM) {
+                if (lp & 1) c = -c;
+                if (e & 0x8000u) c = -c;
+                lp >>= 1;
+            }
+            // a spin cut's entry is the row's zero slot minus the column, in bytes
+            const int col = FERM ? (int)(e & 0x7fffu) : sd - (int)(e >> 3);
+            acc += c * P.x[S->offset + (int64_t)lp * sd + col];
+        }
+        if (!FERM && P.n_xr > 0) {
+            double t = 0.0;
+            for (int i = 0; i < P.n_xr; ++i) {
+                const double h = P.xdl[(int64_t)gl * P.n_xr + i];
+                t += ((w >> P.xr_site[i]) & 1u) ? h : -h;
+            }
+            dg += t;
+        } else {
+            for (int i = 0; i < P.n_xdiag; ++i) {
+                const XDiagDev X = P.xdiag[i];
+                if constexpr (FERM) {   // densities of the two sites (V n_i n_j)
+                    double fl = (double)((lw >> X.li) & 1u), fr = (double)((w >> X.rj) & 1u);
+                    if (X.li2 >= 0) fl += (double)((lw >> X.li2) & 1u);
+                    if (X.rj2 >= 0) fr += (double)((w >> X.rj2) & 1u);
+                    if (X.spin_form) {
+                        fl -= 0.5;
+                        fr -= 0.5;
+                    }
+                    dg += X.coef * fl * fr;
+                } else {
+                    dg += X.coef * ((double)((lw >> X.li) & 1u) - 0.5) * ((double)((w >> X.rj) & 1u) - 0.5);
+                }
+            }
+        }
+        double yv = ef.x * (acc + ra + dg * x0);
+        const int64_t gi = B.offset + E;
+        if (P.z) yv -= ef.y * P.z[gi];
+        P.y[gi] = yv;
+        part += x0 * yv;
+    }
+    if (P.partials) {
+        const double sum = block_sum(part, red);
+        if (threadIdx.x == 0) P.partials[g] = sum;
+    }
+}
+
+template <bool FERM>
+__global__ __launch_bounds__(FLAT_THREADS) void k_flat(const ProblemDev P, int per_xcd) {
+    __shared__ double red[FLAT_THREADS / 64];
+    const int g = xcd_item(8, per_xcd);
+    if (g >= P.flat_groups) return;   // uniform over the group
+    flat_group<FERM>(P, g, red);
+}
+
+__device__ __forceinline__ int batch_problem(const int32_t *__restrict__ off, int n_probs, int it);
+
+// the same over the groups of several problems (problem idx[k] owns groups
+// off[k] .. off[k + 1] - 1), each group as in its problem's own launch
+template <bool FERM>
+__global__ __launch_bounds__(FLAT_THREADS) void k_flat_batch(const ProblemDev *__restrict__ probs,
+                                                             const int32_t *__restrict__ idx,
+                                                             const int32_t *__restrict__ off, int n_probs, int n_groups,
+                                                             int per_xcd) {
+    __shared__ double red[FLAT_THREADS / 64];
+    const int g = xcd_item(8, per_xcd);
+    if (g >= n_groups) return;
+    const int k = batch_problem(off, n_probs, g);
+    flat_group<FERM>(probs[idx[k]], g - off[k], red);
+}
+
+hipError_t launch_flat(const ProblemDev &P, hipStream_t st) {
+    if (P.flat_groups <= 0) return hipSuccess;
+    const int per = (P.flat_groups + 7) / 8;
+    if (P.flat == 2) hipLaunchKernelGGL(k_flat<true>, dim3(8 * per), dim3(FLAT_THREADS), 0, st, P, per);
+    else hipLaunchKernelGGL(k_flat<false>, dim3(8 * per), dim3(FLAT_THREADS), 0, st, P, per);
+    return hipGetLastError();
+}
+
+hipError_t launch_flat_batch(const ProblemDev *probs_d, const int32_t *idx, const int32_t *off, int n_probs,
+                             int n_groups, bool fermion, hipStream_t st) {
+    if (n_groups <= 0) return hipSuccess;
+    const int per = (n_groups + 7) / 8;
+    if (fermion)
+        hipLaunchKernelGGL(k_flat_batch<true>, dim3(8 * per), dim3(FLAT_THREADS), 0, st, probs_d, idx, off, n_probs,
+                           n_groups, per);
+    else
+        hipLaunchKernelGGL(k_flat_batch<false>, dim3(8 * per), dim3(FLAT_THREADS), 0, st, probs_d, idx, off, n_probs,
+                           n_groups, per);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------
 // Left (up-spin) operator over column slabs: y[a, S] = sum_a' H_up[a,a'] x[a', S]
 // for a slab S of SLAB_W consecutive columns.  Every XCD walks a contiguous
 // range of slabs, all its work groups on the same slab at the same time (each
@@ -2082,6 +2255,112 @@ __global__ __launch_bounds__(HUBD_THREADS) void k_hubD_batch(const HubDArgs *__r
     const HubDArgs A = probs[p];
     if (A.val == nullptr) hubD_item<HUBD_BATCH_SLOTS, true, false>(A, it - off[p], red);
     else hubD_item<HUBD_BATCH_SLOTS, false, false>(A, it - off[p], red);
+}
+
+// ------------------------------------------------------------------------
+// Fused Hubbard kernel (short vectors): both operators, diagonal and epilogue
+// of an item (one row x HUBD_THREADS columns) in one pass.  The left operator
+// gathers the neighbour rows at the thread's column (row indices lane-parallel
+// and read back with readlane, as in the left pass), the right operator the
+// source columns, as in the right pass; the left sum stays in a register
+// instead of making a round trip through y, and there is one launch.  Both
+// gathers rest on L2, so this is for short vectors: chains, two passes -> one:
+// 10 sites 10.0 -> 7.6 us (the host's call rate), 11 sites (213,444) 10.0 ->
+// 7.5, 12 sites (853,776) 16.4 both, 13 sites 37 against 41; rings (signed
+// hops), 12 sites 20 against 30.  The terms are summed as there: left operator,
+// right operator in slot order, diagonal.
+// ------------------------------------------------------------------------
+template <int NS, bool UNIF>
+__device__ __forceinline__ void hubF_item(const HubFArgs &F, int it, double *red) {
+    const HubDArgs &A = F.d;
+    const double2 ef = epi_factors(A.dscale, A.xscale, A.zcoef);
+    const int a = it / A.n_chunks;
+    const int c = (it - a * A.n_chunks) * HUBD_THREADS + (int)threadIdx.x;
+    const bool ok = c < A.dR;
+    const int cl = ok ? c : 0;   // lanes past the row end gather column 0; only their store is skipped
+    const int lane = threadIdx.x & 63;
+    const int64_t dR = A.dR;
+    const int q0 = F.hl_ptr[a], deg = F.hl_ptr[a + 1] - q0;
+    const int colv = lane < deg ? F.hl_col[q0 + lane] : 0;
+    const int64_t base = (int64_t)a * dR;
+    const double *__restrict__ xr = A.x + base;
+    const double *__restrict__ xc = A.x + cl;
+    const double x0 = xr[cl];
+    const double zv = A.z ? A.z[base + cl] : 0.0;
+    int src[NS];
+    double v[NS], dn = 0.0, up = 0.0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) src[k] = (ok && k < A.n_slots) ? A.col[(int64_t)k * dR + c] : -1;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) v[k] = src[k] >= 0 ? xr[src[k]] : 0.0;
+    for (int j = 0; j < deg; j += HUBU_NB) {
+        double w[HUBU_NB];
+#pragma unroll
+        for (int u = 0; u < HUBU_NB; ++u)
+            w[u] = j + u < deg ? xc[(int64_t)__builtin_amdgcn_readlane(colv, j + u) * dR] : 0.0;
+#pragma unroll
+        for (int u = 0; u < HUBU_NB; ++u)
+            if (j + u < deg) up += UNIF ? w[u] : F.hl_val[q0 + j + u] * w[u];
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        if constexpr (UNIF) dn += v[k];
+        else if (src[k] >= 0) dn += A.val[(int64_t)k * dR + c] * v[k];
+    }
+    const uint32_t both = A.lwords[a] & A.rwords[cl];
+    double dg;
+    if (A.uniform_u) {
+        dg = A.u0 * (double)__popc(both);
+    } else {
+        dg = 0.0;
+        for (uint32_t m = both; m; m &= m - 1u) dg += A.u[__ffs(m) - 1];
+    }
+    double y = UNIF ? ef.x * (A.hop * up + A.hop * dn + dg * x0) : ef.x * (up + dn + dg * x0);
+    if (A.z) y -= ef.y * zv;
+    if (ok) A.y[base + c] = y;
+    if (A.partials) {
+        const double sum = block_sum(ok ? x0 * y : 0.0, red);
+        if (threadIdx.x == 0) A.partials[it] = sum;
+    }
+}
+
+template <int NS, bool UNIF>
+__global__ __launch_bounds__(HUBD_THREADS) void k_hubF(const HubFArgs F, int per_xcd) {
+    __shared__ double red[HUBD_THREADS / 64];
+    const int it = xcd_item(8, per_xcd);
+    if (it >= F.d.n_items) return;   // uniform over the block
+    hubF_item<NS, UNIF>(F, it, red);
+}
+
+__global__ __launch_bounds__(HUBD_THREADS) void k_hubF_batch(const HubFArgs *__restrict__ probs,
+                                                             const int32_t *__restrict__ off, int n_probs,
+                                                             int n_items, int per_xcd) {
+    __shared__ double red[HUBD_THREADS / 64];
+    const int it = xcd_item(8, per_xcd);
+    if (it >= n_items) return;
+    const int p = batch_problem(off, n_probs, it);
+    const HubFArgs F = probs[p];
+    if (F.d.val == nullptr) hubF_item<HUBD_BATCH_SLOTS, true>(F, it - off[p], red);
+    else hubF_item<HUBD_BATCH_SLOTS, false>(F, it - off[p], red);
+}
+
+hipError_t launch_hubF(const HubFArgs &F, hipStream_t st) {
+    if (F.d.n_items <= 0) return hipSuccess;
+    const int per = (F.d.n_items + 7) / 8;
+    const bool unif = F.d.val == nullptr;
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(8 * per), dim3(HUBD_THREADS), 0, st, F, per); };
+    if (F.d.n_slots <= 8) unif ? go(k_hubF<8, true>) : go(k_hubF<8, false>);
+    else if (F.d.n_slots <= 16) unif ? go(k_hubF<16, true>) : go(k_hubF<16, false>);
+    else if (F.d.n_slots <= HUBD_MAX_SLOTS) unif ? go(k_hubF<HUBD_MAX_SLOTS, true>) : go(k_hubF<HUBD_MAX_SLOTS, false>);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_hubF_batch(const HubFArgs *probs, const int32_t *off, int n_probs, int n_items, hipStream_t st) {
+    if (n_probs <= 0 || n_items <= 0) return hipSuccess;
+    const int per = (n_items + 7) / 8;
+    hipLaunchKernelGGL(k_hubF_batch, dim3(8 * per), dim3(HUBD_THREADS), 0, st, probs, off, n_probs, n_items, per);
+    return hipGetLastError();
 }
 
 hipError_t launch_hub6_batch(const HubUArgs *probs_u, const HubDArgs *probs_d, const int32_t *off_u,

@@ -285,6 +285,7 @@ static void build_plan(const std::vector<LzSolve *> &act, double *out2, StepPlan
     std::vector<const ecut_sectors *> rows_s;
     std::vector<ItemDev> rows_items;
     std::vector<int32_t> rows_tiles;
+    std::vector<char> rows_flat;
     for (LzSolve *L : act) {
         ProblemDev P = L->s->prob;
         P.x = xvec(*L);
@@ -301,18 +302,20 @@ static void build_plan(const std::vector<LzSolve *> &act, double *out2, StepPlan
             const int32_t pi = (int32_t)rows_probs.size();
             rows_probs.push_back(P);
             rows_s.push_back(L->s);
+            rows_flat.push_back(P.flat != 0);
+            rows_tiles.push_back(P.flat ? 0 : max_tile_elems(L->s));
+            if (P.flat) continue;   // no work items: the kernel finds its blocks by group
             for (const ItemDev &it : L->s->items) rows_items.push_back(ItemDev{pi, it.block, it.row0, it.row1, it.slot, 0});
-            rows_tiles.push_back(max_tile_elems(L->s));
         }
     }
-    if (!rows_items.empty()) {
+    if (!rows_probs.empty()) {
         // one work queue over every problem, largest tiles first
         std::stable_sort(rows_items.begin(), rows_items.end(), [&](const ItemDev &a, const ItemDev &b) {
             const int64_t wa = (int64_t)(a.row1 - a.row0) * rows_s[a.prob]->blocks[a.block].d_r;
             const int64_t wb = (int64_t)(b.row1 - b.row0) * rows_s[b.prob]->blocks[b.block].d_r;
             return wa > wb;
         });
-        make_rows_batch(rows_probs, rows_items, rows_tiles, pl.rows);
+        make_rows_batch(rows_probs, rows_items, rows_tiles, rows_flat, pl.rows);
         pl.has_rows = true;
         pl.o_rows = pl.P.put(pl.rows.buf);
     }

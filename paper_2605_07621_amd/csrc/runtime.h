@@ -26,29 +26,26 @@ std::string tune_shape_key(const ecut_sectors *s);
 struct RowsBatch {
     std::vector<char> buf;
     size_t pb = 0;
+    // problems on the flat kernel: their indices and first groups (spin cuts, then
+    // spatial Hubbard cuts), each list as [idx .. | off ..] of ints at o_flat
+    std::vector<int32_t> flat_idx[2], flat_off[2];
+    size_t o_flat[2] = {0, 0};
     int n_spin = 0, n_items = 0, spin_tile = 0, spin_src = 0, rows_tile = 0, rows_split = 1, first_spin = -1;
     ProblemDev spin_single{}, rows_single{};
 };
 void make_rows_batch(const std::vector<ProblemDev> &probs, const std::vector<ItemDev> &items,
-                     const std::vector<int32_t> &tiles, RowsBatch &b);
+                     const std::vector<int32_t> &tiles, const std::vector<char> &flat, RowsBatch &b);
 // launch with dev = a device copy of b.buf
 hipError_t launch_rows_batch(const RowsBatch &b, const void *dev, hipStream_t st);
-// One row-kernel launch over the work items of several problems (two when
-// spin-kernel and generic problems are mixed): copies the problem
-// descriptors and the work items to a per-thread device buffer (pinned
-// staging, asynchronous on `st`) and launches.  Waits for the previous use of
-// the buffer before overwriting it.  tiles[k] = largest row tile of problem k.
-ecut_status batch_launch_rows(const std::vector<ProblemDev> &probs, const std::vector<ItemDev> &items,
-                              const std::vector<int32_t> &tiles, hipStream_t st);
-
 // Hubbard problems of a batch that share one launch per pass of the
 // two-pass kernels: their arguments (with each problem's vectors and
 // epilogue) and the first item of each problem in each pass.
 struct HubBatch {
     std::vector<HubUArgs> u;
     std::vector<HubDArgs> d;
-    std::vector<int32_t> off_u{0}, off_d{0};
-    bool empty() const { return u.empty(); }
+    std::vector<HubFArgs> f;                  // problems on the fused one-pass kernel
+    std::vector<int32_t> off_u{0}, off_d{0}, off_f{0};
+    bool empty() const { return u.empty() && f.empty(); }
 };
 // a problem joins the merged launch when its tuning selects the two-pass
 // kernels (variant 6) and its down-spin table fits the batched kernel
@@ -59,7 +56,7 @@ bool own_launch(const ecut_sectors *s);
 void hub6_batch_add(HubBatch &b, const ecut_sectors *s, const ProblemDev &P);
 // byte offsets of the four arrays in a buffer laid out by hub6_batch_pack
 struct HubBatchLayout {
-    size_t u = 0, d = 0, off_u = 0, off_d = 0, bytes = 0;
+    size_t u = 0, d = 0, f = 0, off_u = 0, off_d = 0, off_f = 0, bytes = 0;
 };
 HubBatchLayout hub6_batch_layout(const HubBatch &b, size_t base);
 void hub6_batch_pack(const HubBatch &b, const HubBatchLayout &l, char *buf);

@@ -578,6 +578,10 @@ ecut_status build_host(const ecut_model_desc *m, const ecut_cut_desc *c, ecut_qn
         for (const BlockDev &B : s->blocks) rows += (size_t)B.d_l;
         s->items_cap = std::max(s->items_cap, rows);
         s->item_slots_cap = std::max<int32_t>(s->item_slots_cap, (int32_t)rows);
+        if (two_pass_rows(s, s->tune)) {
+            s->item_slots = make_spin_items(s, 1, 2, s->items);
+            s->sp_n_one = (int32_t)s->items.size();
+        }
     }
     if (s->kind == ECUT_HUBBARD && s->cut_kind == ECUT_CUT_UPDN) build_hub_tables(s, m);
     return ECUT_OK;
@@ -1154,6 +1158,10 @@ static void build_spin_tables(ecut_sectors *s) {
     make_rank_tables(s);
     build_two_pass_tables(s, (int)s->lsites.size(), {});
     s->spin_ok = true;
+    if (two_pass_rows(s, s->tune)) {   // the default of long vectors
+        s->item_slots = make_spin_items(s, SPIN_MANY_TILE, 2, s->items);
+        for (const ItemDev &it : s->items) s->sp_n_one += it.row1 - it.row0 == 1 ? 1 : 0;
+    }
 }
 
 // Tables of the two-pass row kernels (spin problems and the spatial Hubbard
@@ -1171,6 +1179,17 @@ static void build_spin_tables(ecut_sectors *s) {
 //    (no signs) a flip entry is the column's byte offset in the staged row,
 //    8 * column, and "no term" is 8 * d_r, the zero slot after the row; a
 //    cross entry is the source block's zero slot minus the column, in bytes.
+// Work groups of the flat row kernel: FLAT_THREADS consecutive amplitudes of
+// one block each.
+static void make_flat_groups(ecut_sectors *s) {
+    s->flat_base.clear();
+    if (!s->sp2_ok || s->dim > FLAT_MAX_DIM) return;
+    s->flat_base.push_back(0);
+    for (const BlockDev &B : s->blocks)
+        s->flat_base.push_back(s->flat_base.back() +
+                               (int32_t)(((int64_t)B.d_l * B.d_r + FLAT_THREADS - 1) / FLAT_THREADS));
+}
+
 static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<uint32_t> &rbetw) {
     s->sp2_ok = false;
     if (s->spin_fmask.size() > (size_t)SPIN_MAX_FLIP || s->max_d_r > SPIN_TILE) return;
@@ -1249,6 +1268,7 @@ static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<
     }
     spin_left_blocks(s, HUBU_ROWS, s->sp_lblocks);
     s->sp2_ok = csr_ok && s->max_d_r < 32768;
+    make_flat_groups(s);
 }
 
 int32_t processing_csr(const ecut_sectors *s, const std::vector<int32_t> &order, std::vector<int32_t> &pptr,

@@ -130,7 +130,8 @@ ecut_status apply_tuning(ecut_sectors *s, const ApplyTuning &T) {
         }
     }
     const int32_t tile = T.tile > 0 ? T.tile : SPIN_MANY_TILE, cur = s->tune.tile > 0 ? s->tune.tile : SPIN_MANY_TILE;
-    const int32_t spin_order = T.variant == 2 ? 2 : T.order, cur_order = s->tune.variant == 2 ? 2 : s->tune.order;
+    const bool two = two_pass_rows(s, T), cur_two = two_pass_rows(s, s->tune);
+    const int32_t spin_order = two ? 2 : T.order, cur_order = cur_two ? 2 : s->tune.order;
     if (s->spin_ok && (tile != cur || spin_order != cur_order)) {
         std::vector<ItemDev> items;
         const int32_t slots = make_spin_items(s, tile, spin_order, items);
@@ -144,10 +145,10 @@ ecut_status apply_tuning(ecut_sectors *s, const ApplyTuning &T) {
         s->items.swap(items);
         s->item_slots = slots;
     }
-    if (s->hub_spatial && s->sp2_ok && (T.variant == 2) != (s->tune.variant == 2)) {
+    if (s->hub_spatial && s->sp2_ok && two != cur_two) {
         // every row its own item for the two-pass kernels, else the row kernel's tiles
         std::vector<ItemDev> items;
-        const int32_t slots = T.variant == 2 ? make_spin_items(s, 1, 2, items)
+        const int32_t slots = two ? make_spin_items(s, 1, 2, items)
                                              : (items = s->generic_items, (int32_t)items.size());
         if (items.size() > s->items_cap || slots > s->item_slots_cap)
             return fail(ECUT_EINVAL, "work list exceeds its buffer");
@@ -164,7 +165,7 @@ ecut_status apply_tuning(ecut_sectors *s, const ApplyTuning &T) {
         if (spin_order == 2)
             for (const ItemDev &it : s->items) s->sp_n_one += (it.row1 - it.row0 == 1) ? 1 : 0;
         const int32_t rpi = T.grid > 0 ? T.grid : HUBU_ROWS, cur_rpi = s->tune.grid > 0 ? s->tune.grid : HUBU_ROWS;
-        if (T.variant == 2 && (rpi != cur_rpi || s->tune.variant != 2)) {
+        if (two && (rpi != cur_rpi || !cur_two)) {
             std::vector<SpinLBlock> lb;
             spin_left_blocks(s, rpi, lb);
             if (lb.size() != s->sp_lblocks.size()) return fail(ECUT_EINVAL, "left-pass block table changed size");
@@ -178,6 +179,7 @@ ecut_status apply_tuning(ecut_sectors *s, const ApplyTuning &T) {
     }
     s->tune = T;
     if (s->kernel != 1) s->prob.spin_ok = (s->spin_ok && s->on_device && T.variant == 0) ? 1 : 0;
+    s->prob.flat = flat_on(s) ? (s->hub_spatial ? 2 : 1) : 0;
     return ECUT_OK;
 }
 
@@ -222,6 +224,10 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
         }
     }
     std::vector<ApplyTuning> cands;
+    // the default tuning where it selects the fused or the flat kernel, or is
+    // the only one
+    if (s->kernel == 1 ? s->hub2_ok && s->hub6_ok && s->dim <= HUBF_MAX_DIM : !s->spin_ok || !s->flat_base.empty())
+        cands.push_back(ApplyTuning{0, 0, 0, 0, 0});
     if (s->kernel == 1) {
         if (s->hub2_ok)
             for (int order = 0; order < 6; ++order)
@@ -258,7 +264,6 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
             for (int rows : {4, 8, 16})
                 for (int xcd : {1, 8}) cands.push_back(ApplyTuning{rows, xcd, 0, 2, 0});
     } else {
-        cands.push_back(ApplyTuning{0, 0, 0, 0, 0});
         if (s->sp2_ok)   // the spatial Hubbard cut: the two-pass row kernels
             for (int rows : {4, 8, 16})
                 for (int xcd : {1, 8}) cands.push_back(ApplyTuning{rows, xcd, 0, 2, 0});
@@ -280,6 +285,7 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
         rs = apply_tuning(s, T);
         if (rs != ECUT_OK) break;
         P.spin_ok = s->prob.spin_ok;   // the kernel choice of this candidate
+        P.flat = s->prob.flat;
         rs = launch_apply(s, P, st);   // warm-up
         if (rs != ECUT_OK) break;
         hipEventRecord(e0, st);

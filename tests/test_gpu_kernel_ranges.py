@@ -78,3 +78,62 @@ def test_generic_kernel_slices_vs_oracle(dev):
         assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
         a, _, n2 = ecut.lanczos_tridiag(s, x, 1)
         assert abs(a[0] - float(x @ y) / n2) <= 1e-12 * float(y.norm()) / float(x.norm())
+
+
+def _small_and_long():
+    """(problem, tunings to compare with) on both sides of the sizes where the
+    default tuning changes kernel: the flat kernel up to 2^20 amplitudes, the
+    fused Hubbard kernel up to 2^18, the two-pass kernels above."""
+    rng = np.random.default_rng(41)
+    spin = [dict(tile=512), dict(tile=128, grid=512), dict(variant=2, n_xcd=8, grid=4)]
+    out = []
+    for m, cut, n_up in [(I.xxz_chain(2, 1.0, 0.4), 1, 1), (I.random_spin_model(rng, 11, n_bonds=22), 4, 5),
+                         (I.j1j2_lattice(4, 4), 8, 7), (I.xxz_chain(17, 1.0, 1.3, periodic=True), 3, 8),
+                         (I.xxz_chain(22, 1.0, 0.8), 11, 11), (I.j1j2_lattice(5, 4, 1.0, 0.3), 10, 9),
+                         (I.xxz_chain(23, 1.0, 0.8, periodic=True), 11, 11)]:
+        out.append((I.Problem(m, I.Cut("spatial", I.left_mask_first(cut)), n_up), spin, True))
+    ext = [dict(variant=1), dict(variant=2, n_xcd=8, grid=8)]
+    for n, cut, a, b in [(2, 1, 1, 1), (7, 3, 3, 4), (10, 5, 5, 4), (12, 6, 6, 6), (12, 4, 7, 6)]:
+        out.append((I.Problem(I.random_extended_hubbard_model(rng, n) if n < 12 else I.hubbard_chain(n, 1.0, 3.0, V=0.7),
+                              I.Cut("spatial", I.left_mask_first(cut)), a, b), ext, False))
+    hub = [dict(n_xcd=8), dict(variant=1, n_xcd=8)]
+    for m, a, b in [(I.hubbard_chain(2, 1.0, 3.0), 1, 1), (I.random_hubbard_model(rng, 8, n_bonds=20), 3, 5),
+                    (I.hubbard_chain(10, 1.0, 3.0, periodic=True), 5, 5), (I.hubbard_chain(11, 1.0, 3.0), 5, 6),
+                    (I.hubbard_chain(12, 1.0, 3.0), 4, 7), (I.hubbard_chain(12, 1.0, 3.0, periodic=True), 6, 6)]:
+        out.append((I.Problem(m, I.Cut("updn"), a, b), hub, False))
+    return out
+
+
+def test_default_tuning_by_size(dev):
+    """The default tuning's kernel against the explicit tunings of the general
+    kernels (spin cuts sum in one order: bit for bit; the Hubbard kernels to
+    rounding, relative L2 1e-14 for sums of at most 40 terms), against the
+    oracle on the problems small enough for it (1e-12), and in a batch (bit
+    for bit)."""
+    import oracle as O
+    S, xs, alone = [], [], []
+    for k, (p, alts, bits) in enumerate(_small_and_long()):
+        s = ecut.Sectors.from_problem(p)
+        x = _vec(s.dim, 70 + k, dev)
+        y = s.apply(x)
+        for t in alts:
+            s.set_tuning(**t)
+            z = s.apply(x)
+            if bits:
+                assert torch.equal(y, z), (p.model.name, t)
+            else:
+                assert float((y - z).norm()) <= 1e-14 * float(z.norm()), (p.model.name, t)
+        s.set_tuning()
+        assert torch.equal(s.apply(x), y)
+        if s.dim < 100000:
+            ref = O.Sector(p.model, p.n_up, p.n_dn).apply(s.export(x).cpu().numpy())
+            got = s.export(y).cpu().numpy()
+            assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref), p.model.name
+        a, _, n2 = ecut.lanczos_tridiag(s, x, 1)
+        assert abs(a[0] - float(x @ y) / n2) <= 1e-12 * float(y.norm()) / float(x.norm())
+        S.append(s), xs.append(x), alone.append(y)
+    for noalloc in (False, True):
+        ys = [torch.full_like(x, float("nan")) for x in xs]
+        ecut.apply_batch(S, xs, ys, noalloc=noalloc)
+        for y, z, (p, _, _) in zip(alone, ys, _small_and_long()):
+            assert torch.equal(y, z), p.model.name
