@@ -279,9 +279,10 @@ def serving_bench(n_requests, budget_gb):
 
 
 def kernel_name(S):
-    """Name of the kernel that carries the apply under the handle's tuning."""
+    """Name of the kernel that carries the apply under the handle's tuning
+    (of a host-only handle, which runs none: the kernel of its variant)."""
     info, t = S.info, S.get_tuning()
-    if not any(t.values()):   # the default selects by size
+    if info.device_bytes and not any(t.values()):   # the default selects by size
         if info.kernel == 1 and info.kernel_flags & 32:
             if S.dim <= 1 << 18:
                 return "k_hubF"
