@@ -155,6 +155,9 @@ hipError_t launch_spin2(const SpinLArgs &L, const ProblemDev &P, const uint16_t 
 // canonical <-> bipartite layout of the spatial Hubbard cut (with signs)
 hipError_t launch_perm_hubsp(const HubSpPerm &A, const double *in, double *out, bool to_bip, hipStream_t st);
 hipError_t launch_reduce(const VecJob *jobs_d, int n_jobs, hipStream_t st);
+// the same for one job, which needs no descriptor in device memory
+hipError_t launch_reduce_one(const VecJob &job, hipStream_t st);
+hipError_t launch_axpy_norm_one(const VecJob &job, int n_chunks, hipStream_t st);
 hipError_t launch_axpy_norm(const VecJob *jobs_d, const int32_t *chunk_job_d, const int32_t *chunk_idx_d, int n_chunks,
                             hipStream_t st);
 // gate (nullable, device): when *gate == 0.0 the launch does nothing

@@ -2634,11 +2634,12 @@ __device__ __forceinline__ void lz_next(const LzNextJob &J) {
     J.out2[1] = b2;
 }
 
-__global__ __launch_bounds__(VEC_THREADS) void k_reduce(const VecJob *__restrict__ jobs, int n_jobs) {
+// jobs == nullptr: the one job travels as a kernel argument
+__global__ __launch_bounds__(VEC_THREADS) void k_reduce(const VecJob *__restrict__ jobs, const VecJob one, int n_jobs) {
     __shared__ double red[VEC_THREADS / 64];
     const int j = blockIdx.x;
     if (j >= n_jobs) return;
-    const VecJob J = jobs[j];
+    const VecJob J = jobs ? jobs[j] : one;
     double s = 0.0;
     // fixed assignment of partial slots to threads, then a fixed-order block
     // sum; eight loads in flight, added in slot order
@@ -2661,13 +2662,15 @@ __global__ __launch_bounds__(VEC_THREADS) void k_reduce(const VecJob *__restrict
 }
 
 // y <- y - (scalars[coef_idx] * coef_mul) * x ; partials[chunk] = sum y^2
-__global__ __launch_bounds__(VEC_THREADS) void k_axpy_norm(const VecJob *__restrict__ jobs, const int32_t *__restrict__ chunk_job,
+// (jobs == nullptr: one job, a kernel argument, whose chunks are all there are)
+__global__ __launch_bounds__(VEC_THREADS) void k_axpy_norm(const VecJob *__restrict__ jobs, const VecJob one,
+                                                           const int32_t *__restrict__ chunk_job,
                                                            const int32_t *__restrict__ chunk_idx, int n_chunks) {
     __shared__ double red[VEC_THREADS / 64];
     __shared__ double bcast;
     for (int c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const VecJob J = jobs[chunk_job[c]];
-        const int ci = chunk_idx[c];
+        const VecJob J = jobs ? jobs[chunk_job[c]] : one;
+        const int ci = jobs ? chunk_idx[c] : c;
         const int64_t ck = J.chunk > 0 ? J.chunk : VEC_CHUNK;
         const int64_t i0 = (int64_t)ci * ck;
         const int64_t i1 = i0 + ck < J.n ? i0 + ck : J.n;
@@ -3107,7 +3110,12 @@ hipError_t launch_perm(const ecut_sectors *s, const uint64_t *binom_d, const Blo
 
 hipError_t launch_reduce(const VecJob *jobs_d, int n_jobs, hipStream_t st) {
     if (n_jobs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce, dim3(n_jobs), dim3(VEC_THREADS), 0, st, jobs_d, n_jobs);
+    hipLaunchKernelGGL(k_reduce, dim3(n_jobs), dim3(VEC_THREADS), 0, st, jobs_d, VecJob{}, n_jobs);
+    return hipGetLastError();
+}
+
+hipError_t launch_reduce_one(const VecJob &job, hipStream_t st) {
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(VEC_THREADS), 0, st, (const VecJob *)nullptr, job, 1);
     return hipGetLastError();
 }
 
@@ -3115,7 +3123,16 @@ hipError_t launch_axpy_norm(const VecJob *jobs_d, const int32_t *chunk_job_d, co
                             hipStream_t st) {
     if (n_chunks <= 0) return hipSuccess;
     int grid = n_chunks < 8192 ? n_chunks : 8192;
-    hipLaunchKernelGGL(k_axpy_norm, dim3(grid), dim3(VEC_THREADS), 0, st, jobs_d, chunk_job_d, chunk_idx_d, n_chunks);
+    hipLaunchKernelGGL(k_axpy_norm, dim3(grid), dim3(VEC_THREADS), 0, st, jobs_d, VecJob{}, chunk_job_d, chunk_idx_d,
+                       n_chunks);
+    return hipGetLastError();
+}
+
+hipError_t launch_axpy_norm_one(const VecJob &job, int n_chunks, hipStream_t st) {
+    if (n_chunks <= 0) return hipSuccess;
+    const int grid = n_chunks < 8192 ? n_chunks : 8192;
+    hipLaunchKernelGGL(k_axpy_norm, dim3(grid), dim3(VEC_THREADS), 0, st, (const VecJob *)nullptr, job,
+                       (const int32_t *)nullptr, (const int32_t *)nullptr, n_chunks);
     return hipGetLastError();
 }
 

@@ -171,6 +171,11 @@ static ecut_status run_start_jobs(std::vector<LzSolve *> &act, const std::vector
         R.next = LzNextJob{L.scal, L.scal + 8, L.reorth ? L.dscale : nullptr, 0, 1};
         jr.push_back(R);
     }
+    if (act.size() == 1) {   // the descriptors are kernel arguments
+        hipError_t e = launch_axpy_norm_one(jn[0], (int)cj.size(), st);
+        if (e == hipSuccess) e = launch_reduce_one(jr[0], st);
+        return e == hipSuccess ? ECUT_OK : hip_fail(e, "lanczos start");
+    }
     Pack P;
     size_t o_jn = P.put(jn), o_jr = P.put(jr), o_cj = P.put(cj), o_ci = P.put(ci);
     ecut_status rs = stg.reserve(P.buf.size());
@@ -272,6 +277,8 @@ struct StepPlan {
     Pack P;
     size_t o_rows = 0, o_ja = 0, o_jx = 0, o_jb = 0, o_cj = 0, o_ci = 0;
     int n_ja = 0, n_cj = 0;
+    bool one = false;                         // one solve: its jobs are kernel arguments, P stays empty
+    VecJob ja, jx, jb;
     LzSolve *R = nullptr;                     // the one solve with reorthogonalisation, if any
 };
 }  // namespace
@@ -367,17 +374,24 @@ static void build_plan(const std::vector<LzSolve *> &act, double *out2, StepPlan
         B.next = LzNextJob{L.scal, out2 + 2 * k, L.reorth ? L.dscale : nullptr, L.j + 1, 0};
         jb.push_back(B);
     }
+    pl.n_ja = (int)ja.size();
+    pl.n_cj = (int)cj.size();
+    pl.R = (act.size() == 1 && act[0]->reorth) ? act[0] : nullptr;
+    pl.one = act.size() == 1;
+    if (pl.one) {
+        pl.ja = ja[0];
+        pl.jx = jx[0];
+        pl.jb = jb[0];
+        return;
+    }
     pl.o_ja = pl.P.put(ja);
     pl.o_jx = pl.P.put(jx);
     pl.o_jb = pl.P.put(jb);
     pl.o_cj = pl.P.put(cj);
     pl.o_ci = pl.P.put(ci);
-    pl.n_ja = (int)ja.size();
-    pl.n_cj = (int)cj.size();
-    pl.R = (act.size() == 1 && act[0]->reorth) ? act[0] : nullptr;
 }
 
-// launches of a step; dev: a device copy of pl.P.buf
+// launches of a step; dev: a device copy of pl.P.buf (nullptr when that is empty)
 static ecut_status enqueue_plan(const StepPlan &pl, const void *dev, hipStream_t st) {
     for (size_t k = 0; k < pl.own.size(); ++k) {
         ecut_status rs = launch_apply(pl.own_s[k], pl.own[k], st);
@@ -388,8 +402,11 @@ static ecut_status enqueue_plan(const StepPlan &pl, const void *dev, hipStream_t
     if (pl.has_rows) e = launch_rows_batch(pl.rows, d + pl.o_rows, st);
     if (e == hipSuccess) e = hub6_batch_launch(pl.hub, pl.hub_l, d, st);
     if (e != hipSuccess) return hip_fail(e, "kernel launch (batched apply_H)");
-    if (!pl.fuse_alpha) e = launch_reduce((const VecJob *)(d + pl.o_ja), pl.n_ja, st);
-    if (e == hipSuccess)
+    if (!pl.fuse_alpha)
+        e = pl.one ? launch_reduce_one(pl.ja, st) : launch_reduce((const VecJob *)(d + pl.o_ja), pl.n_ja, st);
+    if (e == hipSuccess && pl.one)
+        e = launch_axpy_norm_one(pl.jx, pl.n_cj, st);
+    else if (e == hipSuccess)
         e = launch_axpy_norm((const VecJob *)(d + pl.o_jx), (const int32_t *)(d + pl.o_cj), (const int32_t *)(d + pl.o_ci),
                              pl.n_cj, st);
     if (e != hipSuccess) return hip_fail(e, "lanczos update");
@@ -416,7 +433,8 @@ static ecut_status enqueue_plan(const StepPlan &pl, const void *dev, hipStream_t
         }
         if (e != hipSuccess) return hip_fail(e, "reorthogonalisation");
     }
-    e = launch_reduce((const VecJob *)(d + pl.o_jb), (int)pl.act.size(), st);   // and the next factors
+    // and the next factors
+    e = pl.one ? launch_reduce_one(pl.jb, st) : launch_reduce((const VecJob *)(d + pl.o_jb), (int)pl.act.size(), st);
     if (e != hipSuccess) return hip_fail(e, "lanczos beta");
     return ECUT_OK;
 }
@@ -440,8 +458,8 @@ static ecut_status capture_step(const std::vector<LzSolve *> &act, hipStream_t s
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(graph scalars)");
     StepPlan pl;
     build_plan(act, g->dev_out, pl);
-    e = hipMallocAsync(&g->dev, pl.P.buf.size(), st);
-    if (e == hipSuccess) e = hipMemcpyAsync(g->dev, pl.P.buf.data(), pl.P.buf.size(), hipMemcpyHostToDevice, st);
+    if (!pl.P.buf.empty()) e = hipMallocAsync(&g->dev, pl.P.buf.size(), st);
+    if (e == hipSuccess && g->dev) e = hipMemcpyAsync(g->dev, pl.P.buf.data(), pl.P.buf.size(), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);   // the pageable source is released on return
     if (e != hipSuccess) return hip_fail(e, "graph descriptors");
     ecut_status rs;
@@ -508,14 +526,16 @@ ecut_status lz_launch(std::vector<LzSolve *> &solves, LzPipe &pipe, hipStream_t 
     } else {
         StepPlan pl;
         build_plan(act, S.host_dev, pl);   // alpha, |w|^2 go straight to pinned host memory
-        rs = stg.reserve(pl.P.buf.size());
-        if (rs != ECUT_OK) return rs;
-        rs = stg.wait();
-        if (rs != ECUT_OK) return rs;
-        std::memcpy(stg.host, pl.P.buf.data(), pl.P.buf.size());
-        rs = stg.upload(pl.P.buf.size(), st);
-        if (rs != ECUT_OK) return rs;
-        rs = enqueue_plan(pl, stg.dev, st);
+        if (!pl.P.buf.empty()) {
+            rs = stg.reserve(pl.P.buf.size());
+            if (rs != ECUT_OK) return rs;
+            rs = stg.wait();
+            if (rs != ECUT_OK) return rs;
+            std::memcpy(stg.host, pl.P.buf.data(), pl.P.buf.size());
+            rs = stg.upload(pl.P.buf.size(), st);
+            if (rs != ECUT_OK) return rs;
+        }
+        rs = enqueue_plan(pl, pl.P.buf.empty() ? nullptr : stg.dev, st);
         if (rs != ECUT_OK) return rs;
         e = hipSuccess;
         S.graph.reset();
