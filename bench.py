@@ -284,7 +284,7 @@ def kernel_name(S):
     info, t = S.info, S.get_tuning()
     if info.device_bytes and not any(t.values()):   # the default selects by size
         if info.kernel == 1 and info.kernel_flags & 32:
-            if S.dim <= 1 << 18:
+            if S.dim <= (1 << 20 if info.kernel_flags & 2 else 1 << 18):
                 return "k_hubF"
             return "k_hubU+k_hub3" if info.kernel_flags & 2 and S.dim >= 1 << 25 else "k_hubU+k_hubD"
         if info.kernel_flags & 64:

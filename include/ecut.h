@@ -262,9 +262,9 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
 /*
  * Launch tuning of ecut_apply_H.  All fields 0, the default, selects the
  * kernels by the vector's size: Hubbard up/down problems of at most 32
- * hopping bonds run one fused kernel up to 2^18 amplitudes, the two-pass
- * kernels (variant 6) above, and variant 7 from 2^25 where it is available;
- * spin problems and the spatial Hubbard cut, where kernel_flags bit 6 is set,
+ * hopping bonds run one fused kernel up to 2^18 amplitudes (2^20 if every
+ * hop has the same value), the two-pass kernels (variant 6) above, and
+ * variant 7 from 2^25 where it is available; spin problems and the spatial Hubbard cut, where kernel_flags bit 6 is set,
  * run one kernel with a thread per amplitude up to 2^20 amplitudes and the
  * two-pass kernels (variant 2) above; other problems run variant 0's kernel.
  * Explicit tunings (used by the Hubbard up/down kernel, whose work groups
@@ -304,8 +304,8 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
  *              kernel_flags bit 4; row_order ignored; n_xcd 1 = plain grid
  *              stride, else 8 XCD chunks),
  *              6 two passes of one work group per item (kernel_flags bit 5;
- *              vectors of at most 2^18 amplitudes take the default's fused
- *              kernel instead, and grid and tile are ignored):
+ *              the vectors the default's fused kernel takes run on it here
+ *              too, and grid and tile are then ignored):
  *              the left operator over column slabs in inversion-level row
  *              order (grid = rows per item, 0 = 4, at most 32), then the
  *              right operator, diagonal and epilogue with the source

@@ -471,13 +471,19 @@ bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T) {
     return s->kernel != 1 && s->sp2_ok && (T.variant == 2 || (s->flat_base.empty() && default_tuning(T)));
 }
 
-// The default tuning, and the two-pass tuning, of a Hubbard up/down problem of
-// at most HUBF_MAX_DIM amplitudes
+// The default tuning, and the two-pass tuning, of a Hubbard up/down problem
+// short enough for the fused kernel.  With one hop value (no value table to
+// read) it is level with the two passes at 853,776 amplitudes (16.4 us both,
+// one launch instead of two); with signed hops it loses there (30 against 20
+// us) and wins at 213,444 (7.5 against 10).
+bool hub_fused_size(const ecut_sectors *s) {
+    return s->kernel == 1 && s->hub6_ok && s->dim <= (s->h6_uniform ? HUBF_MAX_DIM_UNIFORM : HUBF_MAX_DIM);
+}
 bool hub_fused(const ecut_sectors *s) {
-    return s->kernel == 1 && s->hub6_ok && s->dim <= HUBF_MAX_DIM && (s->tune.variant == 6 || default_tuning(s->tune));
+    return hub_fused_size(s) && (s->tune.variant == 6 || default_tuning(s->tune));
 }
 
-// The default tuning above HUBF_MAX_DIM: the two-pass kernels, which beat the
+// The default tuning above those sizes: the two-pass kernels, which beat the
 // one-pass class tiles at every size measured (12-site chain 16.4 against 22.4
 // us, 14-site 180 against 325, 14-site ring 186 against 481); vectors past the
 // last-level cache take the class tiles for the right pass where they exist

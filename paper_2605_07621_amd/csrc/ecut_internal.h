@@ -501,6 +501,7 @@ bool flat_on(const ecut_sectors *s);
 bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T);
 // the Hubbard up/down problem runs the fused one-pass kernel under its tuning
 bool hub_fused(const ecut_sectors *s);
+bool hub_fused_size(const ecut_sectors *s);   // the problem is short enough for it
 // the tuning the Hubbard launches follow: the handle's, or what its default selects by size
 ApplyTuning hub_tuning(const ecut_sectors *s);
 // item counts of the two-pass kernels (variant 6) for the handle's tuning

@@ -51,6 +51,7 @@ constexpr int HUBD_ROWS = 4;                 // default rows per right-operator 
 constexpr int FLAT_THREADS = 256;            // flat row kernel: one amplitude per thread
 constexpr int64_t FLAT_MAX_DIM = (int64_t)1 << 20;        // longest vectors it takes: the two-pass kernels beat it above
 constexpr int64_t HUBF_MAX_DIM = (int64_t)1 << 18;        // the same for the fused Hubbard kernel
+constexpr int64_t HUBF_MAX_DIM_UNIFORM = (int64_t)1 << 20;   // and for it when every hop has one value
 constexpr int VEC_THREADS = 256;
 constexpr int64_t VEC_CHUNK = 8192;          // elements per reduction partial
 constexpr int64_t CGS_CHUNK_MIN = 1024;      // shortest chunk of the reorthogonalisation kernels
