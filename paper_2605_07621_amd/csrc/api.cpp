@@ -262,7 +262,7 @@ ecut_status upload(ecut_sectors *s) {
         o_5ux = A.add(s->hs_ucross);
         o_5it = A.add(s->hs_items);
     }
-    size_t o_6k = 0, o_6v = 0, o_6r = 0, o_6p = 0, o_6c = 0, o_6w = 0;
+    size_t o_6k = 0, o_6v = 0, o_6r = 0, o_6p = 0, o_6c = 0, o_6w = 0, o_hp = 0;
     if (s->hub6_ok) {
         o_6k = A.add(s->h6_col);
         o_6v = A.add(s->h6_val);
@@ -270,6 +270,7 @@ ecut_status upload(ecut_sectors *s) {
         o_6p = A.add(s->h6_pptr);
         o_6c = A.add(s->h6_pcol);
         o_6w = A.add(s->h6_pval);
+        o_hp = A.add(s->hp_panels);
     }
     void *mem = nullptr;
     st = table_alloc(&mem, A.off, dev);
@@ -433,6 +434,13 @@ ecut_status upload(ecut_sectors *s) {
         U.hop = s->hl_val.empty() ? 0.0 : s->hl_val[0];
         U.n_rows = B0.d_l;
         U.dR = B0.d_r;
+        HubPArgs &Pn = s->hp;
+        Pn = HubPArgs{};
+        Pn.panels = (const int32_t *)(b + o_hp);
+        Pn.hop = U.hop;
+        Pn.n_rows = B0.d_l;
+        Pn.dR = B0.d_r;
+        Pn.n_panels = (int32_t)(s->hp_panels.size() / HUBP_PANEL_INTS);
         HubDArgs &D = s->h6d;
         D = HubDArgs{};
         D.n_slots = s->h6_maxq;
@@ -538,6 +546,15 @@ void hub6_shape(const ecut_sectors *s, HubUArgs &U, HubDArgs &D) {
     D.n_items = ((nr + D.rows_per_item - 1) / D.rows_per_item) * D.n_chunks;
 }
 
+// the left operator's pass of the two-pass kernels: on panels where they exist
+static hipError_t launch_left(const ecut_sectors *s, const HubUArgs &U, int n_xcd, hipStream_t st) {
+    if (s->hp_lo == 0) return launch_hub6_left(U, n_xcd, st);
+    HubPArgs A = s->hp;
+    A.x = U.x;
+    A.y = U.y;
+    return launch_hubP(A, s->hp_lo, st);
+}
+
 static HubFArgs hub_fused_args(const ecut_sectors *s, const ProblemDev &P) {
     HubUArgs U = s->h6u;
     HubFArgs F{};
@@ -591,7 +608,7 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
             hub6_shape(s, U, D);
             U.x = D.x = P.x;
             U.y = D.y = P.y;
-            e = launch_hub6_left(U, n_xcd, st);
+            e = launch_left(s, U, n_xcd, st);
             if (e == hipSuccess && T.variant == 6) {
                 D.z = P.z;
                 D.partials = P.partials;
@@ -698,6 +715,16 @@ void hub6_batch_add(HubBatch &b, const ecut_sectors *s, const ProblemDev &P) {
     D.xscale = P.xscale;
     D.zcoef = P.zcoef;
     D.dscale = P.dscale;
+    if (s->hp_lo > 0) {
+        // left pass of its own: the merged launch of the general left passes
+        // gets no item of this problem
+        HubPArgs A = s->hp;
+        A.x = P.x;
+        A.y = P.y;
+        b.p.push_back(A);
+        b.p_lo.push_back(s->hp_lo);
+        U.n_items = 0;
+    }
     b.u.push_back(U);
     b.d.push_back(D);
     b.off_u.push_back(b.off_u.back() + U.n_items);
@@ -729,8 +756,9 @@ void hub6_batch_pack(const HubBatch &b, const HubBatchLayout &l, char *buf) {
 hipError_t hub6_batch_launch(const HubBatch &b, const HubBatchLayout &l, const void *dev, hipStream_t st) {
     if (b.empty()) return hipSuccess;
     const char *d = (const char *)dev;
-    const hipError_t e = launch_hubF_batch((const HubFArgs *)(d + l.f), (const int32_t *)(d + l.off_f), (int)b.f.size(),
+    hipError_t e = launch_hubF_batch((const HubFArgs *)(d + l.f), (const int32_t *)(d + l.off_f), (int)b.f.size(),
                                            b.off_f.back(), st);
+    for (size_t k = 0; k < b.p.size() && e == hipSuccess; ++k) e = launch_hubP(b.p[k], b.p_lo[k], st);
     if (e != hipSuccess) return e;
     return launch_hub6_batch((const HubUArgs *)(d + l.u), (const HubDArgs *)(d + l.d), (const int32_t *)(d + l.off_u),
                              (const int32_t *)(d + l.off_d), (int)b.u.size(), b.off_u.back(), b.off_d.back(), st);

@@ -202,6 +202,20 @@ struct HubUArgs {
     int32_t n_slabs, n_items;         // slab groups (of slab_ways slabs), items
 };
 
+// Pass 1 on panels (open chains with one hop value): rows that share the high
+// part of the up word.  A panel's descriptor, in processing order: first row,
+// particles of the low part | HUBP_HI_OCCUPIED, first row of the panel the bond
+// between the parts comes from (-1: none), number of high hops, then the first
+// row of the panel each high hop comes from.
+struct HubPArgs {
+    const double *x;
+    double *y;
+    const int32_t *panels;            // [n_panels][HUBP_PANEL_INTS]
+    double hop;
+    int32_t n_rows, dR, n_panels;
+    int32_t n_pgroups, n_items;       // filled by the launch
+};
+
 // Pass 2 (right operator, diagonal, epilogue): per element (a, c)
 //   y = xscale (y_pass1 + sum_q val_q x[a, col_q] + diag(a, c) x[a, c]) - zcoef z
 // with the down-spin hops of column c in bond-major slots (col[b * dR + c]).
@@ -411,6 +425,10 @@ struct ecut_sectors {
     std::vector<int32_t> h6_col;
     std::vector<double> h6_val;
     ecut::HubUArgs h6u{};
+    // the left pass on panels (hp_lo low sites; 0: the general left pass)
+    int32_t hp_lo = 0;
+    std::vector<int32_t> hp_panels;
+    ecut::HubPArgs hp{};
     ecut::HubDArgs h6d{};
     ecut::HubDev hub{};
     std::vector<int32_t> hub_lo_cnt, hub_lo_ent, hub_lo_rank, hub_hi_cnt, hub_hi_ent, hub_seg_off, hub_xb;

@@ -43,6 +43,14 @@ constexpr int HUBU_THREADS = 256;            // two-pass kernels: left-operator 
 constexpr int HUBU_NB = 8;                   // neighbour-row loads issued together per lane
 constexpr int HUBU_ROWS = 4;                  // rows of the row order per left-operator item
 constexpr int HUBU_RMAX = 8;                  // most rows of one wave in a left-operator item
+constexpr int HUBP_THREADS = 256;            // left pass on panels: one panel per wave at 64 columns
+constexpr int HUBP_MAX_LO = 8;               // most low sites of the up word (compiled: 7 and 8)
+constexpr int HUBP_MIN_SITES = 14;           // shortest chain it takes
+constexpr size_t HUBP_LDS = 84 * 1024;       // LDS request that keeps one group on a compute unit (160 KB)
+constexpr int HUBP_MAX_PANEL = 70;           // rows of the longest panel, C(8, 4)
+constexpr int HUBP_CHUNK = 28;               // rows whose loads are issued together
+constexpr int HUBP_PANEL_INTS = 16;          // ints of a panel's descriptor
+constexpr int HUBP_HI_OCCUPIED = 256;        // flag beside the low particle number: the high part's first site is occupied
 constexpr int HUBD_THREADS = 256;            // right-operator pass: one column per thread
 constexpr int HUBD_NB = 8;                   // in-row gathers issued together per lane
 constexpr int HUBD_MAX_SLOTS = 32;           // bonds of the down-spin hop table (held in registers)
@@ -114,6 +122,8 @@ hipError_t launch_hub2(const ecut_sectors *s, const ProblemDev &prob, const HubI
 size_t hub3_lds_bytes(const ecut_sectors *s);
 // segment tiles: grid work groups, n_xcd = 8 (items in 8 XCD chunks) or 1
 hipError_t launch_hubseg(const ecut_sectors *s, const HubSegArgs &args, int grid, int n_xcd, hipStream_t st);
+// the left-operator pass on panels (open chains with one hop value)
+hipError_t launch_hubP(const HubPArgs &args, int lo_sites, hipStream_t st);
 // two-pass kernels (variants 6 and 7): the flat left-operator pass (slab
 // items; n_xcd 8 = XCD-contiguous items)
 hipError_t launch_hub6_left(const HubUArgs &U, int n_xcd, hipStream_t st);

@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <type_traits>
+#include <utility>
 
 #include "ecut_internal.h"
 #include "kernels.h"
@@ -2147,6 +2148,167 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_hubU(const HubUArgs A, int n_x
     hubU_item<PAIR, STREAM, OFF32>(A, it);
 }
 
+// ------------------------------------------------------------------------
+// Left (up-spin) operator of an open chain with one hop value, on panels.  A
+// panel is the run of rows that share the high part of the up word (all but
+// its H low sites): C(H, k) rows in increasing order of the low part.  A wave
+// takes one panel at 64 columns and keeps every row's sum in registers:
+//  - hops inside the low part join rows of the panel by a pattern known at
+//    compile time: each row is loaded once and added to its neighbours' sums;
+//  - a hop inside the high part joins the whole panel to another one row by
+//    row: a straight stream, no index loads;
+//  - the bond between the parts (sites H - 1 and H) joins a contiguous run
+//    of rows (those whose low part has site H - 1 occupied come last) to a
+//    contiguous run of the panel with that bond's other site flipped.
+// The general left pass gathers one row per hop; here the low hops, about half
+// of them, cost no load.  The 16-site chain's pass reads and writes the vector
+// at the copy rate in 0.65-0.71 ms when every other load is left out; the high
+// hops' panels must therefore come from L2.  The panels in flight on an XCD are
+// 36 KB per wave, so the launch keeps one group per compute unit (an LDS
+// request nothing uses): 0.865 ms against 0.945 with two (fetched 2.5 GB) and
+// 0.97-1.02 for the general pass; half or three quarters of that in flight
+// 0.98 and 0.91, one and a half times 0.95.  Four waves side by side on one
+// panel (2 KB rows) 0.90, whole rows at a time 1.07.
+// ------------------------------------------------------------------------
+struct LoPattern {
+    int rows = 0;
+    int word[HUBP_MAX_PANEL] = {};
+    int deg[HUBP_MAX_PANEL] = {};
+    int nb[HUBP_MAX_PANEL][HUBP_MAX_LO] = {};
+};
+constexpr int ct_popc(int w) { return w ? (w & 1) + ct_popc(w >> 1) : 0; }
+constexpr int ct_binom(int n, int k) { return k < 0 || k > n ? 0 : k == 0 || k == n ? 1 : ct_binom(n - 1, k - 1) + ct_binom(n - 1, k); }
+// the words of H sites with K particles in increasing order and their
+// nearest-neighbour hops
+constexpr LoPattern lo_pattern(int H, int K) {
+    LoPattern P;
+    int rank[1 << HUBP_MAX_LO] = {};
+    for (int w = 0; w < (1 << H); ++w)
+        if (ct_popc(w) == K) {
+            rank[w] = P.rows;
+            P.word[P.rows++] = w;
+        }
+    for (int j = 0; j < P.rows; ++j)
+        for (int b = 0; b + 1 < H; ++b)
+            if (((P.word[j] >> b) & 1) != ((P.word[j] >> (b + 1)) & 1)) P.nb[j][P.deg[j]++] = rank[P.word[j] ^ (3 << b)];
+    return P;
+}
+template <int H, int K>
+struct LoTable {
+    static constexpr LoPattern P = lo_pattern(H, K);
+};
+
+// adds row J's value to the sums of its low-hop neighbours
+template <int H, int K, int J, size_t... Q>
+__device__ __forceinline__ void lo_scatter(double *acc, double v, std::index_sequence<Q...>) {
+    ((acc[LoTable<H, K>::P.nb[J][Q]] += v), ...);
+}
+template <int H, int K, int J0, size_t... U>
+__device__ __forceinline__ void lo_rows(double *acc, const double *v, std::index_sequence<U...>) {
+    (lo_scatter<H, K, J0 + (int)U>(acc, v[U], std::make_index_sequence<LoTable<H, K>::P.deg[J0 + (int)U]>{}), ...);
+}
+
+// N rows of a panel from the (uniform) row pointer p at the lane's byte offset,
+// all loads before any use: a scalar base and a 32-bit lane offset each
+template <int N>
+__device__ __forceinline__ void panel_load(const double *__restrict__ p, uint32_t off, int64_t dR, double (&v)[N]) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] = *(const double *)((const char *)(p + u * dR) + off);
+}
+// acc[A0 + j] += row j counted from p, j < N
+template <int A0, int N>
+__device__ __forceinline__ void panel_add(const double *__restrict__ p, uint32_t off, int64_t dR, double *acc) {
+    constexpr int C = N < HUBP_CHUNK ? N : HUBP_CHUNK;
+    if constexpr (N > 0) {
+        double v[C];
+        panel_load<C>(p, off, dR, v);
+#pragma unroll
+        for (int u = 0; u < C; ++u) acc[A0 + u] += v[u];
+        panel_add<A0 + C, N - C>(p + C * dR, off, dR, acc);
+    }
+}
+template <int H, int K, int J0>
+__device__ __forceinline__ void panel_lo(const double *__restrict__ p, uint32_t off, int64_t dR, double *acc) {
+    constexpr int R = LoTable<H, K>::P.rows - J0, C = R < HUBP_CHUNK ? R : HUBP_CHUNK;
+    if constexpr (R > 0) {
+        double v[C];
+        panel_load<C>(p, off, dR, v);
+        lo_rows<H, K, J0>(acc, v, std::make_index_sequence<C>{});
+        panel_lo<H, K, J0 + C>(p + C * dR, off, dR, acc);
+    }
+}
+
+template <int H, int K, bool STREAM>
+__device__ __forceinline__ void panel_item(const HubPArgs &A, const int32_t *__restrict__ pan, uint32_t off, bool ok) {
+    constexpr int R = LoTable<H, K>::P.rows;
+    const int64_t dR = A.dR;
+    const double *__restrict__ x = A.x;
+    double acc[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) acc[j] = 0.0;
+    panel_lo<H, K, 0>(x + (int64_t)pan[0] * dR, off, dR, acc);
+    const int nh = pan[3];
+    for (int q = 0; q < nh; ++q) panel_add<0, R>(x + (int64_t)pan[4 + q] * dR, off, dR, acc);
+    // the bond between the parts: pan[2] is the source panel's first row, or -1
+    if (pan[2] >= 0) {
+        const double *__restrict__ xs = x + (int64_t)pan[2] * dR;
+        constexpr int LOW = ct_binom(H - 1, K), TOP = R - LOW, UP = ct_binom(H - 1, K + 1);   // rows with site H - 1 empty, occupied
+        if (pan[1] & HUBP_HI_OCCUPIED) {   // site H occupied here: it comes from site H - 1
+            if constexpr (K < H) panel_add<0, LOW>(xs + UP * dR, off, dR, acc);
+        } else {
+            if constexpr (K > 0) panel_add<LOW, TOP>(xs, off, dR, acc);
+        }
+    }
+    if (ok) {
+        double *y = A.y + (int64_t)pan[0] * dR;
+#pragma unroll
+        for (int j = 0; j < R; ++j) store_result<STREAM>((double *)((char *)(y + j * dR) + off), A.hop * acc[j]);
+    }
+}
+
+template <int H, bool STREAM>
+__global__ __launch_bounds__(HUBP_THREADS, 2) void k_hubP(const HubPArgs A, int per_xcd) {
+    const int it = xcd_item(8, per_xcd);
+    if (it >= A.n_items) return;
+    const int slab = it / A.n_pgroups;
+    const int p = (it - slab * A.n_pgroups) * (HUBP_THREADS / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (p >= A.n_panels) return;
+    const int c = slab * 64 + (int)(threadIdx.x & 63);
+    const bool ok = c < A.dR;
+    const uint32_t off = 8u * (uint32_t)(ok ? c : A.dR - 1);   // lanes past the row end read the last column
+    const int32_t *__restrict__ pan = A.panels + (int64_t)p * HUBP_PANEL_INTS;
+    const int k = pan[1] & 0xff;
+    // uniform over the wave: one branch, the body compiled for its row count
+    if (k == 0) panel_item<H, 0, STREAM>(A, pan, off, ok);
+    else if (k == 1) panel_item<H, 1, STREAM>(A, pan, off, ok);
+    else if (k == 2) panel_item<H, 2, STREAM>(A, pan, off, ok);
+    else if (k == 3) panel_item<H, 3, STREAM>(A, pan, off, ok);
+    else if (k == 4) panel_item<H, 4, STREAM>(A, pan, off, ok);
+    else if (k == 5) panel_item<H, 5, STREAM>(A, pan, off, ok);
+    else if (k == 6) panel_item<H, 6, STREAM>(A, pan, off, ok);
+    else if (k == 7) panel_item<H, 7, STREAM>(A, pan, off, ok);
+    if constexpr (H == 8) {
+        if (k == 8) panel_item<H, 8, STREAM>(A, pan, off, ok);
+    }
+}
+
+hipError_t launch_hubP(const HubPArgs &args, int lo_sites, hipStream_t st) {
+    HubPArgs A = args;
+    constexpr int WAVES = HUBP_THREADS / 64;
+    A.n_pgroups = (A.n_panels + WAVES - 1) / WAVES;
+    A.n_items = A.n_pgroups * ((A.dR + 63) / 64);
+    if (A.n_items <= 0) return hipSuccess;
+    const bool stream = (int64_t)A.n_rows * A.dR >= STREAM_STORE_MIN;
+    const int per = (A.n_items + 7) / 8;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(8 * per), dim3(HUBP_THREADS), HUBP_LDS, st, A, per);
+    };
+    if (lo_sites == 8) stream ? go(k_hubP<8, true>) : go(k_hubP<8, false>);
+    else if (lo_sites == 7) stream ? go(k_hubP<7, true>) : go(k_hubP<7, false>);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 // every byte offset into a vector of n elements (a 16-byte read at most)
 // fits 32 bits
 static bool fits_off32(int64_t n) { return n * 8 + 16 <= (int64_t)UINT32_MAX; }
@@ -2367,7 +2529,8 @@ hipError_t launch_hub6_batch(const HubUArgs *probs_u, const HubDArgs *probs_d, c
                              const int32_t *off_d, int n_probs, int n_items_u, int n_items_d, hipStream_t st) {
     if (n_probs <= 0) return hipSuccess;
     const int pu = (n_items_u + 7) / 8, pd = (n_items_d + 7) / 8;
-    hipLaunchKernelGGL(k_hubU_batch, dim3(8 * pu), dim3(HUBU_THREADS), 0, st, probs_u, off_u, n_probs, n_items_u, pu);
+    if (n_items_u > 0)   // none: every left pass runs on panels
+        hipLaunchKernelGGL(k_hubU_batch, dim3(8 * pu), dim3(HUBU_THREADS), 0, st, probs_u, off_u, n_probs, n_items_u, pu);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_hubD_batch, dim3(8 * pd), dim3(HUBD_THREADS), 0, st, probs_d, off_d, n_probs, n_items_d, pd);
@@ -3087,6 +3250,11 @@ hipError_t set_hub_lds_limits(size_t bytes) {
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void *)k_hub3<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
     if (e != hipSuccess) return e;
+    for (const void *f : {(const void *)k_hubP<7, true>, (const void *)k_hubP<7, false>, (const void *)k_hubP<8, true>,
+                          (const void *)k_hubP<8, false>}) {
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)HUBP_LDS);
+        if (e != hipSuccess) return e;
+    }
     return hipFuncSetAttribute((const void *)k_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ROWS_MAX_LDS);
 }
 

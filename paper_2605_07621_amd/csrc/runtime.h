@@ -43,6 +43,8 @@ hipError_t launch_rows_batch(const RowsBatch &b, const void *dev, hipStream_t st
 struct HubBatch {
     std::vector<HubUArgs> u;
     std::vector<HubDArgs> d;
+    std::vector<HubPArgs> p;                  // left passes on panels, one launch each
+    std::vector<int32_t> p_lo;
     std::vector<HubFArgs> f;                  // problems on the fused one-pass kernel
     std::vector<int32_t> off_u{0}, off_d{0}, off_f{0};
     bool empty() const { return u.empty() && f.empty(); }

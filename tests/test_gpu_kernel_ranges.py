@@ -137,3 +137,26 @@ def test_default_tuning_by_size(dev):
         ecut.apply_batch(S, xs, ys, noalloc=noalloc)
         for y, z, (p, _, _) in zip(alone, ys, _small_and_long()):
             assert torch.equal(y, z), p.model.name
+
+
+# panels of the left pass (open chains of 14 sites and more): the fewest and
+# most particles, panels of 1 to C(7, 3) and C(8, 4) rows, columns that end
+# inside a slab of 64, odd rows; the 17-site chain on the two-pass variant 6
+@pytest.mark.parametrize("n,n_up,n_dn,variant", [(14, 0, 2, 7), (14, 14, 1, 7), (14, 1, 3, 7), (14, 3, 2, 7),
+                                                 (14, 7, 1, 7), (15, 8, 1, 7), (15, 2, 14, 7), (16, 16, 1, 7),
+                                                 (16, 4, 2, 7), (16, 8, 1, 7), (17, 8, 2, 6)])
+def test_left_pass_on_panels_vs_oracle(dev, n, n_up, n_dn, variant):
+    """H psi through the panels against the oracle (relative L2 1e-12) and
+    against a kernel that does not use them (1e-14: sums of at most 40 terms)."""
+    import oracle as O
+    p = I.Problem(I.hubbard_chain(n, 0.9, 3.0), I.Cut("updn"), n_up, n_dn)
+    s = ecut.Sectors.from_problem(p)
+    x = _vec(s.dim, 90 + n_up, dev)
+    s.set_tuning(variant=variant, n_xcd=8)
+    y = s.apply(x)
+    s.set_tuning(variant=1, n_xcd=8)
+    z = s.apply(x)
+    assert float((y - z).norm()) <= 1e-14 * float(z.norm())
+    if s.dim < 500000:
+        ref = O.Sector(p.model, n_up, n_dn).apply(s.export(x).cpu().numpy())
+        assert np.linalg.norm(s.export(y).cpu().numpy() - ref) <= 1e-12 * np.linalg.norm(ref)
