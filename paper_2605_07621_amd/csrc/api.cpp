@@ -532,7 +532,7 @@ static int32_t hub6_rows_d(const ApplyTuning &T) { return T.tile > 0 ? T.tile : 
 
 void hub6_shape(const ecut_sectors *s, HubUArgs &U, HubDArgs &D) {
     const int32_t dR = s->blocks[0].d_r, nr = s->blocks[0].d_l;
-    const int32_t cols = (dR % 2 == 0 ? 2 : 1) * 64;
+    const int32_t cols = (dR > 1 ? 2 : 1) * 64;
     const ApplyTuning T = hub_tuning(s);
     U.rows_per_item = T.grid > 0 ? T.grid : HUBU_ROWS;
     U.n_rgroups = (nr + U.rows_per_item - 1) / U.rows_per_item;

@@ -47,6 +47,10 @@ __device__ double block_sum(double v, double *red) {
     return s;
 }
 
+// Two neighbouring amplitudes in one 16-byte access at 8-byte alignment (the
+// rows of odd length and vectors at odd offsets; the hardware asks for 4).
+typedef double pair8 __attribute__((ext_vector_type(2), aligned(8)));
+
 // Result stores.  A vector larger than the last-level cache is streamed past
 // it (non-temporal: its lines would only evict the source rows that later
 // work still gathers); a smaller one stays cacheable for the next kernel.
@@ -1274,7 +1278,8 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_spinL(const SpinLArgs A, int n
     U.n_rgroups = L.n_rgroups;
     U.n_slabs = L.n_slabs;
     U.n_items = L.n_rgroups * L.n_slabs;
-    hubU_item<false, STREAM>(U, it - L.item0);
+    if (L.d_r > 1) hubU_item<true, STREAM>(U, it - L.item0);
+    else hubU_item<false, STREAM>(U, it - L.item0);
 }
 
 // ONE: one-row items on NT1 threads with M1 amplitudes each (512 x 13 for
@@ -2022,9 +2027,12 @@ __device__ __forceinline__ void hubU_item(const HubUArgs &A, int it) {
     const int slab = sg * ways + wave % ways;
     const int c = (slab * 64 + lane) * CPL;
     const bool ok = c < A.dR;
+    // the last column of an odd row: its lane takes the pair that ends there
+    // and keeps the second half
+    const bool odd_end = PAIR && c + 1 == A.dR;
     // lanes past the row end gather column 0 (always present) instead of
     // masking every load; their store is the one thing skipped
-    const int cl = ok ? c : 0;
+    const int cl = !ok ? 0 : odd_end ? c - 1 : c;
     const int64_t dR = A.dR;
     const int step = HUBU_THREADS / 64 / ways;
     const int r0 = rg * A.rows_per_item + wave / ways;
@@ -2077,7 +2085,7 @@ __device__ __forceinline__ void hubU_item(const HubUArgs &A, int it) {
             for (int u = 0; u < HUBU_NB; ++u) {
                 const double *p = nb_src(k, j + u);
                 if constexpr (PAIR) {
-                    const double2 q = *(const double2 *)p;
+                    const pair8 q = *(const pair8 *)p;
                     v0[u] = q.x;
                     v1[u] = q.y;
                 } else {
@@ -2128,11 +2136,12 @@ __device__ __forceinline__ void hubU_item(const HubUArgs &A, int it) {
         if (ok) {
             double *dst = A.y + (int64_t)a * dR + c;
             if constexpr (PAIR) {
-                if constexpr (STREAM) {
-                    __builtin_nontemporal_store(acc0, dst);
-                    __builtin_nontemporal_store(acc1, dst + 1);
+                if (odd_end) {
+                    store_result<STREAM>(dst, acc1);
                 } else {
-                    *(double2 *)dst = make_double2(acc0, acc1);
+                    const pair8 q = {acc0, acc1};
+                    if constexpr (STREAM) __builtin_nontemporal_store(q, (pair8 *)dst);
+                    else *(pair8 *)dst = q;
                 }
             } else {
                 store_result<STREAM>(dst, acc0);
@@ -2402,8 +2411,7 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_hubU_batch(const HubUArgs *__r
     if (it >= n_items) return;
     const int p = batch_problem(off, n_probs, it);
     const HubUArgs A = probs[p];
-    const bool pair = (A.dR % 2 == 0) && !(((uintptr_t)A.x | (uintptr_t)A.y) & 15);
-    if (pair) hubU_item<true, false>(A, it - off[p]);
+    if (A.dR > 1) hubU_item<true, false>(A, it - off[p]);
     else hubU_item<false, false>(A, it - off[p]);
 }
 
@@ -2547,7 +2555,7 @@ static void launch_hubD(const HubDArgs &D, bool stream, dim3 grid, int xu, int p
 }
 
 hipError_t launch_hub6_left(const HubUArgs &U, int n_xcd, hipStream_t st) {
-    const bool pair = (U.dR % 2 == 0) && !(((uintptr_t)U.x | (uintptr_t)U.y) & 15);
+    const bool pair = U.dR > 1;
     const bool stream = (int64_t)U.n_rows * U.dR >= STREAM_STORE_MIN;
     const int xu = n_xcd == 1 ? 1 : 8;
     const int pu = (U.n_items + xu - 1) / xu;

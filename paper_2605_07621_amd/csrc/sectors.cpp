@@ -1353,7 +1353,7 @@ void spin_left_blocks(const ecut_sectors *s, int32_t rows_per_item, std::vector<
         L.lbase = B.lbase;
         L.item0 = item0;
         L.n_rgroups = (B.d_l + rows_per_item - 1) / rows_per_item;
-        L.n_slabs = (B.d_r + 63) / 64;
+        L.n_slabs = (B.d_r + 127) / 128;   // column pairs on 64 lanes
         item0 += L.n_rgroups * L.n_slabs;
         out.push_back(L);
     }
