@@ -327,7 +327,9 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
  *              items grouped by the left sites no cross term touches (so a
  *              group's rows are each other's cross-term source rows);
  *              n_xcd 1 deals items in launch order, else in 8 contiguous
- *              XCD ranges; tile as for variant 0; the vector is variant
+ *              XCD ranges; tile as for variant 0, but tile 0 makes every
+ *              row an item of its own where at most 4,096 rows have at most
+ *              256 amplitudes; the vector is variant
  *              0's bit for bit.  The spatial Hubbard cut (kernel 2,
  *              kernel_flags bit 6) takes variant 2 too: the same two passes
  *              with the fermion signs of hops inside the right part and

@@ -504,6 +504,7 @@ int32_t hub_column(const ecut_sectors *s, int64_t r);
 // order 0 largest first, 1 segments dealt to 8 XCD chunks (padded list);
 // returns the number of partial-sum slots
 int32_t make_spin_items(const ecut_sectors *s, int32_t tile, int32_t order, std::vector<ItemDev> &out);
+int32_t spin_tile(const ecut_sectors *s, const ApplyTuning &T);
 // The left operator's CSR (hl_ptr / hl_col / hl_val) with its rows permuted:
 // processing position p of a block takes the block's local row order[p]
 // (positions and rows counted from the block's lbase); entries keep their

@@ -30,9 +30,8 @@ constexpr int SPIN_M = 13;                   // element slots per thread of the 
 constexpr int SPIN_TILE = SPIN_THREADS * SPIN_M;
 constexpr int XTAB_SLOTS = 256;               // LDS doubles of a row's folded diagonal table (2^XR_MAX)
 constexpr int SPIN_MAX_FLIP = 64;            // flip-flop terms inside the right part
-constexpr int SPIN_SHORT_THREADS = 256;      // two-pass one-row items of rows up to 256 x 5 amplitudes
-constexpr int SPIN_SHORT_M = 5;
 constexpr int SPIN_MANY_THREADS = 256;       // kernel for items of several short rows
+constexpr int SPIN_FEW_ROWS = 4096;          // two-pass kernels: most short rows that are items of their own by default
 constexpr int SPIN_MANY_TILE = 512;          // most amplitudes per such item: the default and largest tile
 constexpr int HUBROW_THREADS = 1024;
 constexpr int HUBROW_P = 7;                  // column pairs per thread of the whole-row Hubbard kernel

@@ -1282,10 +1282,16 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_spinL(const SpinLArgs A, int n
     else hubU_item<false, STREAM>(U, it - L.item0);
 }
 
-// ONE: one-row items on NT1 threads with M1 amplitudes each (512 x 13 for
-// rows of up to 6,656 amplitudes, 256 x 5 for rows of up to 1,280); the
-// source-column tables replace the ranking tables, which only the items of
-// several rows (ONE = false) load.
+// ONE: one-row items on NT1 threads with M1 amplitudes each, by the longest
+// row of the problem: 256 x 2 (512 amplitudes), 256 x 5 (1,280), 512 x 4
+// (2,048), 512 x 7 (3,584) or 512 x 13 (6,656).  Rows of 1,716 on 512 x 4 instead
+// of 512 x 13: 25-site chain 116 -> 65 us an application, 26 sites 242 -> 153;
+// rows of 3,432 on 512 x 7: 28 sites 741 -> 579.  Staging every source row at
+// once behind one barrier (more registers, fewer groups) measured the same on
+// chains and slower with four left sites (6x4 lattice 71 -> 85 us) and with
+// fermion signs (58 -> 72 us at 12 sites).
+// The source-column tables replace the ranking tables, which only the items
+// of several rows (ONE = false) load.
 template <bool ONE, int NT1, int M1, bool FERM>
 __global__ __launch_bounds__(ONE ? NT1 : SPIN_MANY_THREADS, (ONE && NT1 == SPIN_THREADS) ? 4 : 2) void k_spinR(
     const ProblemDev P, const uint16_t *__restrict__ tab, const int64_t *__restrict__ tbase,
@@ -3181,14 +3187,22 @@ hipError_t launch_spin2(const SpinLArgs &L, const ProblemDev &P, const uint16_t 
         const dim3 g = grid_of(n_one, per);
         const int cap = std::max(max_d_r, 1) + 1;   // + the zero slot
         const size_t lds = (size_t)(cap + XTAB_SLOTS) * 8;   // then the folded diagonal table
-        const bool short_rows = max_d_r <= SPIN_SHORT_THREADS * SPIN_SHORT_M;
-#define ECUT_SPINR(NT_, M_, F_)                                                                              \
-    hipLaunchKernelGGL((k_spinR<true, NT_, M_, F_>), g, dim3(NT_), lds, st, P, tab, tbase, items_d, n_one, xu, per, cap)
-        if (short_rows && fermion) ECUT_SPINR(SPIN_SHORT_THREADS, SPIN_SHORT_M, true);
-        else if (short_rows) ECUT_SPINR(SPIN_SHORT_THREADS, SPIN_SHORT_M, false);
-        else if (fermion) ECUT_SPINR(SPIN_THREADS, SPIN_M, true);
-        else ECUT_SPINR(SPIN_THREADS, SPIN_M, false);
-#undef ECUT_SPINR
+        // threads x amplitudes per thread by the longest row: the slots past a
+        // row's end still run every loop, and fewer registers and threads keep
+        // more groups on a compute unit while one waits at its barriers
+        auto go = [&](auto kern, int nt) {
+            hipLaunchKernelGGL(kern, g, dim3(nt), lds, st, P, tab, tbase, items_d, n_one, xu, per, cap);
+        };
+        auto pick = [&](auto ferm) {
+            constexpr bool F = decltype(ferm)::value;
+            if (max_d_r <= 512) go(k_spinR<true, 256, 2, F>, 256);
+            else if (max_d_r <= 1280) go(k_spinR<true, 256, 5, F>, 256);
+            else if (max_d_r <= 2048) go(k_spinR<true, 512, 4, F>, 512);
+            else if (max_d_r <= 3584) go(k_spinR<true, 512, 7, F>, 512);
+            else go(k_spinR<true, SPIN_THREADS, SPIN_M, F>, SPIN_THREADS);
+        };
+        if (fermion) pick(std::true_type{});
+        else pick(std::false_type{});
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -1201,7 +1201,7 @@ static void build_spin_tables(ecut_sectors *s) {
     build_two_pass_tables(s, (int)s->lsites.size(), {});
     s->spin_ok = true;
     if (two_pass_rows(s, s->tune)) {   // the default of long vectors
-        s->item_slots = make_spin_items(s, SPIN_MANY_TILE, 2, s->items);
+        s->item_slots = make_spin_items(s, spin_tile(s, s->tune), 2, s->items);
         for (const ItemDev &it : s->items) s->sp_n_one += it.row1 - it.row0 == 1 ? 1 : 0;
     }
 }
@@ -1357,6 +1357,20 @@ void spin_left_blocks(const ecut_sectors *s, int32_t rows_per_item, std::vector<
         item0 += L.n_rgroups * L.n_slabs;
         out.push_back(L);
     }
+}
+
+// Tile of the spin kernels' short-row items under T.  The two-pass kernels make
+// every row its own item by default when few rows are short: the separate
+// launch of the several-row items would cost more than their idle threads
+// (24-site chain: 598 rows of at most 256 amplitudes, 20 us in items of 512).
+int32_t spin_tile(const ecut_sectors *s, const ApplyTuning &T) {
+    if (T.tile > 0) return T.tile;
+    if (two_pass_rows(s, T)) {
+        int64_t rows = 0;
+        for (const BlockDev &B : s->blocks) rows += B.d_r <= SPIN_MANY_TILE / 2 ? B.d_l : 0;
+        if (rows <= SPIN_FEW_ROWS) return 1;
+    }
+    return SPIN_MANY_TILE;
 }
 
 // Work items of the spin kernel: a row longer than half the tile is an item of

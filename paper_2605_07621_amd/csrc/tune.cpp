@@ -129,7 +129,7 @@ ecut_status apply_tuning(ecut_sectors *s, const ApplyTuning &T) {
             if (e != hipSuccess) return hip_fail(e, "hipMemcpy(work order)");
         }
     }
-    const int32_t tile = T.tile > 0 ? T.tile : SPIN_MANY_TILE, cur = s->tune.tile > 0 ? s->tune.tile : SPIN_MANY_TILE;
+    const int32_t tile = spin_tile(s, T), cur = spin_tile(s, s->tune);
     const bool two = two_pass_rows(s, T), cur_two = two_pass_rows(s, s->tune);
     const int32_t spin_order = two ? 2 : T.order, cur_order = cur_two ? 2 : s->tune.order;
     if (s->spin_ok && (tile != cur || spin_order != cur_order)) {

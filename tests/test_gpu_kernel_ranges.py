@@ -160,3 +160,26 @@ def test_left_pass_on_panels_vs_oracle(dev, n, n_up, n_dn, variant):
     if s.dim < 500000:
         ref = O.Sector(p.model, n_up, n_dn).apply(s.export(x).cpu().numpy())
         assert np.linalg.norm(s.export(y).cpu().numpy() - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+# threads and amplitudes per thread of the two-pass right kernel by the longest
+# row: 512, 1280, 2048, 3584, 6656; cuts whose longest row ends at or beside them
+@pytest.mark.parametrize("n,cut,n_up,d_r", [(16, 7, 8, 126), (18, 7, 9, 462), (20, 8, 10, 924), (22, 9, 9, 1716),
+                                            (17, 4, 6, 1716), (20, 6, 9, 3432), (17, 2, 8, 6435), (19, 3, 10, 12870)])
+def test_two_pass_row_lengths(dev, n, cut, n_up, d_r):
+    """The two-pass spin kernels at every row class against the one-pass
+    kernel and the flat kernel (bit for bit) and the oracle (1e-12), with the
+    short rows packed and as items of their own."""
+    import oracle as O
+    p = I.Problem(I.xxz_chain(n, 1.0, 0.9, periodic=True), I.Cut("spatial", I.left_mask_first(cut)), n_up)
+    s = ecut.Sectors.from_problem(p)
+    assert s.info.max_d_r == d_r
+    x = _vec(s.dim, 110 + n, dev)
+    y = s.apply(x)
+    ref = O.Sector(p.model, n_up).apply(s.export(x).cpu().numpy())
+    assert np.linalg.norm(s.export(y).cpu().numpy() - ref) <= 1e-12 * np.linalg.norm(ref)
+    if not s.info.kernel_flags & 64:
+        return   # rows too long for the two-pass kernels: the generic kernel
+    for t in (dict(variant=2), dict(variant=2, tile=256), dict(tile=512), dict(variant=2, grid=8, n_xcd=1)):
+        s.set_tuning(**t)
+        assert torch.equal(s.apply(x), y), t
