@@ -15,8 +15,11 @@
 #include <algorithm>
 #include <cmath>
 #include <map>
+#include <mutex>
 #include <numeric>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "ecut_internal.h"
@@ -26,20 +29,70 @@ using namespace ecut;
 
 namespace {
 
-// one rocBLAS handle per thread and device
-ecut_status blas_handle(rocblas_handle *h) {
-    static thread_local std::map<int, rocblas_handle> handles;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return fail(ECUT_EDEVICE, "hipGetDevice");
-    auto it = handles.find(dev);
-    if (it == handles.end()) {
-        rocblas_handle nh = nullptr;
-        if (rocblas_create_handle(&nh) != rocblas_status_success) return fail(ECUT_EDEVICE, "rocblas_create_handle");
-        it = handles.emplace(dev, nh).first;
-    }
-    *h = it->second;
-    return ECUT_OK;
+// A rocBLAS handle with a stream of its own.  The eigensolver is a chain of
+// thousands of small launches per matrix size, so the sizes run side by side,
+// each chain on a lane: the lanes of a call are taken from a process-wide pool
+// and go back to it; the pool keeps at most LANES_KEPT idle ones per device.
+constexpr int LANES = 4;          // per call: the hardware queues of a process
+constexpr size_t LANES_KEPT = 8;
+
+struct Lane {
+    rocblas_handle h = nullptr;
+    hipStream_t st = nullptr;
+    hipEvent_t ev = nullptr;
+};
+
+std::mutex g_lane_mu;
+std::map<int, std::vector<Lane>> g_lanes;   // idle lanes by device
+
+void drop_lane(Lane &l) {
+    if (l.h) (void)rocblas_destroy_handle(l.h);
+    if (l.ev) (void)hipEventDestroy(l.ev);
+    if (l.st) (void)hipStreamDestroy(l.st);
+    l = Lane{};
 }
+
+// The lanes of one call on the current device.  The destructor waits for their
+// work (it reads and writes the caller's memory) before it hands them back.
+struct LaneSet {
+    int dev = -1;
+    std::vector<Lane> lanes;
+
+    ecut_status take(int n) {
+        if (hipGetDevice(&dev) != hipSuccess) return fail(ECUT_EDEVICE, "hipGetDevice");
+        {
+            std::lock_guard<std::mutex> g(g_lane_mu);
+            auto &idle = g_lanes[dev];
+            while ((int)lanes.size() < n && !idle.empty()) {
+                lanes.push_back(idle.back());
+                idle.pop_back();
+            }
+        }
+        while ((int)lanes.size() < n) {
+            Lane l;
+            const bool ok = hipStreamCreateWithFlags(&l.st, hipStreamNonBlocking) == hipSuccess &&
+                            hipEventCreateWithFlags(&l.ev, hipEventDisableTiming) == hipSuccess &&
+                            rocblas_create_handle(&l.h) == rocblas_status_success &&
+                            rocblas_set_stream(l.h, l.st) == rocblas_status_success;
+            if (!ok) {
+                drop_lane(l);
+                return fail(ECUT_EDEVICE, "rocblas_create_handle");
+            }
+            lanes.push_back(l);
+        }
+        return ECUT_OK;
+    }
+
+    ~LaneSet() {
+        for (Lane &l : lanes) (void)hipStreamSynchronize(l.st);
+        std::lock_guard<std::mutex> g(g_lane_mu);
+        auto &idle = g_lanes[dev];
+        for (Lane &l : lanes) {
+            if (idle.size() < LANES_KEPT) idle.push_back(l);
+            else drop_lane(l);
+        }
+    }
+};
 
 int64_t schmidt_count(const ecut_sectors *s) {
     int64_t n = 0;
@@ -77,20 +130,16 @@ std::map<int, std::vector<int32_t>> gram_groups(const ecut_sectors *s) {
 
 extern "C" {
 
-// Workspace: the Gram matrices of the largest group of equal-size blocks,
-// the eigenvalues of every block, the eigensolver's off-diagonals for that
-// group, one status word per block.
+// Workspace: the Gram matrices of every block, its eigenvalues, the
+// eigensolver's off-diagonals, one status word per block (the groups of equal
+// sizes run side by side).
 size_t ecut_entanglement_sizes(const ecut_sectors *s, size_t *n_lambda) {
     if (!s) return 0;
-    size_t g_max = 0, e_max = 0;
-    for (const auto &kv : gram_groups(s)) {
-        const size_t m = (size_t)kv.first, c = kv.second.size();
-        g_max = std::max(g_max, c * m * m);
-        e_max = std::max(e_max, c * m);
-    }
+    size_t grams = 0;
+    for (const auto &kv : gram_groups(s)) grams += kv.second.size() * (size_t)kv.first * (size_t)kv.first;
     const size_t nl = (size_t)schmidt_count(s);
     if (n_lambda) *n_lambda = nl;
-    return g_max + nl + e_max + (s->blocks.size() + 1) / 2 + 1;
+    return grams + 2 * nl + (s->blocks.size() + 1) / 2 + 1;
 }
 
 ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_d, double cutoff, int32_t n_parts,
@@ -108,46 +157,108 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
             if (part_of_block[q] < 0 || part_of_block[q] >= n_parts) return fail(ECUT_EINVAL, "part_of_block out of range");
     for (const BlockDev &B : s->blocks)
         if (std::min(B.d_l, B.d_r) > (1 << 24)) return fail(ECUT_EUNSUPPORTED, "block too large for the Gram matrix");
-    rocblas_handle h = nullptr;
-    ecut_status st = blas_handle(&h);
-    if (st != ECUT_OK) return st;
     const hipStream_t hs = (hipStream_t)stream;
-    if (rocblas_set_stream(h, hs) != rocblas_status_success) return fail(ECUT_EDEVICE, "rocblas_set_stream");
     const auto groups = gram_groups(s);
-    size_t g_max = 0;
-    for (const auto &kv : groups) g_max = std::max(g_max, kv.second.size() * (size_t)kv.first * (size_t)kv.first);
+    size_t grams = 0;
+    for (const auto &kv : groups) grams += kv.second.size() * (size_t)kv.first * (size_t)kv.first;
     const int64_t n_lam = schmidt_count(s);
+    LaneSet set;
+    ecut_status st = set.take(std::max(1, std::min<int>(LANES, (int)groups.size())));
+    if (st != ECUT_OK) return st;
+    // the lanes start after the caller's work on its stream
+    hipError_t le = hipEventRecord(set.lanes[0].ev, hs);
+    for (Lane &l : set.lanes)
+        if (le == hipSuccess) le = hipStreamWaitEvent(l.st, set.lanes[0].ev, 0);
+    if (le != hipSuccess) return hip_fail(le, "entanglement lanes");
     // per group of equal-size blocks: their Gram matrices side by side
     // (rocBLAS syrk each), one batched eigensolve; the eigenvalues of every
-    // group side by side, one copy to the host at the end
-    double *G = workspace_d, *Dg = workspace_d + g_max, *E = Dg + n_lam;
-    size_t e_max = 0;
-    for (const auto &kv : groups) e_max = std::max(e_max, kv.second.size() * (size_t)kv.first);
-    rocblas_int *info = (rocblas_int *)(E + e_max);
+    // group side by side, one copy to the host at the end.  The longest chain
+    // goes first, each group to the lane with the least work so far (the
+    // solver's launches grow with the size, not with the number of blocks).
+    double *G = workspace_d, *Dg = workspace_d + grams, *E = Dg + n_lam;
+    rocblas_int *info = (rocblas_int *)(E + n_lam);
     const double one = 1.0, zero = 0.0;
+    struct Group {
+        int m;
+        const std::vector<int32_t> *q;
+        size_t g;
+        int64_t off;
+        int32_t info;
+    };
+    std::vector<Group> work;
     int64_t goff = 0;
     int32_t ioff = 0;
+    size_t go = 0;
     for (const auto &kv : groups) {
-        const int m = kv.first;
-        const int c = (int)kv.second.size();
-        for (int i = 0; i < c; ++i) {
-            const BlockDev &B = s->blocks[kv.second[i]];
-            // Psi_q is row-major d_L x d_R: column-major it is A (d_R x d_L, lda = d_R)
-            const double *A = psi_d + B.offset;
-            const bool left = B.d_l <= B.d_r;   // Psi Psi^T = A^T A (d_L x d_L), else Psi^T Psi = A A^T
-            rocblas_status rs =
-                rocblas_dsyrk(h, rocblas_fill_upper, left ? rocblas_operation_transpose : rocblas_operation_none, m,
-                              left ? B.d_r : B.d_l, &one, A, B.d_r, &zero, G + (size_t)i * m * m, m);
-            if (rs != rocblas_status_success) return fail(ECUT_EDEVICE, "rocblas_dsyrk: status " + std::to_string((int)rs));
-        }
-        const rocblas_status rs = rocsolver_dsyevd_strided_batched(h, rocblas_evect_none, rocblas_fill_upper, m, G, m,
-                                                                   (rocblas_stride)m * m, Dg + goff, m, E, m,
-                                                                   info + ioff, c);
-        if (rs != rocblas_status_success)
-            return fail(ECUT_EDEVICE, "rocsolver_dsyevd_strided_batched: status " + std::to_string((int)rs));
-        goff += (int64_t)c * m;
-        ioff += c;
+        work.push_back(Group{kv.first, &kv.second, go, goff, ioff});
+        go += kv.second.size() * (size_t)kv.first * (size_t)kv.first;
+        goff += (int64_t)kv.second.size() * kv.first;
+        ioff += (int32_t)kv.second.size();
     }
+    std::vector<int64_t> load(set.lanes.size(), 0);
+    std::vector<std::vector<const Group *>> todo(set.lanes.size());
+    for (auto it = work.rbegin(); it != work.rend(); ++it) {
+        const size_t lane = std::min_element(load.begin(), load.end()) - load.begin();
+        load[lane] += it->m;
+        todo[lane].push_back(&*it);
+    }
+    // one thread per lane: the chains are so many launches that one thread's
+    // launch rate would bound them (14-site spatial Hubbard cut, 64 blocks of
+    // up to 1,225 x 1,225: one chain 82 ms, four lanes from one thread 62, from
+    // four 55; 12 sites 26 -> 14.5 ms)
+    struct Err {
+        const char *what;
+        int status;
+    };
+    std::vector<Err> err(set.lanes.size(), Err{nullptr, 0});
+    auto enqueue = [&](size_t lane) {   // on a thread of its own: reports by err only
+        if (hipSetDevice(set.dev) != hipSuccess) {
+            err[lane] = Err{"hipSetDevice", 0};
+            return;
+        }
+        const rocblas_handle h = set.lanes[lane].h;
+        for (const Group *W : todo[lane]) {
+            const int m = W->m, c = (int)W->q->size();
+            for (int i = 0; i < c; ++i) {
+                const BlockDev &B = s->blocks[(*W->q)[i]];
+                // Psi_q is row-major d_L x d_R: column-major it is A (d_R x d_L, lda = d_R)
+                const double *A = psi_d + B.offset;
+                const bool left = B.d_l <= B.d_r;   // Psi Psi^T = A^T A (d_L x d_L), else Psi^T Psi = A A^T
+                const rocblas_status rs =
+                    rocblas_dsyrk(h, rocblas_fill_upper, left ? rocblas_operation_transpose : rocblas_operation_none, m,
+                                  left ? B.d_r : B.d_l, &one, A, B.d_r, &zero, G + W->g + (size_t)i * m * m, m);
+                if (rs != rocblas_status_success) {
+                    err[lane] = Err{"rocblas_dsyrk", (int)rs};
+                    return;
+                }
+            }
+            const rocblas_status rs = rocsolver_dsyevd_strided_batched(
+                h, rocblas_evect_none, rocblas_fill_upper, m, G + W->g, m, (rocblas_stride)m * m, Dg + W->off, m,
+                E + W->off, m, info + W->info, c);
+            if (rs != rocblas_status_success) {
+                err[lane] = Err{"rocsolver_dsyevd_strided_batched", (int)rs};
+                return;
+            }
+        }
+    };
+    std::vector<std::thread> threads(set.lanes.size());
+    for (size_t lane = 1; lane < set.lanes.size(); ++lane) {
+        try {
+            threads[lane] = std::thread(enqueue, lane);
+        } catch (const std::system_error &) {   // no thread to be had: this one does its work
+            enqueue(lane);
+        }
+    }
+    enqueue(0);
+    for (std::thread &t : threads)
+        if (t.joinable()) t.join();
+    for (const Err &e : err)
+        if (e.what) return fail(ECUT_EDEVICE, std::string(e.what) + ": status " + std::to_string(e.status));
+    for (Lane &l : set.lanes) {   // the copies below follow every lane
+        if (le == hipSuccess) le = hipEventRecord(l.ev, l.st);
+        if (le == hipSuccess) le = hipStreamWaitEvent(hs, l.ev, 0);
+    }
+    if (le != hipSuccess) return hip_fail(le, "entanglement lanes");
     std::vector<double> ev((size_t)n_lam);
     std::vector<rocblas_int> inf((size_t)std::max(ioff, 1), 0);
     hipError_t e = n_lam ? hipMemcpyAsync(ev.data(), Dg, sizeof(double) * n_lam, hipMemcpyDeviceToHost, hs) : hipSuccess;

@@ -183,3 +183,38 @@ def test_two_pass_row_lengths(dev, n, cut, n_up, d_r):
     for t in (dict(variant=2), dict(variant=2, tile=256), dict(tile=512), dict(variant=2, grid=8, n_xcd=1)):
         s.set_tuning(**t)
         assert torch.equal(s.apply(x), y), t
+
+
+def test_entanglement_lanes_and_threads(dev):
+    """The spectrum with one, two and many block sizes (one to four lanes):
+    the values of a second call, of a call that follows work on another
+    stream and of calls from three threads at once equal the first call's bit
+    for bit, and its weights sum to one (1e-12)."""
+    import threading
+    probs = [I.Problem(I.xxz_chain(9, 1.0, 0.7), I.Cut("spatial", 1), 4),
+             I.Problem(I.xxz_chain(10, 1.0, 0.7), I.Cut("spatial", 3), 5),
+             I.Problem(I.hubbard_chain(8, 1.0, 4.0, V=0.5), I.Cut("spatial", I.left_mask_first(4)), 4, 4)]
+    for p in probs:
+        s = ecut.Sectors.from_problem(p)
+        x = _vec(s.dim, 7, dev)
+        ref = s.entanglement(x)
+        assert abs(ref["w_q"].sum() - 1.0) <= 1e-12
+        got = []
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            got.append(s.entanglement(2.0 * (0.5 * x)))
+
+        def call():
+            torch.cuda.set_device(dev)
+            got.append(s.entanglement(x, stream=torch.cuda.Stream()))
+
+        torch.cuda.synchronize()
+        ts = [threading.Thread(target=call) for _ in range(3)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        assert len(got) == 4
+        for r in got + [s.entanglement(x)]:
+            assert np.array_equal(np.concatenate(r["lam"]), np.concatenate(ref["lam"])), p.model.name
