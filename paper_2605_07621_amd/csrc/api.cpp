@@ -481,8 +481,8 @@ bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T) {
     if (!s->flat_base.empty() || !default_tuning(T)) return false;
     // on the spatial Hubbard cut every row is an item of its own, on threads
     // for the longest one: by default only where the mean row is a quarter of
-    // it (14 sites at half filling, 719 of 1,225: 288 against 396 us on the
-    // row kernel; 16 sites with 5 + 5 particles, 320 of 4,900: 1.90 against 1.28 ms)
+    // it (14 sites at half filling, 719 of 1,225: 240 against 396 us on the
+    // row kernel; 16 sites with 5 + 5 particles, 320 of 4,900: 1.74 against 0.75 ms)
     if (!s->hub_spatial) return true;
     int64_t rows = 0;
     for (const BlockDev &B : s->blocks) rows += B.d_l;

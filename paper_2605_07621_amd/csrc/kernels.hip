@@ -767,19 +767,34 @@ hipError_t launch_hubrow(const ecut_sectors *s, const ProblemDev &prob, const in
 // two-pass kernels' left pass) and is read as the starting value.
 // tabR / tabX (given exactly when !LEFT, the two-pass right kernel): the
 // block's source-column tables of the right flip-flop terms and the cross
-// terms, instead of ranking the flipped words (fermion cut: the column,
-// 0xffff for no term; spin cut: the column's byte offset in xs, 8 * dR, the
-// zero slot, for no term, and for a cross term the source row's zero slot
-// minus the column's byte offset); the terms are summed in the same order
-// either way.
+// terms, instead of ranking the flipped words (the column's byte offset in
+// xs, 8 * dR, the zero slot, for no term, and for a cross term the source
+// row's zero slot minus the column's byte offset; a fermion cut's sign in bit
+// 0); the terms are summed in the same order either way.
 // FERM: the spatial Hubbard cut's cross terms (block by the mode's spin,
-// fermion signs from the maps and the tables' bit 15) and right hops with
+// fermion signs from the maps and the tables' bit 0) and right hops with
 // signs; spin problems compile without them.
 static_assert(XTAB_SLOTS >= (1 << XR_MAX), "a table entry for every pattern of the folded sites");
 
 // the staged element at byte offset off of xs (a spin cut's table entry)
 __device__ __forceinline__ double lds_at(const double *xs, uint32_t off) {
     return *(const double *)((const char *)xs + off);
+}
+
+// Read-only data at a uniform address, in the constant address space: scalar
+// loads also after a barrier or a store, where the compiler cannot show by
+// itself that nothing has changed the data (a row's bonds, maps and block
+// descriptors: the right pass of the 14-site spatial cut 171 -> 150 us).
+template <typename T>
+using ConstPtr = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ ConstPtr<T> uniform_ptr(const T *p) {
+    return (ConstPtr<T>)(uintptr_t)p;
+}
+
+// v with its sign flipped where bit 0 of the table entry is set
+__device__ __forceinline__ double signed_by(double v, uint32_t entry) {
+    return __hiloint2double(__double2hiint(v) ^ (int)(entry << 31), __double2loint(v));
 }
 
 template <int NT, int M, bool LEFT, bool FERM = false>
@@ -793,7 +808,9 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
     const int dR = B.d_r;
     const int l = W.row0;
     const int gl = B.lbase + l;
-    const uint32_t lw = P.lwords[gl];
+    const uint32_t lw = uniform_ptr(P.lwords)[gl];
+    const ConstPtr<XBondDev> XB = uniform_ptr(P.xbond);
+    const ConstPtr<double> coef = uniform_ptr(P.rflip_coef);
     const double *__restrict__ xblk = P.x + B.offset;
     const double *__restrict__ xt = xblk + (int64_t)l * dR;
     double acc[M];
@@ -803,6 +820,20 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
         const int e = tid + m * NT;
         wr[m] = e < dR ? P.rwords[B.rbase + e] : 0u;
         acc[m] = 0.0;
+    }
+    // rows short enough for the registers: the own row, a bond's first table
+    // entries and the first right words are loaded ahead of the barriers they
+    // would otherwise wait behind (14-site spatial cut 248 -> 240 us; 25-site
+    // chain 67.8 -> 65.9, but 23 sites on 256 threads 25.2 -> 26.5 and 28 sites
+    // on 7 slots 609 -> 638, where the registers cost a group)
+    constexpr bool EARLY = !LEFT && (FERM ? M <= 10 : M <= 5 && NT == 512);
+    double xv[M];
+    if (EARLY) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int e = tid + m * NT;
+            xv[m] = e < dR ? xt[e] : 0.0;
+        }
     }
     if (!LEFT) {
         double *__restrict__ yt = P.y + B.offset + (int64_t)l * dR;
@@ -833,76 +864,86 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
     const int nx = P.n_xbond;
     int k = 0;
     while (k < nx) {
-        const int li = P.xbond[k].li;
+        const int li = XB[k].li;
         int k1 = k + 1;
-        while (k1 < nx && P.xbond[k1].li == li) ++k1;
+        while (k1 < nx && XB[k1].li == li) ++k1;
         const uint32_t bl = (lw >> li) & 1u;
         // the block with one particle of this mode's kind more or fewer on the left
         int src;
         if constexpr (FERM)
-            src = P.xbond[k].label ? (bl ? B.blk_l2minus : B.blk_l2plus) : (bl ? B.blk_lminus : B.blk_lplus);
+            src = XB[k].label ? (bl ? B.blk_l2minus : B.blk_l2plus) : (bl ? B.blk_lminus : B.blk_lplus);
         else
             src = bl ? B.blk_lminus : B.blk_lplus;
-        int lp = src >= 0 ? P.maps[(bl ? P.xbond[k].lmap_del : P.xbond[k].lmap_ins) + gl] : -1;
+        int lp = src >= 0 ? uniform_ptr(P.maps)[(bl ? XB[k].lmap_del : XB[k].lmap_ins) + gl] : -1;
         bool lneg = false;   // fermions: the left part's sign, in the map's low bit
         if (FERM && lp >= 0) {
             lneg = lp & 1;
             lp >>= 1;
         }
         if (lp >= 0) {
-            const BlockDev S = P.blocks[src];
-            const double *__restrict__ srow = P.x + S.offset + (int64_t)lp * S.d_r;
+            const int sd = uniform_ptr(P.blocks)[src].d_r;
+            const double *__restrict__ srow = P.x + uniform_ptr(P.blocks)[src].offset + (int64_t)lp * sd;
             // every row of a problem on this kernel fits NT * M elements; all
             // loads of the row are in flight before the barrier
             double sv[M];
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 const int e = tid + m * NT;
-                sv[m] = e < S.d_r ? srow[e] : 0.0;
+                sv[m] = e < sd ? srow[e] : 0.0;
+            }
+            uint32_t s0[M];
+            if constexpr (EARLY) {
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int e = tid + m * NT;
+                    s0[m] = e < dR ? tabX[(int64_t)k * dR + e] : 0u;
+                }
             }
             __syncthreads();   // earlier readers of xs are done
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 const int e = tid + m * NT;
-                if (e < S.d_r) xs[e] = sv[m];
+                if (e < sd) xs[e] = sv[m];
             }
-            if (!FERM && !LEFT && tid == 0) xs[S.d_r] = 0.0;   // the slot a term that does not apply reads
+            if (!LEFT && tid == 0) xs[sd] = 0.0;   // the slot a term that does not apply reads
             __syncthreads();
             const uint32_t flipm = bl ? ~0u : 0u;   // bit rj of w ^ flipm: the term applies
-            const int32_t zs = 8 * S.d_r;            // the zero slot's byte offset
+            const int32_t zs = 8 * sd;            // the zero slot's byte offset
             for (int kk = k; kk < k1; ++kk) {
-                const int rj = P.xbond[kk].rj;
-                const double c = lneg ? -P.xbond[kk].coef : P.xbond[kk].coef;
+                const int rj = XB[kk].rj;
+                const double c = lneg ? -XB[kk].coef : XB[kk].coef;
                 if constexpr (!LEFT) {   // from the table
                     uint32_t sx[M];
 #pragma unroll
                     for (int m = 0; m < M; ++m) {
                         const int e = tid + m * NT;
-                        sx[m] = e < dR ? tabX[(int64_t)kk * dR + e] : 0u;
+                        if (EARLY && kk == k) sx[m] = s0[m];
+                        else sx[m] = e < dR ? tabX[(int64_t)kk * dR + e] : 0u;
                     }
-                    if constexpr (FERM) {
+                    // branch-free: a term that does not apply adds c * 0 from
+                    // the zero slot, so all reads of the bond are in flight
+                    // together. The entry is the zero slot minus the source
+                    // column (bytes) and the sign in bit 0; the sign-extended
+                    // bit test (-1 where the term applies, bit rj of the word
+                    // differing from bl) scales it. A slot past the row end
+                    // (sx 0) reads the zero slot, and its sum is never stored.
+                    constexpr int C = FERM ? 7 : M;   // slots at a time: the signs take registers
 #pragma unroll
-                        for (int m = 0; m < M; ++m) {
-                            const int e = tid + m * NT;
-                            if (e < dR && ((wr[m] >> rj) & 1u) != bl)
-                                acc[m] += (sx[m] & 0x8000u ? -c : c) * xs[sx[m] & 0x7fffu];
-                        }
-                    } else {
-                        // branch-free: a term that does not apply adds c * 0 from
-                        // the zero slot, so all reads of the bond are in flight
-                        // together. The entry is the zero slot minus the source
-                        // column (bytes); the sign-extended bit test (-1 where the
-                        // term applies, bit rj of the word differing from bl)
-                        // scales it. A slot past the row end (sx 0) reads the
-                        // zero slot, and its sum is never stored.
-                        double v[M];
+                    for (int m0 = 0; m0 < M; m0 += C) {
+                        double v[C];
 #pragma unroll
-                        for (int m = 0; m < M; ++m) {
+                        for (int u = 0; u < C; ++u) {
+                            const int m = m0 + u;
+                            if (m >= M) break;
                             const int32_t on = __builtin_amdgcn_sbfe((int32_t)(wr[m] ^ flipm), rj, 1);
-                            v[m] = lds_at(xs, (uint32_t)(zs + on * (int32_t)sx[m]));
+                            v[u] = lds_at(xs, (uint32_t)(zs + on * (int32_t)(FERM ? sx[m] & ~7u : sx[m])));
                         }
 #pragma unroll
-                        for (int m = 0; m < M; ++m) acc[m] += c * v[m];
+                        for (int u = 0; u < C; ++u) {
+                            const int m = m0 + u;
+                            if (m >= M) break;
+                            acc[m] += c * (FERM ? signed_by(v[u], sx[m]) : v[u]);
+                        }
                     }
                 } else {
 #pragma unroll
@@ -917,12 +958,22 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
         k = k1;
     }
     // the item's own row
-    {
-        double xv[M];
+    const uint64_t none4 = (uint64_t)(8u * dR) * 0x0001000100010001ull;   // slots past the row's end
+    uint64_t tw[M];
+    if constexpr (EARLY) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             const int e = tid + m * NT;
-            xv[m] = e < dR ? xt[e] : 0.0;
+            tw[m] = n_flip > 0 && e < dR ? *(const uint64_t *)(tabR + (int64_t)e * 4) : none4;
+        }
+    }
+    {
+        if (!EARLY) {
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const int e = tid + m * NT;
+                xv[m] = e < dR ? xt[e] : 0.0;
+            }
         }
         __syncthreads();   // readers of the last source row are done
 #pragma unroll
@@ -930,7 +981,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
             const int e = tid + m * NT;
             if (e < dR) xs[e] = xv[m];
         }
-        if (!FERM && !LEFT && tid == 0) xs[dR] = 0.0;   // the slot a term that does not apply reads
+        if (!LEFT && tid == 0) xs[dR] = 0.0;   // the slot a term that does not apply reads
         if (!LEFT && !FERM && P.n_xr > 0 && tid < (1 << P.n_xr)) {
             // the row's Sz Sz cross terms for every pattern of the n_xr right
             // sites: t = sum_g (bit g ? +1 : -1) xdl[gl][g], in g order
@@ -944,7 +995,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
         __syncthreads();
     }
     // right operator from the staged row, diagonal, epilogue
-    double dgl = P.diag_l[gl];
+    double dgl = uniform_ptr(P.diag_l)[gl];
     double xh[XR_MAX];   // one pass: the row's folded Sz Sz cross terms
 #pragma unroll
     for (int g = 0; g < XR_MAX; ++g) xh[g] = LEFT && !FERM && g < P.n_xr ? P.xdl[(int64_t)gl * P.n_xr + g] : 0.0;
@@ -952,47 +1003,37 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
     double ra[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) ra[m] = 0.0;
-    if constexpr (!LEFT && FERM) {   // four terms' source columns (and signs) per 8-byte load
+    if constexpr (!LEFT) {   // four terms' source columns (and signs) per 8-byte load
+        // branch-free: the table holds 8 * dR, the byte offset of the zero
+        // slot xs[dR], for "no term" (and in its pads); slots past the row end
+        // take four of them
         for (int g = 0; g * 4 < n_flip; ++g) {
             uint64_t t[M];
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 const int e = tid + m * NT;
-                t[m] = e < dR ? *(const uint64_t *)(tabR + ((int64_t)g * dR + e) * 4) : ~0ull;
+                if (EARLY) t[m] = tw[m];
+                else t[m] = e < dR ? *(const uint64_t *)(tabR + ((int64_t)g * dR + e) * 4) : none4;
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int f = 4 * g + i;
-                if (f >= n_flip) break;
-                const double cf = fc[f];
+            if (EARLY && 4 * g + 4 < n_flip) {
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
-                    const uint32_t src = (uint32_t)(t[m] >> (16 * i)) & 0xffffu;
-                    if (src != 0xffffu) ra[m] += (src & 0x8000u ? -cf : cf) * xs[src & 0x7fffu];
+                    const int e = tid + m * NT;
+                    tw[m] = e < dR ? *(const uint64_t *)(tabR + ((int64_t)(g + 1) * dR + e) * 4) : none4;
                 }
-            }
-        }
-    } else if constexpr (!LEFT) {   // four terms' source columns per 8-byte load
-        // branch-free: a spin cut's table holds 8 * dR, the byte offset of the
-        // zero slot xs[dR], for "no term" (and in its pads); slots past the
-        // row end take four of them
-        const uint64_t none4 = (uint64_t)(8u * dR) * 0x0001000100010001ull;
-        for (int g = 0; g * 4 < n_flip; ++g) {
-            uint64_t t[M];
-#pragma unroll
-            for (int m = 0; m < M; ++m) {
-                const int e = tid + m * NT;
-                t[m] = e < dR ? *(const uint64_t *)(tabR + ((int64_t)g * dR + e) * 4) : none4;
             }
             double cf[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) cf[i] = 4 * g + i < n_flip ? fc[4 * g + i] : 0.0;
+            for (int i = 0; i < 4; ++i) cf[i] = coef[4 * g + i];   // padded with zeros to whole words
             // per slot: the 4 terms' reads in flight together, then summed in term order
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 double v[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = lds_at(xs, (uint32_t)(t[m] >> (16 * i)) & 0xffffu);
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t en = (uint32_t)(t[m] >> (16 * i)) & 0xffffu;
+                    v[i] = FERM ? signed_by(lds_at(xs, en & ~7u), en) : lds_at(xs, en);
+                }
                 // the last word's pad entries are the zero slot's offset and
                 // their coefficients 0, so all 4 terms are summed unguarded
 #pragma unroll
@@ -1012,6 +1053,27 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
             ra[m] = e < dR ? P.diag_r[B.rbase + e] : 0.0;
         }
     }
+    if constexpr (FERM) {
+        // the density terms across the cut (V n_i n_j), term by term for all
+        // slots: a term's numbers are loaded once and its left density is the row's
+#pragma unroll
+        for (int m = 0; m < M; ++m) ra[m] = dgl + ra[m];
+        for (int x = 0; x < P.n_xdiag; ++x) {
+            const ConstPtr<XDiagDev> D = uniform_ptr(P.xdiag) + x;
+            const int rj = D->rj, rj2 = D->rj2, spin_form = D->spin_form;
+            double fl = (double)((lw >> D->li) & 1u);
+            if (D->li2 >= 0) fl += (double)((lw >> D->li2) & 1u);
+            if (spin_form) fl -= 0.5;
+            const double cl = D->coef * fl;
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                double fr = (double)((wr[m] >> rj) & 1u);
+                if (rj2 >= 0) fr += (double)((wr[m] >> rj2) & 1u);
+                if (spin_form) fr -= 0.5;
+                ra[m] += cl * fr;
+            }
+        }
+    }
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         const int e = tid + m * NT;
@@ -1023,7 +1085,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
                 const uint32_t msk = fm[f];
                 if (__popc(w & msk) == 1) a += fc[f] * xs[rank16(w ^ msk, rl, rh)];
             }
-        double dg = dgl + (LEFT ? P.diag_r[B.rbase + e] : ra[m]);
+        double dg = FERM ? ra[m] : dgl + (LEFT ? P.diag_r[B.rbase + e] : ra[m]);
         if (!FERM && P.n_xr > 0) {
             if constexpr (LEFT) {   // one pass: the table entry's sum, computed in place
                 double t = 0.0;
@@ -1041,21 +1103,10 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
                 }
                 dg += xtab[ix];
             }
-        } else {
+        } else if constexpr (!FERM) {
             for (int x = 0; x < P.n_xdiag; ++x) {
                 const XDiagDev X = P.xdiag[x];
-                if constexpr (FERM) {   // densities of the two sites (V n_i n_j)
-                    double fl = (double)((lw >> X.li) & 1u), fr = (double)((w >> X.rj) & 1u);
-                    if (X.li2 >= 0) fl += (double)((lw >> X.li2) & 1u);
-                    if (X.rj2 >= 0) fr += (double)((w >> X.rj2) & 1u);
-                    if (X.spin_form) {
-                        fl -= 0.5;
-                        fr -= 0.5;
-                    }
-                    dg += X.coef * fl * fr;
-                } else {
-                    dg += X.coef * ((double)((lw >> X.li) & 1u) - 0.5) * ((double)((w >> X.rj) & 1u) - 0.5);
-                }
+                dg += X.coef * ((double)((lw >> X.li) & 1u) - 0.5) * ((double)((w >> X.rj) & 1u) - 0.5);
             }
         }
         const double x0 = xs[e];
@@ -1290,6 +1341,13 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_spinL(const SpinLArgs A, int n
 // once behind one barrier (more registers, fewer groups) measured the same on
 // chains and slower with four left sites (6x4 lattice 71 -> 85 us) and with
 // fermion signs (58 -> 72 us at 12 sites).
+// FERM rows take 128 x 4 (512) and 128 x 10 (1,280) instead of 256 x 2 and
+// 256 x 5: an item is a chain of loads that wait for each other (item, block,
+// map, source row, gathers) between barriers, and twice as many groups wait
+// side by side.  14 sites, spatial cut: 265 -> 240 us an application, 15 sites
+// 833 -> 749; longer rows (13 sites, 4,900) lost on fewer threads, and so did
+// spin rows of 924 (24-site chain 41.4 -> 43.6).  Loads that are clamped
+// instead of skipped past the row's end lost too (more registers, 240 -> 251).
 // The source-column tables replace the ranking tables, which only the items
 // of several rows (ONE = false) load.
 template <bool ONE, int NT1, int M1, bool FERM>
@@ -1302,27 +1360,29 @@ __global__ __launch_bounds__(ONE ? NT1 : SPIN_MANY_THREADS, (ONE && NT1 == SPIN_
     __shared__ double red[NT / 64];
     __shared__ int32_t rl[ONE ? 1 : 256];
     __shared__ int32_t rh[ONE ? 1 : 256 * 9];
-    __shared__ uint32_t fm[SPIN_MAX_FLIP];
-    __shared__ double fc[SPIN_MAX_FLIP];
+    __shared__ uint32_t fm[ONE ? 1 : SPIN_MAX_FLIP];
+    __shared__ double fc[ONE ? 1 : SPIN_MAX_FLIP];
     const int it = xcd_item(n_xcd, per_xcd);
     if (it >= n_items) return;   // uniform over the work group
     const ItemDev W = items[it];
     if (W.row1 <= W.row0) return;
     const int tid = threadIdx.x;
+    const BlockDev B = P.blocks[W.block];   // before the barrier: scalar loads
+    const int64_t tb0 = tbase[2 * W.block], tb1 = tbase[2 * W.block + 1];
     const int n_flip = P.n_rflip;
-    if (!ONE) {
+    if constexpr (!ONE) {
         for (int i = tid; i < 256; i += NT) rl[i] = P.rank_lo[i];
         for (int i = tid; i < 256 * 9; i += NT) rh[i] = P.rank_hi[i];
     }
-    for (int i = tid; i < n_flip; i += NT) {
-        fm[i] = P.rflip_mask[i];
-        fc[i] = P.rflip_coef[i];
+    if (!ONE) {
+        for (int i = tid; i < n_flip; i += NT) {
+            fm[i] = P.rflip_mask[i];
+            fc[i] = P.rflip_coef[i];
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    const BlockDev B = P.blocks[W.block];
     if constexpr (ONE)
-        spin_one_row<NT, M, false, FERM>(P, B, W, xs, rl, rh, fm, fc, n_flip, red, xs + xtab_off, tab + tbase[2 * W.block],
-                                         tab + tbase[2 * W.block + 1]);
+        spin_one_row<NT, M, false, FERM>(P, B, W, xs, rl, rh, fm, fc, n_flip, red, xs + xtab_off, tab + tb0, tab + tb1);
     else
         spin_many_rows<NT, M, false>(P, B, W, xs, rl, rh, fm, fc, n_flip, red);
 }
@@ -1343,8 +1403,8 @@ __global__ __launch_bounds__(ONE ? NT1 : SPIN_MANY_THREADS, (ONE && NT1 == SPIN_
 // (the host's call rate), 20 sites 22.4 -> 8.1, 22 sites 60 -> 22.5.  Past
 // about 2^20 amplitudes the left operator's rows no longer come from L2 and
 // the two-pass kernels' slab order wins: 22 sites 22.5 against 27 us, 23 sites
-// (1.35M) 41 against 35.5, 24 sites 76 against 53; spatial Hubbard cut, 12
-// sites 29.5 against 44.6, 13 sites (2.9M) 87 against 74.
+// (1.35M) 41 against 25, 24 sites 76 against 41; spatial Hubbard cut, 12
+// sites 23 against 31, 13 sites (2.9M) 87 against 64.
 // ------------------------------------------------------------------------
 template <bool FERM>
 __device__ __forceinline__ void flat_group(const ProblemDev &P, int g, double *red) {
@@ -1383,10 +1443,9 @@ __device__ __forceinline__ void flat_group(const ProblemDev &P, int g, double *r
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const uint32_t s = (uint32_t)((u < 4 ? t0 : t1) >> (16 * (u & 3))) & 0xffffu;
-                on[u] = f0 + u < n_flip && s != (FERM ? 0xffffu : 8u * (uint32_t)dR);
-                neg[u] = FERM && (s & 0x8000u);
-                const uint32_t off = FERM ? 8u * (s & 0x7fffu) : s;   // a spin cut's entry is a byte offset
-                v[u] = on[u] ? *(const double *)((const char *)xrow + off) : 0.0;
+                on[u] = f0 + u < n_flip && s != 8u * (uint32_t)dR;
+                neg[u] = FERM && (s & 1u);
+                v[u] = on[u] ? *(const double *)((const char *)xrow + (FERM ? s & ~7u : s)) : 0.0;
             }
             if (f0 + 8 < n_flip) t0 = tw[(int64_t)(f0 / 4 + 2) * dR];
             if (f0 + 12 < n_flip) t1 = tw[(int64_t)(f0 / 4 + 3) * dR];
@@ -1412,12 +1471,11 @@ __device__ __forceinline__ void flat_group(const ProblemDev &P, int g, double *r
             double c = X.coef;
             if constexpr (FERM) {
                 if (lp & 1) c = -c;
-                if (e & 0x8000u) c = -c;
+                if (e & 1u) c = -c;
                 lp >>= 1;
             }
-            // a spin cut's entry is the row's zero slot minus the column, in bytes
-            const int col = FERM ? (int)(e & 0x7fffu) : sd - (int)(e >> 3);
-            acc += c * P.x[S->offset + (int64_t)lp * sd + col];
+            // the entry is the row's zero slot minus the column, in bytes
+            acc += c * P.x[S->offset + (int64_t)lp * sd + sd - (int)(e >> 3)];
         }
         if (!FERM && P.n_xr > 0) {
             double t = 0.0;
@@ -3195,8 +3253,8 @@ hipError_t launch_spin2(const SpinLArgs &L, const ProblemDev &P, const uint16_t 
         };
         auto pick = [&](auto ferm) {
             constexpr bool F = decltype(ferm)::value;
-            if (max_d_r <= 512) go(k_spinR<true, 256, 2, F>, 256);
-            else if (max_d_r <= 1280) go(k_spinR<true, 256, 5, F>, 256);
+            if (max_d_r <= 512) go(k_spinR<true, F ? 128 : 256, F ? 4 : 2, F>, F ? 128 : 256);
+            else if (max_d_r <= 1280) go(k_spinR<true, F ? 128 : 256, F ? 10 : 5, F>, F ? 128 : 256);
             else if (max_d_r <= 2048) go(k_spinR<true, 512, 4, F>, 512);
             else if (max_d_r <= 3584) go(k_spinR<true, 512, 7, F>, 512);
             else go(k_spinR<true, SPIN_THREADS, SPIN_M, F>, SPIN_THREADS);

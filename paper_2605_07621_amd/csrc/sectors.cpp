@@ -1206,21 +1206,6 @@ static void build_spin_tables(ecut_sectors *s) {
     }
 }
 
-// Tables of the two-pass row kernels (spin problems and the spatial Hubbard
-// cut), for left words of lbits bits:
-//  - the rows of every block by inversion level of the left word (a hop or
-//    flip-flop on bond (i, j) moves a word at most |i - j| levels, so the
-//    neighbour rows of a level lie in the levels next to it), and the left
-//    operator's CSR in that order;
-//  - per block, the source column of every right term (spin_fmask /
-//    spin_fcoef: a flip-flop or a hop of one spin, with the fermion sign
-//    (-1)^popc(w & rbetw[f]) when rbetw is given) and of every cross term
-//    (the right word with bit rj flipped; on the spatial Hubbard cut with
-//    the right part's sign (-1)^(occupied modes before the mode)), in the
-//    low 15 bits, the sign in bit 15, 0xffff for no term. On a spin cut
-//    (no signs) a flip entry is the column's byte offset in the staged row,
-//    8 * column, and "no term" is 8 * d_r, the zero slot after the row; a
-//    cross entry is the source block's zero slot minus the column, in bytes.
 // Work groups of the flat row kernel: FLAT_THREADS consecutive amplitudes of
 // one block each.
 static void make_flat_groups(ecut_sectors *s) {
@@ -1232,6 +1217,20 @@ static void make_flat_groups(ecut_sectors *s) {
                                (int32_t)(((int64_t)B.d_l * B.d_r + FLAT_THREADS - 1) / FLAT_THREADS));
 }
 
+// Tables of the two-pass row kernels (spin problems and the spatial Hubbard
+// cut), for left words of lbits bits:
+//  - the rows of every block by inversion level of the left word (a hop or
+//    flip-flop on bond (i, j) moves a word at most |i - j| levels, so the
+//    neighbour rows of a level lie in the levels next to it), and the left
+//    operator's CSR in that order;
+//  - per block, the source column of every right term (spin_fmask /
+//    spin_fcoef: a flip-flop or a hop of one spin, with the fermion sign
+//    (-1)^popc(w & rbetw[f]) when rbetw is given) and of every cross term
+//    (the right word with bit rj flipped; on the spatial Hubbard cut with
+//    the right part's sign (-1)^(occupied modes before the mode)), the sign in
+//    bit 0. A flip entry is the column's byte offset in the staged row,
+//    8 * column, and "no term" is 8 * d_r, the zero slot after the row; a
+//    cross entry is the source block's zero slot minus the column, in bytes.
 static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<uint32_t> &rbetw) {
     s->sp2_ok = false;
     if (s->spin_fmask.size() > (size_t)SPIN_MAX_FLIP || s->max_d_r > SPIN_TILE) return;
@@ -1268,17 +1267,15 @@ static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<
         n += (int64_t)nx * s->blocks[b].d_r;
         n = (n + 3) & ~(int64_t)3;   // 8-byte aligned groups
     }
-    s->sp_tab.assign((size_t)std::max<int64_t>(n, 4), 0xffff);
-    // "no term" in a flip table: 0xffff with fermion signs; for spin cuts the
-    // byte offset of the zero slot the kernel keeps after the row (8 * d_r),
-    // so a term that does not apply (and a pad entry) reads 0 with no test
-    static_assert(SPIN_TILE * 8 < 0xffff, "a spin cut's byte offsets fit 16 bits");
-    const int64_t unit = fermion ? 1 : 8;   // a spin cut's entries are byte offsets
-    if (!fermion)
-        for (size_t b = 0; b < s->blocks.size(); ++b)
-            std::fill(s->sp_tab.begin() + s->sp_tbase[2 * b],
-                      s->sp_tab.begin() + s->sp_tbase[2 * b] + (int64_t)ng * 4 * s->blocks[b].d_r,
-                      (uint16_t)(8 * s->blocks[b].d_r));
+    s->sp_tab.assign((size_t)std::max<int64_t>(n, 4), 0);
+    // "no term" in a flip table: the byte offset of the zero slot the kernel
+    // keeps after the row (8 * d_r), so a term that does not apply (and a pad
+    // entry) reads 0 with no test
+    static_assert(SPIN_TILE * 8 < 0xffff, "byte offsets fit 16 bits");
+    for (size_t b = 0; b < s->blocks.size(); ++b)
+        std::fill(s->sp_tab.begin() + s->sp_tbase[2 * b],
+                  s->sp_tab.begin() + s->sp_tbase[2 * b] + (int64_t)ng * 4 * s->blocks[b].d_r,
+                  (uint16_t)(8 * s->blocks[b].d_r));
     for (size_t b = 0; b < s->blocks.size(); ++b) {
         const BlockDev &B = s->blocks[b];
         for (int32_t e = 0; e < B.d_r; ++e) {
@@ -1287,28 +1284,29 @@ static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<
                 if (__builtin_popcount(w & s->spin_fmask[f]) == 1) {
                     const int sg = rbetw.empty() ? 0 : (__builtin_popcount(w & rbetw[f]) & 1);
                     s->sp_tab[(size_t)(s->sp_tbase[2 * b] + ((int64_t)(f / 4) * B.d_r + e) * 4 + f % 4)] =
-                        (uint16_t)(unit * rank(w ^ s->spin_fmask[f]) | (sg << 15));
+                        (uint16_t)(8 * rank(w ^ s->spin_fmask[f]) | sg);
                 }
             for (int k = 0; k < nx; ++k) {
                 const XBondDev &X = s->xbond[k];
                 const uint32_t wp = w ^ (1u << X.rj);
-                uint16_t v;
+                // the source block's zero slot minus the source column, in
+                // bytes: the kernel subtracts it from the zero slot when the
+                // term applies (a source block too wide for the kernel does
+                // not exist in a problem on it, and its entry is never read)
+                int64_t z = (int64_t)binom(nR, __builtin_popcount(wp));
+                int sg = 0;
                 if (fermion) {
-                    const int sg = occ_before(w, X.label, X.label ? X.rj : X.rj - nR) & 1;
-                    v = (uint16_t)(rank(wp) | (sg << 15));
-                } else {
-                    // the source block's zero slot minus the source column, in
-                    // bytes: the kernel subtracts it from the zero slot when the
-                    // term applies (a source block too wide for the kernel does
-                    // not exist in a problem on it, and its entry is never read)
-                    const int64_t z = 8 * (int64_t)binom(nR, __builtin_popcount(wp));
-                    v = z <= 8 * (int64_t)s->max_d_r ? (uint16_t)(z - 8 * rank(wp)) : (uint16_t)0;
+                    const uint32_t dn = wp & ((1u << nR) - 1u), up = wp >> nR;
+                    z = (int64_t)binom(nR, __builtin_popcount(up)) * (int64_t)binom(nR, __builtin_popcount(dn));
+                    sg = occ_before(w, X.label, X.label ? X.rj : X.rj - nR) & 1;
                 }
+                const uint16_t v = z <= s->max_d_r ? (uint16_t)(8 * (z - rank(wp)) | sg) : (uint16_t)0;
                 s->sp_tab[(size_t)(s->sp_tbase[2 * b + 1] + (int64_t)k * B.d_r + e)] = v;
             }
         }
     }
     spin_left_blocks(s, HUBU_ROWS, s->sp_lblocks);
+    s->spin_fcoef.resize((size_t)ng * 4, 0.0);   // to whole words of the tables
     s->sp2_ok = csr_ok && s->max_d_r < 32768;
     make_flat_groups(s);
 }

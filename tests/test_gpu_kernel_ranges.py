@@ -185,6 +185,32 @@ def test_two_pass_row_lengths(dev, n, cut, n_up, d_r):
         assert torch.equal(s.apply(x), y), t
 
 
+# threads and amplitudes per thread of the spatial Hubbard cut's right kernel by
+# the longest row: 512, 1280, 2048, 3584, 6656
+@pytest.mark.parametrize("n,cut,n_up,n_dn,d_r", [(4, 2, 2, 1, 4), (9, 3, 4, 4, 400), (10, 3, 5, 5, 1225), (10, 2, 3, 2, 1568),
+                                                 (10, 2, 3, 3, 3136), (10, 2, 5, 4, 4900)])
+def test_two_pass_fermion_row_lengths(dev, n, cut, n_up, n_dn, d_r):
+    """The two-pass kernels with fermion signs at every row class, on a chain
+    with a density term across the cut and on random couplings (many right
+    terms and cross terms, a last table word that is not full), against the
+    oracle (1e-12) and the flat kernel (1e-14: the same terms, sums of at most
+    a few hundred)."""
+    import oracle as O
+    rng = np.random.default_rng(n * 10 + cut)
+    for m in (I.hubbard_chain(n, 1.0, 3.0, V=0.7), I.random_extended_hubbard_model(rng, n)):
+        p = I.Problem(m, I.Cut("spatial", I.left_mask_first(cut)), n_up, n_dn)
+        s = ecut.Sectors.from_problem(p)
+        assert s.info.max_d_r == d_r and s.info.kernel_flags & 64
+        x = _vec(s.dim, 130 + n, dev)
+        z = s.apply(x)
+        ref = O.Sector(p.model, n_up, n_dn).apply(s.export(x).cpu().numpy())
+        for grid in (0, 8):
+            s.set_tuning(variant=2, n_xcd=8, grid=grid)
+            y = s.apply(x)
+            assert np.linalg.norm(s.export(y).cpu().numpy() - ref) <= 1e-12 * np.linalg.norm(ref)
+            assert float((y - z).norm()) <= 1e-14 * float(z.norm())
+
+
 def test_entanglement_lanes_and_threads(dev):
     """The spectrum with one, two and many block sizes (one to four lanes):
     the values of a second call, of a call that follows work on another
