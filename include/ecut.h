@@ -264,9 +264,11 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
  * kernels by the vector's size: Hubbard up/down problems of at most 32
  * hopping bonds run one fused kernel up to 2^18 amplitudes (2^20 if every
  * hop has the same value), the two-pass kernels (variant 6) above, and
- * variant 7 from 2^25 where it is available; spin problems and the spatial Hubbard cut, where kernel_flags bit 6 is set,
- * run one kernel with a thread per amplitude up to 2^20 amplitudes and the
- * two-pass kernels (variant 2) above; other problems run variant 0's kernel.
+ * variant 7 from 2^25 where it is available; spin problems and the spatial
+ * Hubbard cut, where kernel_flags bit 6 is set, run one kernel with a thread
+ * per amplitude up to 2^20 amplitudes and the two-pass kernels (variant 2)
+ * above, as do spin problems with rows of 6,657 to 13,312 amplitudes whose mean
+ * row is a fifth of the longest; other problems run variant 0's kernel.
  * Explicit tunings (used by the Hubbard up/down kernel, whose work groups
  * each own one row of Psi at a time):
  *   grid:      work groups (0 = one per compute unit);

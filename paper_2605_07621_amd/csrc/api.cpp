@@ -527,9 +527,10 @@ int32_t max_tile_elems(const ecut_sectors *s) {
 int32_t rows_split_of(const ecut_sectors *s) {
     if (s->kernel == 1 || s->spin_ok || s->item_slots <= 0) return 1;
     int64_t tile = 0;
-    for (const ItemDev &it : s->hub_spatial ? s->generic_items : s->items)
+    const bool own = s->hub_spatial || s->wide_rows;   // items may hold the two-pass kernels' rows
+    for (const ItemDev &it : own ? s->generic_items : s->items)
         tile = std::max<int64_t>(tile, (int64_t)(it.row1 - it.row0) * s->blocks[it.block].d_r);
-    const int64_t n = s->hub_spatial ? (int64_t)s->generic_items.size() : s->item_slots;
+    const int64_t n = own ? (int64_t)s->generic_items.size() : s->item_slots;
     const int64_t most = (tile + ROWS_THREADS - 1) / ROWS_THREADS;
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(most, std::min<int64_t>(ROWS_MIN_GROUPS / n, 65535)));
 }
@@ -1054,7 +1055,8 @@ ecut_status ecut_sectors_get_info(const ecut_sectors *s, ecut_sectors_info *info
     I.n_cross_diag = (int32_t)s->xdiag.size();
     I.kernel = s->kernel;
     I.kernel_flags = (s->hub2_ok ? 1 : 0) | (s->hub3_ok ? 2 : 0) | (s->spin_ok ? 4 : 0) | (s->hubrow_ok ? 8 : 0) |
-                     (s->hubseg_ok ? 16 : 0) | (s->hub6_ok ? 32 : 0) | (s->sp2_ok ? 64 : 0);
+                     (s->hubseg_ok ? 16 : 0) | (s->hub6_ok ? 32 : 0) |
+                     (s->sp2_ok && !s->wide_rows ? 64 : 0);
     I.device_bytes = (int64_t)s->dev_bytes;
     I.n_eff = s->n_eff;
     *info = I;

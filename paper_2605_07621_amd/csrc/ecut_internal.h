@@ -458,6 +458,7 @@ struct ecut_sectors {
     std::vector<int32_t> sp_level_rows;
     std::vector<int32_t> sp_pptr, sp_pcol;   // left operator's CSR in that order (per block, at lbase)
     std::vector<double> sp_pval;
+    bool wide_rows = false;                  // two-pass tables for rows longer than SPIN_TILE (default tuning only)
     bool sp2_ok = false;                     // every left word has at most 64 neighbours
     // source columns of the right flip-flop terms and of the cross terms, per
     // block: right term f of column e at tbase[2b] + ((f / 4) * d_R + e) * 4 + f % 4,

@@ -28,6 +28,8 @@ constexpr int SLAB_THREADS = 256;
 constexpr int SPIN_THREADS = 512;
 constexpr int SPIN_M = 13;                   // element slots per thread of the spin kernel
 constexpr int SPIN_TILE = SPIN_THREADS * SPIN_M;
+constexpr int SPIN_WIDE_THREADS = 1024;       // two-pass right kernel on rows longer than SPIN_TILE
+constexpr int SPIN_WIDE_TILE = SPIN_WIDE_THREADS * SPIN_M;
 constexpr int XTAB_SLOTS = 256;               // LDS doubles of a row's folded diagonal table (2^XR_MAX)
 constexpr int SPIN_MAX_FLIP = 64;            // flip-flop terms inside the right part
 constexpr int SPIN_MANY_THREADS = 256;       // kernel for items of several short rows

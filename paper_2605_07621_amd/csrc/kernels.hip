@@ -797,7 +797,7 @@ __device__ __forceinline__ double signed_by(double v, uint32_t entry) {
     return __hiloint2double(__double2hiint(v) ^ (int)(entry << 31), __double2loint(v));
 }
 
-template <int NT, int M, bool LEFT, bool FERM = false>
+template <int NT, int M, bool LEFT, bool FERM = false, bool WIDE = false>
 __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev &B, const ItemDev &W, double *xs,
                                              const int32_t *rl, const int32_t *rh, const uint32_t *fm,
                                              const double *fc, int n_flip, double *red, double *xtab,
@@ -805,6 +805,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
                                              const uint16_t *__restrict__ tabX = nullptr) {
     const double2 ef = epi_factors(P.dscale, P.xscale, P.zcoef);
     const int tid = threadIdx.x;
+    constexpr int U = WIDE ? 1 : 8, SH = WIDE ? 3 : 0;   // table entries: columns (rows past 16-bit byte offsets) or bytes
     const int dR = B.d_r;
     const int l = W.row0;
     const int gl = B.lbase + l;
@@ -908,7 +909,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
             if (!LEFT && tid == 0) xs[sd] = 0.0;   // the slot a term that does not apply reads
             __syncthreads();
             const uint32_t flipm = bl ? ~0u : 0u;   // bit rj of w ^ flipm: the term applies
-            const int32_t zs = 8 * sd;            // the zero slot's byte offset
+            const int32_t zs = U * sd;            // the zero slot's byte offset
             for (int kk = k; kk < k1; ++kk) {
                 const int rj = XB[kk].rj;
                 const double c = lneg ? -XB[kk].coef : XB[kk].coef;
@@ -936,7 +937,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
                             const int m = m0 + u;
                             if (m >= M) break;
                             const int32_t on = __builtin_amdgcn_sbfe((int32_t)(wr[m] ^ flipm), rj, 1);
-                            v[u] = lds_at(xs, (uint32_t)(zs + on * (int32_t)(FERM ? sx[m] & ~7u : sx[m])));
+                            v[u] = lds_at(xs, (uint32_t)(zs + on * (int32_t)(FERM ? sx[m] & ~7u : sx[m])) << SH);
                         }
 #pragma unroll
                         for (int u = 0; u < C; ++u) {
@@ -958,7 +959,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
         k = k1;
     }
     // the item's own row
-    const uint64_t none4 = (uint64_t)(8u * dR) * 0x0001000100010001ull;   // slots past the row's end
+    const uint64_t none4 = (uint64_t)((uint32_t)U * dR) * 0x0001000100010001ull;   // slots past the row's end
     uint64_t tw[M];
     if constexpr (EARLY) {
 #pragma unroll
@@ -1032,7 +1033,7 @@ __device__ __forceinline__ void spin_one_row(const ProblemDev &P, const BlockDev
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const uint32_t en = (uint32_t)(t[m] >> (16 * i)) & 0xffffu;
-                    v[i] = FERM ? signed_by(lds_at(xs, en & ~7u), en) : lds_at(xs, en);
+                    v[i] = FERM ? signed_by(lds_at(xs, en & ~7u), en) : lds_at(xs, en << SH);
                 }
                 // the last word's pad entries are the zero slot's offset and
                 // their coefficients 0, so all 4 terms are summed unguarded
@@ -1350,8 +1351,8 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_spinL(const SpinLArgs A, int n
 // instead of skipped past the row's end lost too (more registers, 240 -> 251).
 // The source-column tables replace the ranking tables, which only the items
 // of several rows (ONE = false) load.
-template <bool ONE, int NT1, int M1, bool FERM>
-__global__ __launch_bounds__(ONE ? NT1 : SPIN_MANY_THREADS, (ONE && NT1 == SPIN_THREADS) ? 4 : 2) void k_spinR(
+template <bool ONE, int NT1, int M1, bool FERM, bool WIDE = false>
+__global__ __launch_bounds__(ONE ? NT1 : SPIN_MANY_THREADS, (ONE && NT1 >= SPIN_THREADS) ? 4 : 2) void k_spinR(
     const ProblemDev P, const uint16_t *__restrict__ tab, const int64_t *__restrict__ tbase,
     const ItemDev *__restrict__ items, int n_items, int n_xcd, int per_xcd, int xtab_off) {
     constexpr int NT = ONE ? NT1 : SPIN_MANY_THREADS;
@@ -1382,7 +1383,7 @@ __global__ __launch_bounds__(ONE ? NT1 : SPIN_MANY_THREADS, (ONE && NT1 == SPIN_
         __syncthreads();
     }
     if constexpr (ONE)
-        spin_one_row<NT, M, false, FERM>(P, B, W, xs, rl, rh, fm, fc, n_flip, red, xs + xtab_off, tab + tb0, tab + tb1);
+        spin_one_row<NT, M, false, FERM, WIDE>(P, B, W, xs, rl, rh, fm, fc, n_flip, red, xs + xtab_off, tab + tb0, tab + tb1);
     else
         spin_many_rows<NT, M, false>(P, B, W, xs, rl, rh, fm, fc, n_flip, red);
 }
@@ -3223,7 +3224,8 @@ hipError_t launch_spin(const ProblemDev *probs_d, const ProblemDev &single, cons
 hipError_t launch_spin2(const SpinLArgs &L, const ProblemDev &P, const uint16_t *tab, const int64_t *tbase,
                         const ItemDev *items_d, int n_one, int n_items, int max_d_r, int n_xcd, bool fermion,
                         hipStream_t st) {
-    if (max_d_r > SPIN_TILE) return hipErrorInvalidValue;
+    const bool wide = max_d_r > SPIN_TILE;   // one-row items only
+    if (wide && (max_d_r > SPIN_WIDE_TILE || fermion || n_items > n_one)) return hipErrorInvalidValue;
     const int xu = n_xcd == 1 ? 1 : 8;
     auto grid_of = [&](int n, int &per) {
         per = (n + xu - 1) / xu;
@@ -3259,7 +3261,8 @@ hipError_t launch_spin2(const SpinLArgs &L, const ProblemDev &P, const uint16_t 
             else if (max_d_r <= 3584) go(k_spinR<true, 512, 7, F>, 512);
             else go(k_spinR<true, SPIN_THREADS, SPIN_M, F>, SPIN_THREADS);
         };
-        if (fermion) pick(std::true_type{});
+        if (wide) go(k_spinR<true, SPIN_WIDE_THREADS, SPIN_M, false, true>, SPIN_WIDE_THREADS);
+        else if (fermion) pick(std::true_type{});
         else pick(std::false_type{});
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -3296,6 +3299,9 @@ hipError_t set_hub_lds_limits(size_t bytes) {
     hipError_t e = hipSuccess;
     const int b = (int)bytes;
     e = hipFuncSetAttribute((const void *)k_spin<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SPIN_TILE * 8);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute((const void *)k_spinR<true, SPIN_WIDE_THREADS, SPIN_M, false, true>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (SPIN_WIDE_TILE + 1 + XTAB_SLOTS) * 8);
     if (e != hipSuccess) return e;
 
     e = hipFuncSetAttribute((const void *)k_hubrow<1024, HUBROW_P, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,

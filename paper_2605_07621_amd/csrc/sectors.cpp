@@ -139,6 +139,7 @@ inline bool fermion_hop(uint32_t w, int i, int j, uint32_t &w2, int &sign) {
 static void build_hub_tables(ecut_sectors *s, const ecut_model_desc *m);
 static void build_panels(ecut_sectors *s, const ecut_model_desc *m);
 static void build_spin_tables(ecut_sectors *s);
+static void build_wide_tables(ecut_sectors *s);
 static void fold_cross_diagonal(ecut_sectors *s);
 static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<uint32_t> &rbetw);
 static int inversions(uint32_t w, int n);
@@ -1183,12 +1184,42 @@ static void fold_cross_diagonal(ecut_sectors *s) {
     s->xr_site = sites;
 }
 
+// Rows longer than the spin kernels take (a right part of 16 sites): the
+// default of vectors past the flat kernel's size is the two-pass kernels on
+// groups of 1,024 threads; every other tuning runs the generic row kernel.
+// Every row is a group, so only where the mean row is a fifth of the longest:
+// 7x4 J1-J2 lattice at half filling (40M amplitudes, 0.76 of 12,870) 6.09 ms
+// an application on the generic kernel, 1.16 on these; 28-site chain with 10
+// up spins (0.25) 460 against 375 us, with 9 (0.13) 228 against 287; 30 sites
+// with 10 (0.15) 1.08 against 1.20 ms.
+static void build_wide_tables(ecut_sectors *s) {
+    int64_t rows = 0;
+    for (const BlockDev &B : s->blocks) rows += B.d_l;
+    if (s->max_d_r > SPIN_WIDE_TILE || s->dim <= FLAT_MAX_DIM || 5 * s->dim < rows * s->max_d_r) return;
+    s->wide_rows = true;
+    make_rank_tables(s);
+    build_two_pass_tables(s, (int)s->lsites.size(), {});
+    if (!s->sp2_ok) {
+        s->wide_rows = false;
+        return;
+    }
+    s->generic_items = s->items;
+    s->items_cap = std::max(s->items_cap, (size_t)rows);
+    s->item_slots_cap = std::max<int32_t>(s->item_slots_cap, (int32_t)rows);
+    s->item_slots = make_spin_items(s, 1, 2, s->items);
+    s->sp_n_one = (int32_t)s->items.size();
+}
+
 static void build_spin_tables(ecut_sectors *s) {
     s->spin_ok = false;
+    s->wide_rows = false;
     if (s->kind != ECUT_SPIN_HALF) return;
     if (s->lsites.size() > 16 || s->rsites.size() > 16) return;
     if (s->spin_fmask.size() > (size_t)SPIN_MAX_FLIP) return;
-    if (s->max_d_r > SPIN_TILE) return;
+    if (s->max_d_r > SPIN_TILE) {
+        build_wide_tables(s);
+        return;
+    }
     s->item_slots = make_spin_items(s, SPIN_MANY_TILE, 0, s->items);
     // every item holds at least one row, so no tile size gives more slots
     // than there are rows; an XCD-dealt list pads each of its 8 chunks to the
@@ -1210,7 +1241,7 @@ static void build_spin_tables(ecut_sectors *s) {
 // one block each.
 static void make_flat_groups(ecut_sectors *s) {
     s->flat_base.clear();
-    if (!s->sp2_ok || s->dim > FLAT_MAX_DIM) return;
+    if (!s->sp2_ok || s->wide_rows || s->dim > FLAT_MAX_DIM) return;
     s->flat_base.push_back(0);
     for (const BlockDev &B : s->blocks)
         s->flat_base.push_back(s->flat_base.back() +
@@ -1233,7 +1264,7 @@ static void make_flat_groups(ecut_sectors *s) {
 //    cross entry is the source block's zero slot minus the column, in bytes.
 static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<uint32_t> &rbetw) {
     s->sp2_ok = false;
-    if (s->spin_fmask.size() > (size_t)SPIN_MAX_FLIP || s->max_d_r > SPIN_TILE) return;
+    if (s->spin_fmask.size() > (size_t)SPIN_MAX_FLIP || s->max_d_r > (s->wide_rows ? SPIN_WIDE_TILE : SPIN_TILE)) return;
     const int nR = (int)s->rsites.size();
     const bool fermion = s->hub_spatial;
     // a right word's column inside its group
@@ -1272,10 +1303,11 @@ static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<
     // keeps after the row (8 * d_r), so a term that does not apply (and a pad
     // entry) reads 0 with no test
     static_assert(SPIN_TILE * 8 < 0xffff, "byte offsets fit 16 bits");
+    const int64_t unit = s->wide_rows ? 1 : 8;   // wide rows: columns instead of byte offsets
     for (size_t b = 0; b < s->blocks.size(); ++b)
         std::fill(s->sp_tab.begin() + s->sp_tbase[2 * b],
                   s->sp_tab.begin() + s->sp_tbase[2 * b] + (int64_t)ng * 4 * s->blocks[b].d_r,
-                  (uint16_t)(8 * s->blocks[b].d_r));
+                  (uint16_t)(unit * s->blocks[b].d_r));
     for (size_t b = 0; b < s->blocks.size(); ++b) {
         const BlockDev &B = s->blocks[b];
         for (int32_t e = 0; e < B.d_r; ++e) {
@@ -1284,7 +1316,7 @@ static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<
                 if (__builtin_popcount(w & s->spin_fmask[f]) == 1) {
                     const int sg = rbetw.empty() ? 0 : (__builtin_popcount(w & rbetw[f]) & 1);
                     s->sp_tab[(size_t)(s->sp_tbase[2 * b] + ((int64_t)(f / 4) * B.d_r + e) * 4 + f % 4)] =
-                        (uint16_t)(8 * rank(w ^ s->spin_fmask[f]) | sg);
+                        (uint16_t)(unit * rank(w ^ s->spin_fmask[f]) | sg);
                 }
             for (int k = 0; k < nx; ++k) {
                 const XBondDev &X = s->xbond[k];
@@ -1300,7 +1332,7 @@ static void build_two_pass_tables(ecut_sectors *s, int lbits, const std::vector<
                     z = (int64_t)binom(nR, __builtin_popcount(up)) * (int64_t)binom(nR, __builtin_popcount(dn));
                     sg = occ_before(w, X.label, X.label ? X.rj : X.rj - nR) & 1;
                 }
-                const uint16_t v = z <= s->max_d_r ? (uint16_t)(8 * (z - rank(wp)) | sg) : (uint16_t)0;
+                const uint16_t v = z <= s->max_d_r ? (uint16_t)(unit * (z - rank(wp)) | sg) : (uint16_t)0;
                 s->sp_tab[(size_t)(s->sp_tbase[2 * b + 1] + (int64_t)k * B.d_r + e)] = v;
             }
         }

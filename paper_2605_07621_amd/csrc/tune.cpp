@@ -75,7 +75,7 @@ void write_cache(const char *path, const std::map<std::string, ApplyTuning> &m) 
 ecut_status apply_tuning(ecut_sectors *s, const ApplyTuning &T) {
     if (T.order < 0 || T.order > 10 || T.grid < 0 || T.n_xcd < 0 || T.variant < 0 || T.variant > 7)
         return fail(ECUT_EINVAL, "bad tuning");
-    if (s->kernel != 1 && T.variant > (s->spin_ok || s->sp2_ok ? 2 : 1))
+    if (s->kernel != 1 && T.variant > (s->spin_ok || (s->sp2_ok && !s->wide_rows) ? 2 : 1))
         return fail(ECUT_EINVAL, "spin problems take variant 0, 1 or 2, generic problems 0 or 1 (2 with two-pass tables)");
     if (s->kernel != 1 && T.variant == 2) {
         if (!s->sp2_ok)
@@ -145,7 +145,7 @@ ecut_status apply_tuning(ecut_sectors *s, const ApplyTuning &T) {
         s->items.swap(items);
         s->item_slots = slots;
     }
-    if (s->hub_spatial && s->sp2_ok && two != cur_two) {
+    if ((s->hub_spatial || s->wide_rows) && s->sp2_ok && two != cur_two) {
         // every row its own item for the two-pass kernels, else the row kernel's tiles
         std::vector<ItemDev> items;
         const int32_t slots = two ? make_spin_items(s, 1, 2, items)
@@ -264,7 +264,7 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
             for (int rows : {4, 8, 16})
                 for (int xcd : {1, 8}) cands.push_back(ApplyTuning{rows, xcd, 0, 2, 0});
     } else {
-        if (s->sp2_ok)   // the spatial Hubbard cut: the two-pass row kernels
+        if (s->sp2_ok && !s->wide_rows)   // the spatial Hubbard cut: the two-pass row kernels
             for (int rows : {4, 8, 16})
                 for (int xcd : {1, 8}) cands.push_back(ApplyTuning{rows, xcd, 0, 2, 0});
     }

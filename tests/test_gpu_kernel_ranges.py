@@ -185,6 +185,38 @@ def test_two_pass_row_lengths(dev, n, cut, n_up, d_r):
         assert torch.equal(s.apply(x), y), t
 
 
+# rows past the spin kernels' 6,656 amplitudes, on vectors past the flat kernel's
+# size: the longest rows of a 16-site right part, on a chain of odd length too, and
+# a cut whose rows are too short on average
+@pytest.mark.parametrize("n,cut,n_up,d_r", [(23, 7, 11, 12870), (24, 8, 12, 12870), (25, 9, 8, 12870)])
+def test_wide_rows(dev, n, cut, n_up, d_r):
+    """The default of long rows against the generic kernel (1e-14: sums of at
+    most 64 terms in another order) and the oracle (1e-12), alone, in a batch
+    and after a change of the tuning and back; the two-pass tuning stays
+    refused by name."""
+    import oracle as O
+    p = I.Problem(I.xxz_chain(n, 1.0, 0.9, periodic=True), I.Cut("spatial", I.left_mask_first(cut)), n_up)
+    s = ecut.Sectors.from_problem(p)
+    assert s.info.max_d_r == d_r and not s.info.kernel_flags & 64
+    x = _vec(s.dim, 140 + n, dev)
+    y = s.apply(x)
+    ref = O.Sector(p.model, n_up).apply(s.export(x).cpu().numpy())
+    assert np.linalg.norm(s.export(y).cpu().numpy() - ref) <= 1e-12 * np.linalg.norm(ref)
+    z = torch.empty_like(x)
+    ecut.apply_batch([s], [x], [z])
+    assert torch.equal(z, y)
+    a, b, _ = ecut.lanczos_tridiag(s, x, 6)
+    s.set_tuning(variant=1)
+    g = s.apply(x)
+    assert float((y - g).norm()) <= 1e-14 * float(g.norm())
+    a1, b1, _ = ecut.lanczos_tridiag(s, x, 6)   # the partial sums of both kernels (1e-11: six steps)
+    assert np.allclose(a, a1, rtol=1e-11, atol=1e-11) and np.allclose(b, b1, rtol=1e-11, atol=1e-11)
+    with pytest.raises(Exception):
+        s.set_tuning(variant=2)
+    s.set_tuning()
+    assert torch.equal(s.apply(x), y)
+
+
 # threads and amplitudes per thread of the spatial Hubbard cut's right kernel by
 # the longest row: 512, 1280, 2048, 3584, 6656
 @pytest.mark.parametrize("n,cut,n_up,n_dn,d_r", [(4, 2, 2, 1, 4), (9, 3, 4, 4, 400), (10, 3, 5, 5, 1225), (10, 2, 3, 2, 1568),
