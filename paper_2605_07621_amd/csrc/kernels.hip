@@ -1338,7 +1338,9 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_spinL(const SpinLArgs A, int n
 // row of the problem: 256 x 2 (512 amplitudes), 256 x 5 (1,280), 512 x 4
 // (2,048), 512 x 7 (3,584) or 512 x 13 (6,656).  Rows of 1,716 on 512 x 4 instead
 // of 512 x 13: 25-site chain 116 -> 65 us an application, 26 sites 242 -> 153;
-// rows of 3,432 on 512 x 7: 28 sites 741 -> 579.  Staging every source row at
+// rows of 3,432 on 512 x 7: 28 sites 741 -> 579.  WIDE: 1,024 x 13 (13,312),
+// table entries in columns (byte offsets pass 16 bits), one group a compute
+// unit by its 105 KB of LDS: 7x4 lattice 6.09 -> 1.14 ms.  Staging every source row at
 // once behind one barrier (more registers, fewer groups) measured the same on
 // chains and slower with four left sites (6x4 lattice 71 -> 85 us) and with
 // fermion signs (58 -> 72 us at 12 sites).

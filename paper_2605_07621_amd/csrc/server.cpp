@@ -220,15 +220,16 @@ static ecut_status tune_once(ecut_sectors *s, const double *x, double *y, hipStr
     ecut_tuning best{};
     ecut_status rs;
     if (merged && s->kernel == 1 && s->hub6_ok && s->dim <= SMALL_HUB_DIM && s->h6_maxq <= HUBD_BATCH_SLOTS) {
-        // small Hubbard problems take the two-pass kernels, so that every
-        // step runs all of them in one merged launch per pass
+        // small Hubbard problems take the fused kernel (two passes where it
+        // does not reach), so that every step runs all of them in one merged
+        // launch
         best = ecut_tuning{0, 8, 1, 6, 2};
         rs = ecut_set_tuning(s, &best);
     } else {
         rs = ecut_autotune(s, x, y, st, &best);
         if (rs == ECUT_OK && merged && s->spin_ok && s->dim <= SMALL_SPIN_DIM && best.variant != 0) {
-            // small spin problems keep the one-pass kernel, whose work items
-            // join every other spin problem's in one merged launch per step
+            // small spin problems keep the default, whose work groups join
+            // every other small spin problem's in one merged launch per step
             best = ecut_tuning{0, 0, 0, 0, 0};
             rs = ecut_set_tuning(s, &best);
         }
