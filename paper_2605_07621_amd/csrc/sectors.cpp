@@ -1012,50 +1012,60 @@ static void build_hubseg_tables(ecut_sectors *s) {
 }
 
 // Tables of the two-pass flat kernels: the down-spin operator H_dn in column
-// space (class-major columns), one slot per bond: col[b * d_R + c] is the
-// column reached from column c by a hop across bond b, or -1 if the bond
-// cannot hop there (both sites empty or both occupied); val[b * d_R + c] its
-// value -t_b times the fermion sign.  Bond-major slots make the gathers of a
-// wave for one bond touch neighbouring addresses: a hop inside the high half
-// moves a whole segment of columns by the same offset, a hop inside the low
-// half stays in the segment.  The values are dropped when every hop of both
-// spins has the same value (the kernels then scale the neighbour sums once).
+// space (class-major columns), one slot per pair of sites with a hop (bonds
+// that repeat a pair are summed first, and a pair that cancels has no slot):
+// col[k * d_R + c] is the column reached from column c by a hop across pair k,
+// or -1 if the pair cannot hop there (both sites empty or both occupied);
+// val[k * d_R + c] its value -t times the fermion sign.  Pair-major slots make
+// the gathers of a wave for one pair touch neighbouring addresses: a hop inside
+// the high half moves a whole segment of columns by the same offset, a hop
+// inside the low half stays in the segment.  The values are dropped when every
+// slot and every up-spin hop has the same value (the kernels then scale the
+// neighbour sums once).
 static void build_hub6_tables(ecut_sectors *s, const ecut_model_desc *m) {
     s->hub6_ok = false;
     const BlockDev &B = s->blocks[0];
     const int64_t dR = B.d_r;
     if (dR < 1 || B.d_l < 1 || dR >= (1ll << 30)) return;
-    std::vector<int> bonds;
-    for (int b = 0; b < m->n_bonds; ++b)
-        if (m->t[b] != 0.0) bonds.push_back(b);
-    const int nb = (int)bonds.size();
-    if (nb > HUBD_MAX_SLOTS || (int64_t)std::max(nb, 1) * dR >= (1ll << 31)) return;
-    bool uniform = true;
-    double hop = 0.0;
-    bool have = false;
-    for (const std::vector<double> *v : {&s->hl_val, &s->hr_val})
-        for (double x : *v) {
-            if (!have) { hop = x; have = true; }
-            uniform = uniform && x == hop;
-        }
-    s->h6_uniform = uniform;
-    s->h6_hop = hop;
+    struct Pair {
+        int i, j;
+        double t;
+    };
+    std::vector<Pair> pairs;   // in the order of their first bonds
+    int listed = 0;
+    for (int b = 0; b < m->n_bonds; ++b) {
+        if (m->t[b] == 0.0) continue;
+        ++listed;
+        const int i = std::min(m->bond_i[b], m->bond_j[b]), j = std::max(m->bond_i[b], m->bond_j[b]);
+        auto it = std::find_if(pairs.begin(), pairs.end(), [&](const Pair &p) { return p.i == i && p.j == j; });
+        if (it == pairs.end()) pairs.push_back(Pair{i, j, m->t[b]});
+        else it->t += m->t[b];
+    }
+    if (listed > HUBD_MAX_SLOTS || (int64_t)std::max(listed, 1) * dR >= (1ll << 31)) return;
+    pairs.erase(std::remove_if(pairs.begin(), pairs.end(), [](const Pair &p) { return p.t == 0.0; }), pairs.end());
+    const int nb = (int)pairs.size();
     s->h6_maxq = nb;
     s->h6_col.assign(std::max<int64_t>(1, (int64_t)nb * dR), -1);
-    s->h6_val.clear();
-    if (!uniform) s->h6_val.assign(std::max<int64_t>(1, (int64_t)nb * dR), 0.0);
+    s->h6_val.assign(std::max<int64_t>(1, (int64_t)nb * dR), 0.0);
+    bool uniform = true, have = !s->hl_val.empty();
+    double hop = have ? s->hl_val[0] : 0.0;
+    for (double x : s->hl_val) uniform = uniform && x == hop;
     for (int64_t c = 0; c < dR; ++c) {
         const uint32_t w = s->hub_rw32[c];
         for (int k = 0; k < nb; ++k) {
-            const int b = bonds[k];
             uint32_t w2;
             int sg;
-            if (!fermion_hop(w, m->bond_i[b], m->bond_j[b], w2, sg) && !fermion_hop(w, m->bond_j[b], m->bond_i[b], w2, sg))
-                continue;
+            if (!fermion_hop(w, pairs[k].i, pairs[k].j, w2, sg)) continue;
+            const double v = -pairs[k].t * sg;
             s->h6_col[(size_t)k * dR + c] = s->hub_col_of_rank[colex_rank(w2)];
-            if (!uniform) s->h6_val[(size_t)k * dR + c] = -m->t[b] * sg;
+            s->h6_val[(size_t)k * dR + c] = v;
+            if (!have) { hop = v; have = true; }
+            uniform = uniform && v == hop;
         }
     }
+    if (uniform) std::vector<double>().swap(s->h6_val);
+    s->h6_uniform = uniform;
+    s->h6_hop = hop;
     s->hub6_ok = true;
     build_panels(s, m);
 }
