@@ -793,7 +793,15 @@ int32_t apply_partial_slots(const ecut_sectors *s) {
     return tiles ? (int32_t)s->hub_items.size() : s->blocks[0].d_l;
 }
 
-// workspace size: either Hubbard variant may run on the same workspace
+// Slots the generic row kernel writes: one a slice of its items.  From the host
+// tables alone, so that a host-only handle gives the sizes of a device handle.
+static int32_t rows_partial_slots(const ecut_sectors *s) {
+    if (s->spin_ok) return 0;   // whole items, counted by item_slots_cap
+    const bool own = s->hub_spatial || s->wide_rows;   // items may hold the two-pass kernels' rows
+    return (own ? (int32_t)s->generic_items.size() : s->item_slots) * rows_split_of(s);
+}
+
+// workspace size: any kernel of the problem may run on the same workspace
 int32_t apply_partial_slots_max(const ecut_sectors *s) {
     // the two-pass kernels use the most slots with one row per right-pass item
     const int32_t h6 = s->hub6_ok ? s->blocks[0].d_l * ((s->blocks[0].d_r + HUBD_THREADS - 1) / HUBD_THREADS) : 0;
@@ -801,7 +809,7 @@ int32_t apply_partial_slots_max(const ecut_sectors *s) {
                                                                                     (int32_t)s->hub_items.size()),
                                                                   s->hubseg_ok ? s->hs_n_slots : 0),
                                               h6)
-                          : std::max(std::max(s->item_slots_cap, s->item_slots) * std::max(1, s->prob.rows_split),
+                          : std::max(std::max(std::max(s->item_slots_cap, s->item_slots), rows_partial_slots(s)),
                                      s->flat_base.empty() ? 0 : s->flat_base.back());
 }
 
