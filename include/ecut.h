@@ -509,7 +509,8 @@ ecut_status ecut_continued_fraction(const double *alpha, const double *beta, int
  *   w_q, chi_q:  host, n_blocks entries; w_p: host, n_parts (nullable if
  *                n_parts == 1).
  * Synchronises the stream.  Errors: ECUT_EINVAL (null or bad arguments, zero
- * state), ECUT_ENOTCONV (the eigensolver did not converge), ECUT_EDEVICE.
+ * state), ECUT_ENOTCONV (the eigensolver did not converge), ECUT_EDEVICE (also
+ * a stream that is being captured: the capture itself goes on).
  * ------------------------------------------------------------------------- */
 typedef struct ecut_entanglement {
     int32_t n_blocks;

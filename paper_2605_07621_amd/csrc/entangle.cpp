@@ -14,11 +14,11 @@
 
 #include <algorithm>
 #include <cmath>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <numeric>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -158,6 +158,11 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
     for (const BlockDev &B : s->blocks)
         if (std::min(B.d_l, B.d_r) > (1 << 24)) return fail(ECUT_EUNSUPPORTED, "block too large for the Gram matrix");
     const hipStream_t hs = (hipStream_t)stream;
+    // refused before the lanes join the caller's capture: they go back to the
+    // pool for other threads' calls
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(hs, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+        return fail(ECUT_EDEVICE, "the spectrum synchronises its stream and cannot be captured");
     const auto groups = gram_groups(s);
     size_t grams = 0;
     for (const auto &kv : groups) grams += kv.second.size() * (size_t)kv.first * (size_t)kv.first;
@@ -245,7 +250,7 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
     for (size_t lane = 1; lane < set.lanes.size(); ++lane) {
         try {
             threads[lane] = std::thread(enqueue, lane);
-        } catch (const std::system_error &) {   // no thread to be had: this one does its work
+        } catch (const std::exception &) {   // no thread to be had: this one does its work
             enqueue(lane);
         }
     }
