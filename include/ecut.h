@@ -503,7 +503,9 @@ ecut_status ecut_continued_fraction(const double *alpha, const double *beta, int
  * syevd, on the device, up to four sizes at a time on streams of the library
  * (ordered after the caller's work on `stream`); the rest on the host.
  *   psi_d:       state in the bipartite layout (dim doubles, any norm, not 0).
- *   workspace_d: ecut_entanglement_sizes(s, &n_lambda) doubles (device).
+ *   workspace_d: ecut_entanglement_sizes(s, &n_lambda) doubles (device): the Gram
+ *                matrices of the largest size and, beside them, of the others
+ *                that run at a time, at most 1 GiB of those.
  *   lambda, xi:  host, n_lambda doubles each, blocks in order (xi nullable;
  *                +inf where lambda <= 0).
  *   w_q, chi_q:  host, n_blocks entries; w_p: host, n_parts (nullable if

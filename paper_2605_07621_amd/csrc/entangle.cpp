@@ -126,20 +126,73 @@ std::map<int, std::vector<int32_t>> gram_groups(const ecut_sectors *s) {
     return g;
 }
 
+// The groups of equal sizes dealt to lanes: the longest chain first, each to
+// the lane with the least work so far (the solver's launches grow with the size,
+// not with the number of blocks).  A lane's groups run one after the other in
+// one Gram buffer and one off-diagonal buffer, as large as its largest group
+// needs.  Side by side the lanes need more than one chain does; where that is
+// past LANES_EXTRA, fewer lanes run, down to one, so that a large spectrum fits
+// where the largest group and its eigenvalues fit (32 sites in halves: 2.1 GB
+// instead of 4.8 for every block at once).
+constexpr size_t LANES_EXTRA = (size_t)1 << 27;   // doubles, 1 GiB
+
+struct Group {
+    int m;
+    std::vector<int32_t> q;
+    int64_t off;     // its eigenvalues in the list of all
+    int32_t info;    // its first status word
+};
+
+struct Schedule {
+    std::vector<Group> groups;                 // by size, ascending
+    std::vector<std::vector<int>> todo;        // per lane: groups, largest first
+    std::vector<size_t> gram, diag;            // per lane: doubles of its buffers
+    size_t doubles = 0;                        // of all lanes' buffers
+};
+
+Schedule lane_schedule(const ecut_sectors *s) {
+    Schedule S;
+    int64_t off = 0;
+    int32_t info = 0;
+    size_t largest = 0;
+    for (const auto &kv : gram_groups(s)) {
+        const size_t m = (size_t)kv.first, c = kv.second.size();
+        S.groups.push_back(Group{kv.first, kv.second, off, info});
+        off += (int64_t)(c * m);
+        info += (int32_t)c;
+        largest = std::max(largest, c * m * m);
+    }
+    for (int n = std::max(1, std::min<int>(LANES, (int)S.groups.size())); n >= 1; --n) {
+        std::vector<int64_t> load(n, 0);
+        S.todo.assign(n, {});
+        S.gram.assign(n, 0);
+        S.diag.assign(n, 0);
+        for (int g = (int)S.groups.size() - 1; g >= 0; --g) {
+            const size_t lane = std::min_element(load.begin(), load.end()) - load.begin();
+            const size_t m = (size_t)S.groups[g].m, c = S.groups[g].q.size();
+            load[lane] += (int64_t)m;
+            S.todo[lane].push_back(g);
+            S.gram[lane] = std::max(S.gram[lane], c * m * m);
+            S.diag[lane] = std::max(S.diag[lane], c * m);
+        }
+        const size_t grams = std::accumulate(S.gram.begin(), S.gram.end(), (size_t)0);
+        S.doubles = grams + std::accumulate(S.diag.begin(), S.diag.end(), (size_t)0);
+        if (grams - largest <= LANES_EXTRA) break;
+    }
+    return S;
+}
+
 }  // namespace
 
 extern "C" {
 
-// Workspace: the Gram matrices of every block, its eigenvalues, the
-// eigensolver's off-diagonals, one status word per block (the groups of equal
-// sizes run side by side).
+// Workspace: every lane's Gram matrices and the eigensolver's off-diagonals, the
+// eigenvalues and one status word of every block.
 size_t ecut_entanglement_sizes(const ecut_sectors *s, size_t *n_lambda) {
     if (!s) return 0;
-    size_t grams = 0;
-    for (const auto &kv : gram_groups(s)) grams += kv.second.size() * (size_t)kv.first * (size_t)kv.first;
     const size_t nl = (size_t)schmidt_count(s);
     if (n_lambda) *n_lambda = nl;
-    return grams + 2 * nl + (s->blocks.size() + 1) / 2 + 1;
+    return lane_schedule(s).doubles + nl + (s->blocks.size() + 1) / 2 + 1;
 }
 
 ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_d, double cutoff, int32_t n_parts,
@@ -163,12 +216,10 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(hs, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
         return fail(ECUT_EDEVICE, "the spectrum synchronises its stream and cannot be captured");
-    const auto groups = gram_groups(s);
-    size_t grams = 0;
-    for (const auto &kv : groups) grams += kv.second.size() * (size_t)kv.first * (size_t)kv.first;
+    const Schedule S = lane_schedule(s);
     const int64_t n_lam = schmidt_count(s);
     LaneSet set;
-    ecut_status st = set.take(std::max(1, std::min<int>(LANES, (int)groups.size())));
+    ecut_status st = set.take((int)S.todo.size());
     if (st != ECUT_OK) return st;
     // the lanes start after the caller's work on its stream
     hipError_t le = hipEventRecord(set.lanes[0].ev, hs);
@@ -177,35 +228,16 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
     if (le != hipSuccess) return hip_fail(le, "entanglement lanes");
     // per group of equal-size blocks: their Gram matrices side by side
     // (rocBLAS syrk each), one batched eigensolve; the eigenvalues of every
-    // group side by side, one copy to the host at the end.  The longest chain
-    // goes first, each group to the lane with the least work so far (the
-    // solver's launches grow with the size, not with the number of blocks).
-    double *G = workspace_d, *Dg = workspace_d + grams, *E = Dg + n_lam;
-    rocblas_int *info = (rocblas_int *)(E + n_lam);
+    // group side by side, one copy to the host at the end
+    double *Dg = workspace_d + S.doubles;
+    rocblas_int *info = (rocblas_int *)(Dg + n_lam);
     const double one = 1.0, zero = 0.0;
-    struct Group {
-        int m;
-        const std::vector<int32_t> *q;
-        size_t g;
-        int64_t off;
-        int32_t info;
-    };
-    std::vector<Group> work;
-    int64_t goff = 0;
-    int32_t ioff = 0;
-    size_t go = 0;
-    for (const auto &kv : groups) {
-        work.push_back(Group{kv.first, &kv.second, go, goff, ioff});
-        go += kv.second.size() * (size_t)kv.first * (size_t)kv.first;
-        goff += (int64_t)kv.second.size() * kv.first;
-        ioff += (int32_t)kv.second.size();
-    }
-    std::vector<int64_t> load(set.lanes.size(), 0);
-    std::vector<std::vector<const Group *>> todo(set.lanes.size());
-    for (auto it = work.rbegin(); it != work.rend(); ++it) {
-        const size_t lane = std::min_element(load.begin(), load.end()) - load.begin();
-        load[lane] += it->m;
-        todo[lane].push_back(&*it);
+    std::vector<double *> Gm, Ed;   // the lanes' buffers
+    double *p = workspace_d;
+    for (size_t lane = 0; lane < S.todo.size(); ++lane) {
+        Gm.push_back(p);
+        Ed.push_back(p + S.gram[lane]);
+        p += S.gram[lane] + S.diag[lane];
     }
     // one thread per lane: the chains are so many launches that one thread's
     // launch rate would bound them (14-site spatial Hubbard cut, 64 blocks of
@@ -222,24 +254,26 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
             return;
         }
         const rocblas_handle h = set.lanes[lane].h;
-        for (const Group *W : todo[lane]) {
-            const int m = W->m, c = (int)W->q->size();
+        double *G = Gm[lane], *E = Ed[lane];
+        for (const int g : S.todo[lane]) {
+            const Group &W = S.groups[g];
+            const int m = W.m, c = (int)W.q.size();
             for (int i = 0; i < c; ++i) {
-                const BlockDev &B = s->blocks[(*W->q)[i]];
+                const BlockDev &B = s->blocks[W.q[i]];
                 // Psi_q is row-major d_L x d_R: column-major it is A (d_R x d_L, lda = d_R)
                 const double *A = psi_d + B.offset;
                 const bool left = B.d_l <= B.d_r;   // Psi Psi^T = A^T A (d_L x d_L), else Psi^T Psi = A A^T
                 const rocblas_status rs =
                     rocblas_dsyrk(h, rocblas_fill_upper, left ? rocblas_operation_transpose : rocblas_operation_none, m,
-                                  left ? B.d_r : B.d_l, &one, A, B.d_r, &zero, G + W->g + (size_t)i * m * m, m);
+                                  left ? B.d_r : B.d_l, &one, A, B.d_r, &zero, G + (size_t)i * m * m, m);
                 if (rs != rocblas_status_success) {
                     err[lane] = Err{"rocblas_dsyrk", (int)rs};
                     return;
                 }
             }
             const rocblas_status rs = rocsolver_dsyevd_strided_batched(
-                h, rocblas_evect_none, rocblas_fill_upper, m, G + W->g, m, (rocblas_stride)m * m, Dg + W->off, m,
-                E + W->off, m, info + W->info, c);
+                h, rocblas_evect_none, rocblas_fill_upper, m, G, m, (rocblas_stride)m * m, Dg + W.off, m, E, m,
+                info + W.info, c);
             if (rs != rocblas_status_success) {
                 err[lane] = Err{"rocsolver_dsyevd_strided_batched", (int)rs};
                 return;
@@ -265,26 +299,24 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
     }
     if (le != hipSuccess) return hip_fail(le, "entanglement lanes");
     std::vector<double> ev((size_t)n_lam);
-    std::vector<rocblas_int> inf((size_t)std::max(ioff, 1), 0);
+    const int32_t n_info = S.groups.empty() ? 0 : S.groups.back().info + (int32_t)S.groups.back().q.size();
+    std::vector<rocblas_int> inf((size_t)std::max(n_info, 1), 0);
     hipError_t e = n_lam ? hipMemcpyAsync(ev.data(), Dg, sizeof(double) * n_lam, hipMemcpyDeviceToHost, hs) : hipSuccess;
-    if (e == hipSuccess && ioff)
-        e = hipMemcpyAsync(inf.data(), info, sizeof(rocblas_int) * ioff, hipMemcpyDeviceToHost, hs);
+    if (e == hipSuccess && n_info)
+        e = hipMemcpyAsync(inf.data(), info, sizeof(rocblas_int) * n_info, hipMemcpyDeviceToHost, hs);
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
     if (e != hipSuccess) return fail(ECUT_EDEVICE, std::string("entanglement spectrum: ") + hipGetErrorString(e));
     // each block's eigenvalues, descending, at its place in block order
     std::vector<int64_t> lam_off((size_t)nb + 1, 0);
     for (int32_t q = 0; q < nb; ++q)
         lam_off[q + 1] = lam_off[q] + std::min(s->blocks[q].d_l, s->blocks[q].d_r);
-    goff = 0;
-    ioff = 0;
-    for (const auto &kv : groups) {
-        const int m = kv.first;
-        for (size_t i = 0; i < kv.second.size(); ++i, ++ioff) {
-            const int32_t q = kv.second[i];
-            if (inf[ioff] != 0) return fail(ECUT_ENOTCONV, "rocsolver_dsyevd did not converge on block " + std::to_string(q));
-            for (int k = 0; k < m; ++k) lambda[lam_off[q] + k] = ev[(size_t)(goff + (int64_t)i * m + m - 1 - k)];
+    for (const Group &W : S.groups) {
+        const int m = W.m;
+        for (size_t i = 0; i < W.q.size(); ++i) {
+            const int32_t q = W.q[i];
+            if (inf[W.info + i] != 0) return fail(ECUT_ENOTCONV, "rocsolver_dsyevd did not converge on block " + std::to_string(q));
+            for (int k = 0; k < m; ++k) lambda[lam_off[q] + k] = ev[(size_t)(W.off + (int64_t)i * m + m - 1 - k)];
         }
-        goff += (int64_t)kv.second.size() * m;
     }
     int64_t off_l = n_lam;
     // normalise to the state's norm: the eigenvalues of rho_L of psi / |psi|
@@ -322,17 +354,17 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
         std::fill(w_p, w_p + n_parts, 0.0);
         for (int32_t q = 0; q < nb; ++q) w_p[part[q]] += w_q[q] * w_q[q];
     }
-    ecut_entanglement S{};
-    S.n_blocks = nb;
-    S.n_parts = n_parts;
-    S.n_lambda = off_l;
-    S.norm2 = norm2;
-    S.weight_ipr = w2 > 0.0 ? 1.0 / w2 : 0.0;
-    S.n_eff = c2 > 0.0 ? 1.0 / c2 : 0.0;
-    S.entropy = 0.0;
+    ecut_entanglement R{};
+    R.n_blocks = nb;
+    R.n_parts = n_parts;
+    R.n_lambda = off_l;
+    R.norm2 = norm2;
+    R.weight_ipr = w2 > 0.0 ? 1.0 / w2 : 0.0;
+    R.n_eff = c2 > 0.0 ? 1.0 / c2 : 0.0;
+    R.entropy = 0.0;
     for (int64_t i = 0; i < off_l; ++i)
-        if (lambda[i] > 0.0) S.entropy -= lambda[i] * std::log(lambda[i]);
-    *summary = S;
+        if (lambda[i] > 0.0) R.entropy -= lambda[i] * std::log(lambda[i]);
+    *summary = R;
     return ECUT_OK;
 }
 

@@ -28,3 +28,26 @@ def test_refused_while_the_stream_is_captured(dev):
         assert np.array_equal(np.concatenate(s.entanglement(x)["lam"]), ref)
         torch.cuda.synchronize()
         assert torch.equal(y, sum([x] * (2 * k - 1), x))
+
+
+# (problem, the old single chain's workspace in words): the largest group of
+# equal blocks, its off-diagonals, every eigenvalue, a status word a block
+@pytest.mark.parametrize("p", [
+    I.Problem(I.xxz_chain(12, 1.0, 0.7), I.Cut("spatial", I.left_mask_first(6)), 6),
+    I.Problem(I.xxz_chain(30, 1.0, 0.7), I.Cut("spatial", I.left_mask_first(15)), 15),
+    I.Problem(I.xxz_chain(31, 1.0, 0.7), I.Cut("spatial", I.left_mask_first(15)), 15),
+    I.Problem(I.xxz_chain(32, 1.0, 0.7), I.Cut("spatial", I.left_mask_first(16)), 16),
+    I.Problem(I.hubbard_chain(14, 1.0, 4.0, V=0.5), I.Cut("spatial", I.left_mask_first(7)), 7, 7)],
+    ids=["spin12", "spin30", "spin31", "spin32", "hubbard14"])
+def test_workspace_beside_the_largest_group_is_bounded(p):
+    """The blocks that run side by side take at most 1 GiB (and their
+    off-diagonals) more than the largest group of equal blocks alone."""
+    import ctypes
+    S = E.Sectors.from_problem(p, host_only=True)
+    m = S.blocks()[:, 2:4].min(axis=1)
+    sizes, counts = np.unique(m[m > 0], return_counts=True)
+    one_chain = int(max(sizes * sizes * counts) + max(sizes * counts) + m.sum() + (len(m) + 1) // 2 + 1)
+    nl = E._sz()
+    got = int(E.lib().ecut_entanglement_sizes(S.h, ctypes.byref(nl)))
+    assert nl.value == m.sum()
+    assert one_chain <= got <= one_chain + (1 << 27) + m.sum()
