@@ -279,24 +279,17 @@ def serving_bench(n_requests, budget_gb):
 
 
 def kernel_name(S):
-    """Name of the kernel that carries the apply under the handle's tuning
-    (of a host-only handle, which runs none: the kernel of its variant)."""
+    """Names of the kernels of an apply under the handle's tuning (of a
+    host-only handle, which runs none: the kernel of its variant)."""
     info, t = S.info, S.get_tuning()
-    two_pass = "k_hubP+k_hub3" if info.n_left_sites >= 14 else "k_hubU+k_hub3"   # panels: uniform open chains only
-    if (info.device_bytes and info.kernel == 1 and info.kernel_flags & 32 and (t["variant"] == 6 or not any(t.values()))
-            and S.dim <= (1 << 20 if info.kernel_flags & 2 else 1 << 18)):
-        return "k_hubF"
-    if info.device_bytes and not any(t.values()):   # the default selects by size
-        if info.kernel == 1 and info.kernel_flags & 32:
-            return two_pass if info.kernel_flags & 2 and S.dim >= 1 << 25 else "k_hubU+k_hubD"
-        if info.kernel_flags & 64:
-            return "k_flat" if S.dim <= 1 << 20 else "k_spinL+k_spinR"
+    if info.device_bytes:
+        return S.apply_kernels()
     if info.kernel == 1:
         v = t["variant"]
         if v == 0:
             return "k_hub3" if info.kernel_flags & 2 else "k_hub2"
         return {1: "k_hub", 2: "k_hub2", 3: "k_upslab+k_hub3", 4: "k_hubrow", 5: "k_hubseg", 6: "k_hubU+k_hubD",
-                7: two_pass}[v]
+                7: "k_hubU+k_hub3"}[v]
     if info.kernel_flags & 64 and t["variant"] == 2:
         return "k_spinL+k_spinR"
     return "k_spin" if (info.kernel_flags & 4 and t["variant"] == 0) else "k_rows"

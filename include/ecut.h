@@ -371,6 +371,14 @@ ecut_status ecut_get_tuning(const ecut_sectors *s, ecut_tuning *t);
 ecut_status ecut_set_tuning(ecut_sectors *s, const ecut_tuning *t);
 
 /*
+ * Names of the kernels that ecut_apply_H launches under the handle's tuning,
+ * in launch order, joined by '+' ("k_hubU+k_hubD"): a static string.  Of a
+ * host-only handle: those that the same handle on a device would launch.
+ * NULL handle: "".
+ */
+const char *ecut_apply_kernels(const ecut_sectors *s);
+
+/*
  * Autotuner: times ecut_apply_H(x_d -> y_d) for each candidate launch tuning
  * (Hubbard: kernel variant, row order, XCD chunking; spin: short-row tile and
  * grid, the generic row kernel, the two-pass kernels) with HIP events on `stream`, keeps the

@@ -704,6 +704,24 @@ ecut_status launch_apply(const ecut_sectors *s, const ProblemDev &P, hipStream_t
     return ECUT_OK;
 }
 
+// the kernels launch_apply runs, in the order of its branches
+static const char *kernel_names(const ecut_sectors *s) {
+    if (hub_fused(s)) return "k_hubF";
+    if (s->kernel == 1) {
+        const ApplyTuning T = hub_tuning(s);
+        const bool panels = s->hp_lo > 0;
+        if ((T.variant == 0 || T.variant == 3) && s->hub3_ok) return T.variant == 3 ? "k_upslab+k_hub3" : "k_hub3";
+        if (T.variant == 6 && s->hub6_ok) return panels ? "k_hubP+k_hubD" : "k_hubU+k_hubD";
+        if (T.variant == 7 && s->hub3_ok) return panels ? "k_hubP+k_hub3" : "k_hubU+k_hub3";
+        if (T.variant == 5 && s->hubseg_ok) return "k_hubseg";
+        if (T.variant == 4 && s->hubrow_ok) return "k_hubrow";
+        return (T.variant == 0 || T.variant == 2) && s->hub2_ok ? "k_hub2" : "k_hub";
+    }
+    if (two_pass_rows(s, s->tune)) return "k_spinL+k_spinR";
+    if (!s->flat_base.empty() && default_tuning(s->tune)) return "k_flat";
+    return s->spin_ok && s->tune.variant == 0 ? "k_spin" : "k_rows";
+}
+
 bool own_launch(const ecut_sectors *s) { return s->kernel == 1 || two_pass_rows(s, s->tune); }
 
 bool hub6_batchable(const ecut_sectors *s) {
@@ -1049,6 +1067,8 @@ void ecut_sectors_free(ecut_sectors *s) {
     release_device(s);
     delete s;
 }
+
+const char *ecut_apply_kernels(const ecut_sectors *s) { return s ? kernel_names(s) : ""; }
 
 ecut_status ecut_sectors_get_info(const ecut_sectors *s, ecut_sectors_info *info) {
     if (!s || !info) return fail(ECUT_EINVAL, "null argument");

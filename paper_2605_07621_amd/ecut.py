@@ -108,6 +108,7 @@ SYMBOLS = [
     ("ecut_apply_H_batch_noalloc", _i32, [_i32, _vp, _vp, _vp, _vp]),
     ("ecut_get_tuning", _i32, [_vp, ctypes.POINTER(Tuning)]),
     ("ecut_set_tuning", _i32, [_vp, ctypes.POINTER(Tuning)]),
+    ("ecut_apply_kernels", ctypes.c_char_p, [_vp]),
     ("ecut_autotune", _i32, [_vp, _vp, _vp, _vp, ctypes.POINTER(Tuning)]),
     ("ecut_lanczos_workspace", _sz, [_vp, ctypes.POINTER(LanczosOpts)]),
     ("ecut_lanczos_ground_state", _i32, [_vp, _vp, ctypes.POINTER(LanczosOpts), ctypes.POINTER(_dbl), _vp,
@@ -315,6 +316,10 @@ class Sectors:
     def set_tuning(self, grid=0, n_xcd=0, row_order=0, variant=0, tile=0):
         t = Tuning(int(grid), int(n_xcd), int(row_order), int(variant), int(tile))
         _check(lib().ecut_set_tuning(self.h, ctypes.byref(t)))
+
+    def apply_kernels(self):
+        """ecut_apply_kernels: names of the kernels of one application under the handle's tuning."""
+        return lib().ecut_apply_kernels(self.h).decode()
 
     def autotune(self, x, y, stream=None):
         t = Tuning()
