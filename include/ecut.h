@@ -306,8 +306,8 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
  *              kernel_flags bit 4; row_order ignored; n_xcd 1 = plain grid
  *              stride, else 8 XCD chunks),
  *              6 two passes of one work group per item (kernel_flags bit 5;
- *              the vectors the default's fused kernel takes run on it here
- *              too, and grid and tile are then ignored):
+ *              with every other field 0, the vectors the default's fused
+ *              kernel takes run on it here too):
  *              the left operator over column slabs in inversion-level row
  *              order (grid = rows per item, 0 = 4, at most 32), then the
  *              right operator, diagonal and epilogue with the source

@@ -497,8 +497,12 @@ bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T) {
 bool hub_fused_size(const ecut_sectors *s) {
     return s->kernel == 1 && s->hub6_ok && s->dim <= (s->h6_uniform ? HUBF_MAX_DIM_UNIFORM : HUBF_MAX_DIM);
 }
+// Variant 6 with no other field set leaves the choice to the library too; with
+// any of them it names the two passes and their launch shape.
 bool hub_fused(const ecut_sectors *s) {
-    return hub_fused_size(s) && (s->tune.variant == 6 || default_tuning(s->tune));
+    const ApplyTuning &T = s->tune;
+    return hub_fused_size(s) && T.grid == 0 && T.n_xcd == 0 && T.order == 0 && T.tile == 0 &&
+           (T.variant == 0 || T.variant == 6);
 }
 
 // The default tuning above those sizes: the two-pass kernels, which beat the

@@ -201,7 +201,7 @@ static double sector_states(const ecut_model_desc &m, ecut_qnum q) {
 // solve overwrites later) and reused for every later request of the shape.
 static std::mutex g_tune_mu;
 // Hubbard problems up to this many amplitudes (chains of up to 10 sites at
-// half filling) share the merged two-pass launches of a step
+// half filling) share the merged launch of a step
 static constexpr int64_t SMALL_HUB_DIM = (int64_t)1 << 18;
 static constexpr int64_t SMALL_SPIN_DIM = (int64_t)1 << 20;
 static std::map<std::string, ecut_tuning> g_tunings;
@@ -220,10 +220,9 @@ static ecut_status tune_once(ecut_sectors *s, const double *x, double *y, hipStr
     ecut_tuning best{};
     ecut_status rs;
     if (merged && s->kernel == 1 && s->hub6_ok && s->dim <= SMALL_HUB_DIM && s->h6_maxq <= HUBD_BATCH_SLOTS) {
-        // small Hubbard problems take the fused kernel (two passes where it
-        // does not reach), so that every step runs all of them in one merged
-        // launch
-        best = ecut_tuning{0, 8, 1, 6, 2};
+        // small Hubbard problems take the fused kernel, so that every step
+        // runs all of them in one merged launch
+        best = ecut_tuning{0, 0, 0, 6, 0};
         rs = ecut_set_tuning(s, &best);
     } else {
         rs = ecut_autotune(s, x, y, st, &best);

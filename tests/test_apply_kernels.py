@@ -29,6 +29,14 @@ def test_default_kernels(p, want):
 
 
 def test_kernels_of_named_variants():
+    """A tuning that names a launch shape runs the kernels the shape belongs
+    to, at every size; variant 6 alone leaves the choice to the library."""
+    S = E.Sectors.from_problem(_hub(10, 5, 5), host_only=True)
+    S.set_tuning(variant=6)
+    assert S.apply_kernels() == "k_hubF"
+    for t in (dict(grid=4), dict(tile=1), dict(n_xcd=8), dict(n_xcd=1), dict(row_order=1)):
+        S.set_tuning(variant=6, **t)
+        assert S.apply_kernels() == "k_hubU+k_hubD", t
     S = E.Sectors.from_problem(_hub(16, 8, 8), host_only=True)
     for v, want in ((1, "k_hub"), (2, "k_hub2"), (3, "k_upslab+k_hub3"), (4, "k_hubrow"), (5, "k_hubseg")):
         S.set_tuning(variant=v, n_xcd=8)
