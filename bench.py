@@ -51,7 +51,7 @@ def kernel_source_hash():
 # Launch tuning of each workload's timed applies: the autotuner's pick on
 # MI355X (its candidates within run noise of each other), pinned so that the
 # rocprofv3 counters committed under profiles/ describe the benchmarked run.
-PINNED_TUNING = {"hubbard16": "8,8,8,7,0", "j1j2_6x5": "4,8,0,2,0"}
+PINNED_TUNING = {"hubbard16": "0,8,8,7,0", "j1j2_6x5": "4,8,0,2,0"}
 
 
 def traffic_from_profile(kernel, workload, per_launch_alg):

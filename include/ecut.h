@@ -309,14 +309,18 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
  *              with every other field 0, the vectors the default's fused
  *              kernel takes run on it here too):
  *              the left operator over column slabs in inversion-level row
- *              order (grid = rows per item, 0 = 4, at most 32), then the
+ *              order (grid = rows per item, 0 = 4, at most 32), or, on open
+ *              chains of 14 to 20 sites with one hop value and where grid is
+ *              0 and n_xcd is not 1, over panels of rows that share the high
+ *              part of the up word; then the
  *              right operator, diagonal and epilogue with the source
  *              column of every hopping bond held in registers (tile = rows
  *              per item of that pass, 1, 2, 4, 8 or 16; 0 = 2); items dealt
  *              to the XCDs in contiguous ranges (n_xcd 1 = in launch order),
  *              7 the same left pass, then the right operator on class tiles
  *              (needs kernel_flags bit 1); tile = slabs side by side in one
- *              left-pass item (0 = 1, or 2 or 4; grid at most 32 / tile).
+ *              left-pass item (0 = 1, or 2 or 4; grid at most 32 / tile; any
+ *              but 0 selects the general left pass).
  *              Spin and generic problems (kernel 2) take variant 0 (the
  *              ranking-table spin kernel when kernel_flags bit 2 is set, else
  *              the generic row kernel) or 1 (the generic row kernel, which

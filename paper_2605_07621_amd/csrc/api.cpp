@@ -561,9 +561,16 @@ void hub6_shape(const ecut_sectors *s, HubUArgs &U, HubDArgs &D) {
     D.n_items = ((nr + D.rows_per_item - 1) / D.rows_per_item) * D.n_chunks;
 }
 
-// the left operator's pass of the two-pass kernels: on panels where they exist
+// The left operator's pass runs on panels where they exist, unless the tuning
+// names the general pass's shape: rows per item, items in launch order, or
+// slabs side by side.
+static bool left_on_panels(const ecut_sectors *s) {
+    const ApplyTuning &T = s->tune;
+    return s->hp_lo > 0 && T.grid == 0 && T.n_xcd != 1 && !(T.variant == 7 && T.tile > 0);
+}
+
 static hipError_t launch_left(const ecut_sectors *s, const HubUArgs &U, int n_xcd, hipStream_t st) {
-    if (s->hp_lo == 0) return launch_hub6_left(U, n_xcd, st);
+    if (!left_on_panels(s)) return launch_hub6_left(U, n_xcd, st);
     HubPArgs A = s->hp;
     A.x = U.x;
     A.y = U.y;
@@ -713,7 +720,7 @@ static const char *kernel_names(const ecut_sectors *s) {
     if (hub_fused(s)) return "k_hubF";
     if (s->kernel == 1) {
         const ApplyTuning T = hub_tuning(s);
-        const bool panels = s->hp_lo > 0;
+        const bool panels = left_on_panels(s);
         if ((T.variant == 0 || T.variant == 3) && s->hub3_ok) return T.variant == 3 ? "k_upslab+k_hub3" : "k_hub3";
         if (T.variant == 6 && s->hub6_ok) return panels ? "k_hubP+k_hubD" : "k_hubU+k_hubD";
         if (T.variant == 7 && s->hub3_ok) return panels ? "k_hubP+k_hub3" : "k_hubU+k_hub3";
@@ -748,7 +755,7 @@ void hub6_batch_add(HubBatch &b, const ecut_sectors *s, const ProblemDev &P) {
     D.xscale = P.xscale;
     D.zcoef = P.zcoef;
     D.dscale = P.dscale;
-    if (s->hp_lo > 0) {
+    if (left_on_panels(s)) {
         // left pass of its own: the merged launch of the general left passes
         // gets no item of this problem
         HubPArgs A = s->hp;

@@ -224,9 +224,9 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
         }
     }
     std::vector<ApplyTuning> cands;
-    // the default tuning where it selects the fused or the flat kernel, or is
-    // the only one
-    if (s->kernel == 1 ? hub_fused_size(s) : !s->spin_ok || !s->flat_base.empty())
+    // the default tuning where it selects the fused or the flat kernel or the
+    // left pass on panels, or is the only one
+    if (s->kernel == 1 ? hub_fused_size(s) || s->hp_lo > 0 : !s->spin_ok || !s->flat_base.empty())
         cands.push_back(ApplyTuning{0, 0, 0, s->kernel == 1 && !s->hub2_ok ? 6 : 0, 0});
     if (s->kernel == 1) {
         if (s->hub2_ok)
@@ -253,6 +253,11 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
         if (s->hub3_ok)
             for (int urows : {4, 8})
                 for (int order : {7, 8}) cands.push_back(ApplyTuning{urows, 8, order, 7, 0});
+        if (s->hp_lo > 0) {   // the left pass on panels: no shape of the general pass named
+            for (int rows : {2, 8}) cands.push_back(ApplyTuning{0, 8, 0, 6, rows});
+            if (s->hub3_ok)
+                for (int order : {7, 8}) cands.push_back(ApplyTuning{0, 8, order, 7, 0});
+        }
     } else if (s->spin_ok) {
         // spin kernel: short-row tile and grid; then the generic row kernel
         for (int order : {0, 1})

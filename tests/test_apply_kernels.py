@@ -41,6 +41,13 @@ def test_kernels_of_named_variants():
     for v, want in ((1, "k_hub"), (2, "k_hub2"), (3, "k_upslab+k_hub3"), (4, "k_hubrow"), (5, "k_hubseg")):
         S.set_tuning(variant=v, n_xcd=8)
         assert S.apply_kernels() == want
+    S = E.Sectors.from_problem(_hub(16, 8, 8), host_only=True)
+    for t, want in ((dict(variant=6), "k_hubP+k_hubD"), (dict(variant=6, n_xcd=8, tile=8), "k_hubP+k_hubD"),
+                    (dict(variant=6, grid=4), "k_hubU+k_hubD"), (dict(variant=6, n_xcd=1), "k_hubU+k_hubD"),
+                    (dict(variant=7, n_xcd=8, row_order=8), "k_hubP+k_hub3"), (dict(variant=7, grid=8), "k_hubU+k_hub3"),
+                    (dict(variant=7, tile=2), "k_hubU+k_hub3"), (dict(variant=7, n_xcd=1), "k_hubU+k_hub3")):
+        S.set_tuning(**t)
+        assert S.apply_kernels() == want, t
     S = E.Sectors.from_problem(_spin(24, 12, 12), host_only=True)
     for t, want in ((dict(tile=512), "k_spin"), (dict(variant=1), "k_rows"), (dict(variant=2), "k_spinL+k_spinR")):
         S.set_tuning(**t)
