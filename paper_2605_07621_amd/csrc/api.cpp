@@ -483,10 +483,14 @@ bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T) {
     // for the longest one: by default only where the mean row is a quarter of
     // it (14 sites at half filling, 719 of 1,225: 240 against 396 us on the
     // row kernel; 16 sites with 5 + 5 particles, 320 of 4,900: 1.74 against 0.75 ms)
+    // and fills the 128 threads of the smallest group (13 sites at half filling
+    // cut after 7, mean row 183: 84 against 103 us; after 8, 49: 196 against 102;
+    // after 10, 5: 1,700 against 106; cut after 7 with 6 + 5 particles, 145: 75
+    // against 81; with 5 + 5, 115: 70 against 63)
     if (!s->hub_spatial) return true;
     int64_t rows = 0;
     for (const BlockDev &B : s->blocks) rows += B.d_l;
-    return s->dim >= rows * s->max_d_r / 4;
+    return s->dim >= rows * s->max_d_r / 4 && s->dim >= rows * HUBSP_MIN_MEAN_ROW;
 }
 
 // The default tuning, and the two-pass tuning, of a Hubbard up/down problem

@@ -269,6 +269,7 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
             for (int rows : {4, 8, 16})
                 for (int xcd : {1, 8}) cands.push_back(ApplyTuning{rows, xcd, 0, 2, 0});
     } else {
+        if (s->sp2_ok) cands.push_back(ApplyTuning{0, 0, 0, 1, 0});   // the row kernel by name: the default may be another
         if (s->sp2_ok && !s->wide_rows)   // the spatial Hubbard cut: the two-pass row kernels
             for (int rows : {4, 8, 16})
                 for (int xcd : {1, 8}) cands.push_back(ApplyTuning{rows, xcd, 0, 2, 0});

@@ -21,6 +21,8 @@ def _ext(n, cut, a, b):
     (_spin(16, 8, 8), "k_flat"), (_spin(24, 12, 12), "k_spinL+k_spinR"), (_spin(24, 8, 12), "k_spinL+k_spinR"),
     (_spin(28, 12, 9), "k_rows"), (_spin(36, 17, 3, ring=True), "k_rows"),
     (_ext(10, 5, 5, 5), "k_flat"), (_ext(14, 7, 7, 7), "k_spinL+k_spinR"), (_ext(16, 8, 5, 5), "k_rows"),
+    (_ext(13, 7, 6, 6), "k_spinL+k_spinR"), (_ext(13, 7, 5, 5), "k_rows"), (_ext(13, 8, 6, 6), "k_rows"),
+    (_ext(13, 10, 6, 6), "k_rows"),
     (_hub(12, 6, 6), "k_hubF"), (_hub(13, 6, 7, ring=True), "k_hubU+k_hubD"), (_hub(14, 7, 7), "k_hubP+k_hubD"),
     (_hub(16, 8, 8), "k_hubP+k_hub3")],
     ids=lambda v: v if isinstance(v, str) else f"{v.model.name}_{v.n_up}_{v.n_dn}_{v.cut.left_mask}")
