@@ -487,9 +487,13 @@ bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T) {
     // cut after 7, mean row 183: 84 against 103 us; after 8, 49: 196 against 102;
     // after 10, 5: 1,700 against 106; cut after 7 with 6 + 5 particles, 145: 75
     // against 81; with 5 + 5, 115: 70 against 63)
-    if (!s->hub_spatial) return true;
+    // spin rows shorter than half a wave on average stay on the one-pass kernel,
+    // several rows a group (right part of 7 sites, 23-site chain, mean row 22: 62
+    // against 67 us; 24 sites with 9 up spins, 26: 59 both; 24 sites cut after
+    // 16, 42: 117 against 87)
     int64_t rows = 0;
     for (const BlockDev &B : s->blocks) rows += B.d_l;
+    if (!s->hub_spatial) return s->dim >= rows * SPIN_MIN_MEAN_ROW;
     return s->dim >= rows * s->max_d_r / 4 && s->dim >= rows * HUBSP_MIN_MEAN_ROW;
 }
 

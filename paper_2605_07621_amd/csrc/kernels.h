@@ -34,6 +34,7 @@ constexpr int XTAB_SLOTS = 256;               // LDS doubles of a row's folded d
 constexpr int SPIN_MAX_FLIP = 64;            // flip-flop terms inside the right part
 constexpr int SPIN_MANY_THREADS = 256;       // kernel for items of several short rows
 constexpr int SPIN_FEW_ROWS = 4096;          // two-pass kernels: most short rows that are items of their own by default
+constexpr int SPIN_MIN_MEAN_ROW = 24;         // shortest mean row of the two-pass spin kernels by default
 constexpr int HUBSP_MIN_MEAN_ROW = 128;      // spatial Hubbard cut: shortest mean row of the two-pass kernels by default
 constexpr int SPIN_MANY_TILE = 512;          // most amplitudes per such item: the default and largest tile
 constexpr int HUBROW_THREADS = 1024;

@@ -20,6 +20,7 @@ def _ext(n, cut, a, b):
 @pytest.mark.parametrize("p,want", [
     (_spin(16, 8, 8), "k_flat"), (_spin(24, 12, 12), "k_spinL+k_spinR"), (_spin(24, 8, 12), "k_spinL+k_spinR"),
     (_spin(28, 12, 9), "k_rows"), (_spin(36, 17, 3, ring=True), "k_rows"),
+    (_spin(23, 16, 11), "k_spin"), (_spin(24, 16, 9), "k_spinL+k_spinR"), (_spin(24, 16, 12), "k_spinL+k_spinR"),
     (_ext(10, 5, 5, 5), "k_flat"), (_ext(14, 7, 7, 7), "k_spinL+k_spinR"), (_ext(16, 8, 5, 5), "k_rows"),
     (_ext(13, 7, 6, 6), "k_spinL+k_spinR"), (_ext(13, 7, 5, 5), "k_rows"), (_ext(13, 8, 6, 6), "k_rows"),
     (_ext(13, 10, 6, 6), "k_rows"),
