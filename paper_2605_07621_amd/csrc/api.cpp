@@ -497,6 +497,17 @@ bool two_pass_rows(const ecut_sectors *s, const ApplyTuning &T) {
     return s->dim >= rows * s->max_d_r / 4 && s->dim >= rows * HUBSP_MIN_MEAN_ROW;
 }
 
+// Many short rows (one particle or hole of the down spin, or none): the fused
+// and the two-pass kernels give every row lanes of its own, the class tiles
+// pack rows.  The line is in the number of rows: 15 sites with 7 + 1 particles
+// (6,435 rows of 15) fused 14.6 against 15.5 us, 16 sites with 6 + 1 (8,008 of 16)
+// 17.3 against 15.3, with 8 + 0 (12,870 of 1) 25.6 against 10.3; 18 sites with
+// 9 + 1 (48,620 of 18) 150 against 68, 20 with 10 + 1 (184,756 of 20), two passes,
+// 264 against 214.
+static bool hub_short_rows(const ecut_sectors *s) {
+    return s->hub2_ok && s->blocks[0].d_r < HUB_SHORT_ROW && s->blocks[0].d_l >= HUB_SHORT_ROW_MIN_ROWS;
+}
+
 // The default tuning, and the two-pass tuning, of a Hubbard up/down problem
 // short enough for the fused kernel.  With one hop value (no value table to
 // read) it is level with the two passes at 853,776 amplitudes (16.4 us both,
@@ -510,7 +521,7 @@ bool hub_fused_size(const ecut_sectors *s) {
 bool hub_fused(const ecut_sectors *s) {
     const ApplyTuning &T = s->tune;
     return hub_fused_size(s) && T.grid == 0 && T.n_xcd == 0 && T.order == 0 && T.tile == 0 &&
-           (T.variant == 0 || T.variant == 6);
+           (T.variant == 6 || (T.variant == 0 && !hub_short_rows(s)));
 }
 
 // The default tuning above those sizes: the two-pass kernels, which beat the
@@ -519,7 +530,7 @@ bool hub_fused(const ecut_sectors *s) {
 // last-level cache take the class tiles for the right pass where they exist
 // (16-site chain: 2.2 against 2.8 ms).
 ApplyTuning hub_tuning(const ecut_sectors *s) {
-    if (s->kernel != 1 || !default_tuning(s->tune) || !s->hub6_ok) return s->tune;
+    if (s->kernel != 1 || !default_tuning(s->tune) || !s->hub6_ok || hub_short_rows(s)) return s->tune;
     if (s->hub3_ok && s->dim >= STREAM_STORE_MIN) return ApplyTuning{8, 8, 0, 7, 0};
     return ApplyTuning{0, 8, 0, 6, 0};
 }

@@ -37,6 +37,8 @@ constexpr int SPIN_FEW_ROWS = 4096;          // two-pass kernels: most short row
 constexpr int SPIN_MIN_MEAN_ROW = 24;         // shortest mean row of the two-pass spin kernels by default
 constexpr int HUBSP_MIN_MEAN_ROW = 128;      // spatial Hubbard cut: shortest mean row of the two-pass kernels by default
 constexpr int SPIN_MANY_TILE = 512;          // most amplitudes per such item: the default and largest tile
+constexpr int HUB_SHORT_ROW = 32;             // up/down cut: shorter rows, if there are this many of them, take the
+constexpr int HUB_SHORT_ROW_MIN_ROWS = 7168;  // class tiles by default
 constexpr int HUBROW_THREADS = 1024;
 constexpr int HUBROW_P = 7;                  // column pairs per thread of the whole-row Hubbard kernel
 constexpr int HUBROW_P_SHORT = 4;            // the same for 512-thread groups on rows of <= 4096 columns

@@ -224,10 +224,11 @@ ecut_status ecut_autotune(ecut_sectors *s, const double *x_d, double *y_d, void 
         }
     }
     std::vector<ApplyTuning> cands;
-    // the default tuning where it selects the fused or the flat kernel or the
-    // left pass on panels, or is the only one
-    if (s->kernel == 1 ? hub_fused_size(s) || s->hp_lo > 0 : !s->spin_ok || !s->flat_base.empty())
-        cands.push_back(ApplyTuning{0, 0, 0, s->kernel == 1 && !s->hub2_ok ? 6 : 0, 0});
+    // the fused kernel; the default tuning where it selects the flat kernel or
+    // may select the left pass on panels, or is the only one
+    if (s->kernel == 1 && hub_fused_size(s)) cands.push_back(ApplyTuning{0, 0, 0, 6, 0});
+    else if (s->kernel == 1 ? s->hp_lo > 0 && s->hub2_ok : !s->spin_ok || !s->flat_base.empty())
+        cands.push_back(ApplyTuning{0, 0, 0, 0, 0});
     if (s->kernel == 1) {
         if (s->hub2_ok)
             for (int order = 0; order < 6; ++order)

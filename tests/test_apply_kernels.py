@@ -25,7 +25,10 @@ def _ext(n, cut, a, b):
     (_ext(13, 7, 6, 6), "k_spinL+k_spinR"), (_ext(13, 7, 5, 5), "k_rows"), (_ext(13, 8, 6, 6), "k_rows"),
     (_ext(13, 10, 6, 6), "k_rows"),
     (_hub(12, 6, 6), "k_hubF"), (_hub(13, 6, 7, ring=True), "k_hubU+k_hubD"), (_hub(14, 7, 7), "k_hubP+k_hubD"),
-    (_hub(16, 8, 8), "k_hubP+k_hub3")],
+    (_hub(16, 8, 8), "k_hubP+k_hub3"),
+    (_hub(15, 7, 1), "k_hubF"), (_hub(16, 8, 1), "k_hub3"), (_hub(16, 8, 0), "k_hub3"), (_hub(16, 1, 8), "k_hubF"),
+    (_hub(16, 8, 1, ring=True), "k_hub2"), (_hub(18, 9, 1), "k_hub2"), (_hub(20, 10, 1), "k_hub2"),
+    (_hub(20, 10, 19), "k_hub2"), (_hub(16, 8, 2), "k_hubP+k_hubD")],
     ids=lambda v: v if isinstance(v, str) else f"{v.model.name}_{v.n_up}_{v.n_dn}_{v.cut.left_mask}")
 def test_default_kernels(p, want):
     assert E.Sectors.from_problem(p, host_only=True).apply_kernels() == want
