@@ -582,9 +582,25 @@ void hub6_shape(const ecut_sectors *s, HubUArgs &U, HubDArgs &D) {
 
 // The left operator's pass runs on panels where they exist, unless the tuning
 // names the general pass's shape: rows per item, items in launch order, or
-// slabs side by side.
+// slabs side by side.  The default takes them where a solve's three vectors no
+// longer share the last-level cache and panels are long: a panel's low hops cost no load, but its few waves must keep
+// the high hops' panels in L2, and with many high sites those are most of the
+// loads.  Whole applications, general pass -> panels, by mean rows a panel:
+// 16 sites 8 + 8 particles (50 rows) 2,029 -> 1,950 us, 8 + 5 859 -> 818, 6 + 6 (32)
+// 855 -> 840, 5 + 8 (20) 716 -> 738, 4 + 8 (11) 298 -> 340; 15 sites 7 + 7 (25)
+// 562 -> 549, 5 + 7 (14) 255 -> 277; 17 sites 8 + 4 (48) 977 -> 947, 6 + 4 (27) 499 ->
+// 504; 18 sites 9 + 4 (48) 2,563 -> 2,511, but 2,516 with 8 rows an item, 7 + 4 (33)
+// level, 6 + 4 (23) 984 -> 1,019; 20 sites 10 + 3 (45) 3,917 -> 3,985.  At the line in
+// size, 14 sites 7 + 7 (27; 11.8M amplitudes): 180 -> 172 on three vectors in turn,
+// 125 -> 133 on one pair; below, 16 sites 8 + 3 (50; 7.2M) 89 -> 97 on one pair.
+static bool panels_by_default(const ecut_sectors *s) {
+    const int64_t panels = (int64_t)s->hp_panels.size() / HUBP_PANEL_INTS;
+    return s->n_sites <= 17 && s->dim >= HUBP_MIN_DIM &&
+           s->blocks[0].d_l >= panels * (s->n_sites <= 16 ? HUBP_MIN_MEAN : HUBP_MIN_MEAN_17);
+}
 static bool left_on_panels(const ecut_sectors *s) {
     const ApplyTuning &T = s->tune;
+    if (default_tuning(T)) return s->hp_lo > 0 && panels_by_default(s);
     return s->hp_lo > 0 && T.grid == 0 && T.n_xcd != 1 && !(T.variant == 7 && T.tile > 0);
 }
 

@@ -53,6 +53,9 @@ constexpr int HUBP_MAX_LO = 8;               // most low sites of the up word (c
 constexpr int HUBP_MIN_SITES = 14;           // shortest chain it takes
 constexpr size_t HUBP_LDS = 84 * 1024;       // LDS request that keeps one group on a compute unit (160 KB)
 constexpr int HUBP_MAX_PANEL = 70;           // rows of the longest panel, C(8, 4)
+constexpr int64_t HUBP_MIN_DIM = ((int64_t)256 << 20) / 24;   // by default: shortest vectors (three in 256 MB),
+constexpr int HUBP_MIN_MEAN = 25;            // mean rows a panel,
+constexpr int HUBP_MIN_MEAN_17 = 38;         // and those on 17 sites
 constexpr int HUBP_CHUNK = 28;               // rows whose loads are issued together
 constexpr int HUBP_PANEL_INTS = 16;          // ints of a panel's descriptor
 constexpr int HUBP_HI_OCCUPIED = 256;        // flag beside the low particle number: the high part's first site is occupied
