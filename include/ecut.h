@@ -264,7 +264,7 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
  * kernels by the vector's size: Hubbard up/down problems of at most 32
  * hopping bonds run one fused kernel up to 2^18 amplitudes (2^20 if every
  * hop has the same value), the two-pass kernels (variant 6) above, and
- * variant 7 from 2^25 where it is available (open chains of 14 to 17 sites with
+ * variant 7 from 21 * 2^20 where it is available (open chains of 14 to 17 sites with
  * one hop value and 11.2 million amplitudes or more: the left pass on panels,
  * if those are 25 rows long on average, 38 on 17 sites); spin problems and the spatial
  * Hubbard cut, where kernel_flags bit 6 is set, run one kernel with a thread

@@ -526,12 +526,14 @@ bool hub_fused(const ecut_sectors *s) {
 
 // The default tuning above those sizes: the two-pass kernels, which beat the
 // one-pass class tiles at every size measured (12-site chain 16.4 against 22.4
-// us, 14-site 180 against 325, 14-site ring 186 against 481); vectors past the
-// last-level cache take the class tiles for the right pass where they exist
-// (16-site chain: 2.2 against 2.8 ms).
+// us, 14-site 180 against 325, 14-site ring 186 against 481); long vectors take
+// the class tiles for the right pass where they exist (16-site chain: 2.2 against
+// 2.8 ms; 4 + 8 particles, 23.4M amplitudes, 300 against 365 us, where the one-pass
+// class tiles take 344; 8 + 4, 371 against 402; 15 sites, 19.3M, 5 + 7 264 against
+// 290, but 7 + 5 312 against 297).
 ApplyTuning hub_tuning(const ecut_sectors *s) {
     if (s->kernel != 1 || !default_tuning(s->tune) || !s->hub6_ok || hub_short_rows(s)) return s->tune;
-    if (s->hub3_ok && s->dim >= STREAM_STORE_MIN) return ApplyTuning{8, 8, 0, 7, 0};
+    if (s->hub3_ok && s->dim >= HUB7_MIN_DIM) return ApplyTuning{8, 8, 0, 7, 0};
     return ApplyTuning{0, 8, 0, 6, 0};
 }
 

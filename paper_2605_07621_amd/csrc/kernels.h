@@ -44,6 +44,7 @@ constexpr int HUBROW_P = 7;                  // column pairs per thread of the w
 constexpr int HUBROW_P_SHORT = 4;            // the same for 512-thread groups on rows of <= 4096 columns
 constexpr int HUBROW_COLS = 2 * HUBROW_P * HUBROW_THREADS;
 constexpr int HUBROW_MAX_BOND = 64;
+constexpr int64_t HUB7_MIN_DIM = (int64_t)21 << 20;   // right pass on class tiles by default: shortest vectors
 constexpr int HUBU_THREADS = 256;            // two-pass kernels: left-operator pass, one row per wave at a time
 constexpr int HUBU_NB = 8;                   // neighbour-row loads issued together per lane
 constexpr int HUBU_ROWS = 4;                  // rows of the row order per left-operator item

@@ -29,8 +29,8 @@ def _ext(n, cut, a, b):
     (_hub(15, 7, 1), "k_hubF"), (_hub(16, 8, 1), "k_hub3"), (_hub(16, 8, 0), "k_hub3"), (_hub(16, 1, 8), "k_hubF"),
     (_hub(16, 8, 1, ring=True), "k_hub2"), (_hub(18, 9, 1), "k_hub2"), (_hub(20, 10, 1), "k_hub2"),
     (_hub(20, 10, 19), "k_hub2"), (_hub(16, 8, 2), "k_hubU+k_hubD"),
-    (_hub(14, 7, 6), "k_hubU+k_hubD"), (_hub(15, 7, 7), "k_hubP+k_hub3"), (_hub(15, 7, 5), "k_hubP+k_hubD"), (_hub(15, 6, 7), "k_hubU+k_hubD"),
-    (_hub(16, 6, 6), "k_hubP+k_hub3"), (_hub(16, 5, 8), "k_hubU+k_hub3"), (_hub(16, 4, 8), "k_hubU+k_hubD"),
+    (_hub(14, 7, 6), "k_hubU+k_hubD"), (_hub(15, 7, 7), "k_hubP+k_hub3"), (_hub(15, 7, 5), "k_hubP+k_hubD"), (_hub(15, 6, 7), "k_hubU+k_hub3"), (_hub(15, 5, 7), "k_hubU+k_hubD"),
+    (_hub(16, 6, 6), "k_hubP+k_hub3"), (_hub(16, 5, 8), "k_hubU+k_hub3"), (_hub(16, 4, 8), "k_hubU+k_hub3"),
     (_hub(16, 3, 8), "k_hubU+k_hubD"), (_hub(17, 8, 4), "k_hubP+k_hubD"), (_hub(17, 6, 4), "k_hubU+k_hubD"),
     (_hub(18, 9, 3), "k_hubU+k_hubD")],
     ids=lambda v: v if isinstance(v, str) else f"{v.model.name}_{v.n_up}_{v.n_dn}_{v.cut.left_mask}")
