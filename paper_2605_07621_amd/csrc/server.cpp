@@ -224,14 +224,12 @@ static ecut_status tune_once(ecut_sectors *s, const double *x, double *y, hipStr
         // runs all of them in one merged launch
         best = ecut_tuning{0, 0, 0, 6, 0};
         rs = ecut_set_tuning(s, &best);
+    } else if (merged && s->spin_ok && s->dim <= SMALL_SPIN_DIM) {
+        // small spin problems keep the default, whose work groups join every
+        // other small spin problem's in one merged launch per step
+        rs = ecut_set_tuning(s, &best);
     } else {
         rs = ecut_autotune(s, x, y, st, &best);
-        if (rs == ECUT_OK && merged && s->spin_ok && s->dim <= SMALL_SPIN_DIM && best.variant != 0) {
-            // small spin problems keep the default, whose work groups join
-            // every other small spin problem's in one merged launch per step
-            best = ecut_tuning{0, 0, 0, 0, 0};
-            rs = ecut_set_tuning(s, &best);
-        }
     }
     if (rs != ECUT_OK) return rs;
     std::lock_guard<std::mutex> g(g_tune_mu);
