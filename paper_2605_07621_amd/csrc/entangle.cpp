@@ -57,6 +57,8 @@ void drop_lane(Lane &l) {
 struct LaneSet {
     int dev = -1;
     std::vector<Lane> lanes;
+    bool direct = false;        // the one lane's handle is on the caller's stream
+    hipStream_t caller = nullptr;
 
     ecut_status take(int n) {
         if (hipGetDevice(&dev) != hipSuccess) return fail(ECUT_EDEVICE, "hipGetDevice");
@@ -83,7 +85,22 @@ struct LaneSet {
         return ECUT_OK;
     }
 
+    // one lane: its chain runs on the caller's stream itself
+    ecut_status on_stream(hipStream_t st) {
+        if (rocblas_set_stream(lanes[0].h, st) != rocblas_status_success) return fail(ECUT_EDEVICE, "rocblas_set_stream");
+        direct = true;
+        caller = st;
+        return ECUT_OK;
+    }
+
     ~LaneSet() {
+        if (direct) {
+            (void)hipStreamSynchronize(caller);
+            if (rocblas_set_stream(lanes[0].h, lanes[0].st) != rocblas_status_success) {
+                drop_lane(lanes[0]);
+                lanes.clear();
+            }
+        }
         for (Lane &l : lanes) (void)hipStreamSynchronize(l.st);
         std::lock_guard<std::mutex> g(g_lane_mu);
         auto &idle = g_lanes[dev];
@@ -133,7 +150,12 @@ std::map<int, std::vector<int32_t>> gram_groups(const ecut_sectors *s) {
 // needs.  Side by side the lanes need more than one chain does; where that is
 // past LANES_EXTRA, fewer lanes run, down to one, so that a large spectrum fits
 // where the largest group and its eigenvalues fit (32 sites in halves: 2.1 GB
-// instead of 4.8 for every block at once).
+// instead of 4.8 for every block at once).  A short spectrum is one chain on the
+// caller's stream: a lane costs threads, events and slower launches (sizes 1, 6,
+// 15 and 20, 12-site spin chain: 834 us in one chain, 908 on four lanes; 1, 4 and
+// 6: 247 against 343; one size of 252: 5.8 against 6.3 ms on a lane's own stream;
+// the sizes of an 8-site spatial Hubbard cut, 87 rows: 1.60 against 1.25 ms).
+constexpr int LANES_MIN_ROWS = 64;   // sum of the sizes from which lanes run
 constexpr size_t LANES_EXTRA = (size_t)1 << 27;   // doubles, 1 GiB
 
 struct Group {
@@ -162,7 +184,10 @@ Schedule lane_schedule(const ecut_sectors *s) {
         info += (int32_t)c;
         largest = std::max(largest, c * m * m);
     }
-    for (int n = std::max(1, std::min<int>(LANES, (int)S.groups.size())); n >= 1; --n) {
+    int64_t rows = 0;
+    for (const Group &W : S.groups) rows += W.m;
+    const int most = rows < LANES_MIN_ROWS ? 1 : std::max(1, std::min<int>(LANES, (int)S.groups.size()));
+    for (int n = most; n >= 1; --n) {
         std::vector<int64_t> load(n, 0);
         S.todo.assign(n, {});
         S.gram.assign(n, 0);
@@ -221,11 +246,16 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
     LaneSet set;
     ecut_status st = set.take((int)S.todo.size());
     if (st != ECUT_OK) return st;
-    // the lanes start after the caller's work on its stream
-    hipError_t le = hipEventRecord(set.lanes[0].ev, hs);
-    for (Lane &l : set.lanes)
-        if (le == hipSuccess) le = hipStreamWaitEvent(l.st, set.lanes[0].ev, 0);
-    if (le != hipSuccess) return hip_fail(le, "entanglement lanes");
+    hipError_t le = hipSuccess;
+    if (set.lanes.size() == 1) {
+        st = set.on_stream(hs);
+        if (st != ECUT_OK) return st;
+    } else {   // the lanes start after the caller's work on its stream
+        le = hipEventRecord(set.lanes[0].ev, hs);
+        for (Lane &l : set.lanes)
+            if (le == hipSuccess) le = hipStreamWaitEvent(l.st, set.lanes[0].ev, 0);
+        if (le != hipSuccess) return hip_fail(le, "entanglement lanes");
+    }
     // per group of equal-size blocks: their Gram matrices side by side
     // (rocBLAS syrk each), one batched eigensolve; the eigenvalues of every
     // group side by side, one copy to the host at the end
@@ -294,6 +324,7 @@ ecut_status ecut_entanglement_spectrum(const ecut_sectors *s, const double *psi_
     for (const Err &e : err)
         if (e.what) return fail(ECUT_EDEVICE, std::string(e.what) + ": status " + std::to_string(e.status));
     for (Lane &l : set.lanes) {   // the copies below follow every lane
+        if (set.direct) break;
         if (le == hipSuccess) le = hipEventRecord(l.ev, l.st);
         if (le == hipSuccess) le = hipStreamWaitEvent(hs, l.ev, 0);
     }
