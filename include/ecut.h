@@ -261,16 +261,23 @@ ecut_status ecut_apply_H_batch_noalloc(int32_t n, const ecut_sectors *const *s, 
 
 /*
  * Launch tuning of ecut_apply_H.  All fields 0, the default, selects the
- * kernels by the vector's size: Hubbard up/down problems of at most 32
- * hopping bonds run one fused kernel up to 2^18 amplitudes (2^20 if every
- * hop has the same value), the two-pass kernels (variant 6) above, and
- * variant 7 from 21 * 2^20 where it is available (open chains of 14 to 17 sites with
- * one hop value and 11.2 million amplitudes or more: the left pass on panels,
- * if those are 25 rows long on average, 38 on 17 sites); spin problems and the spatial
- * Hubbard cut, where kernel_flags bit 6 is set, run one kernel with a thread
- * per amplitude up to 2^20 amplitudes and the two-pass kernels (variant 2)
- * above, as do spin problems with rows of 6,657 to 13,312 amplitudes whose mean
- * row is a fifth of the longest; other problems run variant 0's kernel.
+ * kernels by the problem's shape (ecut_apply_kernels names them):
+ *   Hubbard up/down problems of at most 32 hopping bonds: one fused kernel up
+ *     to 2^18 amplitudes (2^20 if every hop has the same value), above that the
+ *     two-pass kernels (variant 6), from 21 * 2^20 amplitudes variant 7 where it
+ *     is available.  The left pass of either runs on panels on open chains of
+ *     14 to 17 sites with one hop value and 11.2 million amplitudes or more whose
+ *     panels have 25 rows on average (38 on 17 sites).  7,168 rows and more of
+ *     fewer than 32 amplitudes take variant 0's kernel at every size.
+ *   Spin problems and the spatial Hubbard cut where kernel_flags bit 6 is set:
+ *     one kernel with a thread per amplitude up to 2^20 amplitudes, above that
+ *     the two-pass kernels (variant 2) where rows are long enough: 24 amplitudes
+ *     on average for spin, for the spatial Hubbard cut 128 and a quarter of the
+ *     longest row; else variant 0's kernel.
+ *   Spin problems with rows of 6,657 to 13,312 amplitudes (bit 6 not set): the
+ *     two-pass kernels above 2^20 amplitudes where the mean row is a fifth of
+ *     the longest.
+ *   Other problems run variant 0's kernel.
  * Explicit tunings (used by the Hubbard up/down kernel, whose work groups
  * each own one row of Psi at a time):
  *   grid:      work groups (0 = one per compute unit);
@@ -573,7 +580,10 @@ typedef struct ecut_server_opts {
                                  sites, particle numbers, blocks, dimension) is autotuned on its own
                                  workspace (ecut_autotune); the tuning is kept for the life of the
                                  process and applied to every later request of that shape, in any
-                                 server.  0: default launch tuning */
+                                 server.  Small requests of a worker that batches (spin problems of
+                                 up to 2^20 amplitudes, Hubbard up/down of up to 2^18) are not
+                                 timed: they keep the kernels whose launches merge.  0: default
+                                 launch tuning */
     int64_t large_dim;        /* > 0 (and not sequential): requests of at least this many amplitudes
                                  run on a second worker with its own stream, one at a time with
                                  the tuning for a problem alone, while the others batch on the

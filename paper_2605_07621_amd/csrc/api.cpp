@@ -510,9 +510,10 @@ static bool hub_short_rows(const ecut_sectors *s) {
 
 // The default tuning, and the two-pass tuning, of a Hubbard up/down problem
 // short enough for the fused kernel.  With one hop value (no value table to
-// read) it is level with the two passes at 853,776 amplitudes (16.4 us both,
-// one launch instead of two); with signed hops it loses there (30 against 20
-// us) and wins at 213,444 (7.5 against 10).
+// read) it wins at 853,776 amplitudes (13.3 against 17 us, one launch instead of
+// two) and is level at 2.9M (37 us both); with signed hops it wins at 213,444
+// (7.5 against 10), is level at 853,776 (20 us both) and loses at 2.9M (56
+// against 48).
 bool hub_fused_size(const ecut_sectors *s) {
     return s->kernel == 1 && s->hub6_ok && s->dim <= (s->h6_uniform ? HUBF_MAX_DIM_UNIFORM : HUBF_MAX_DIM);
 }

@@ -2241,8 +2241,8 @@ __global__ __launch_bounds__(HUBU_THREADS) void k_hubU(const HubUArgs A, int n_x
 // at the copy rate in 0.65-0.71 ms when every other load is left out; the high
 // hops' panels must therefore come from L2.  The panels in flight on an XCD are
 // 36 KB per wave, so the launch keeps one group per compute unit (an LDS
-// request nothing uses): 0.865 ms against 0.945 with two (fetched 2.5 GB) and
-// 0.97-1.02 for the general pass; half or three quarters of that in flight
+// request nothing uses): 0.865 ms against 0.945 with two (3.3 GB fetched against
+// 5.2; the vector is 1.3) and 0.97-1.02 for the general pass; half or three quarters of that in flight
 // 0.98 and 0.91, one and a half times 0.95.  Four waves side by side on one
 // panel (2 KB rows) 0.90, whole rows at a time 1.07.
 // ------------------------------------------------------------------------
@@ -2503,9 +2503,9 @@ __global__ __launch_bounds__(HUBD_THREADS) void k_hubD_batch(const HubDArgs *__r
 // instead of making a round trip through y, and there is one launch.  Both
 // gathers rest on L2, so this is for short vectors: chains, two passes -> one:
 // 10 sites 10.0 -> 7.6 us (the host's call rate), 11 sites (213,444) 10.0 ->
-// 7.5, 12 sites (853,776) 16.4 both, 13 sites 37 against 41; rings (signed
-// hops), 12 sites 20 against 30.  The terms are summed as there: left operator,
-// right operator in slot order, diagonal.
+// 7.5, 12 sites (853,776) 17 -> 13.3, 13 sites (2.9M) level at 37; rings (signed
+// hops), 12 sites level at 20, 13 sites 48 -> 56.  The terms are summed as there:
+// left operator, right operator in slot order, diagonal.
 // ------------------------------------------------------------------------
 template <int NS, bool UNIF>
 __device__ __forceinline__ void hubF_item(const HubFArgs &F, int it, double *red) {

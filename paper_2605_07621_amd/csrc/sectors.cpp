@@ -1072,10 +1072,9 @@ static void build_hub6_tables(ecut_sectors *s, const ecut_model_desc *m) {
 
 // Panels of the left pass: an open chain (every bond (i, i + 1) once, one hop
 // value, so no hop carries a sign) of at least 14 sites.  The low part takes 7
-// sites, 8 from 16 sites on.  Whole applications, general left pass -> panels:
-// 16 sites 2.02 -> 1.93 ms, 15 sites 626 -> 547 us, 14 sites 180 -> 172; 13 sites
-// 37.5 -> 42 (panels of at most 20 rows at 6 low sites): those keep the general
-// pass.
+// sites, 8 from 16 sites on.  13 sites at half filling lost (37.5 -> 42 us, panels
+// of at most 20 rows at 6 low sites); which of the longer chains run on them is
+// the default tuning's rule, and the autotuner's.
 static void build_panels(ecut_sectors *s, const ecut_model_desc *m) {
     s->hp_lo = 0;
     s->hp_panels.clear();

@@ -97,3 +97,19 @@ def test_default_tuning_at_its_limits(dev, p, kernels):
     assert torch.equal(y, z)
     a, _, n2 = E.lanczos_tridiag(s, x, 1)
     assert abs(a[0] - float(x @ y) / n2) <= 1e-12 * float(y.norm()) / float(x.norm())
+
+
+@pytest.mark.parametrize("name", list(KINDS))
+def test_vectors_at_odd_offsets(dev, solo, name):
+    """Vectors that start 8 bytes past a 16-byte boundary, alone and in a
+    batch: the aligned vectors' result bit for bit."""
+    s, x, y = solo[name]
+    src, dst = torch.empty(s.dim + 1, dtype=x.dtype, device=dev), torch.full((s.dim + 1,), float("nan"),
+                                                                             dtype=x.dtype, device=dev)
+    src[1:] = x
+    assert src[1:].data_ptr() % 16 == 8 and dst[1:].data_ptr() % 16 == 8
+    s.apply(src[1:], out=dst[1:])
+    assert torch.equal(dst[1:], y) and bool(torch.isnan(dst[0]))
+    dst[1:] = float("nan")
+    E.apply_batch([s], [src[1:]], [dst[1:]])
+    assert torch.equal(dst[1:], y) and bool(torch.isnan(dst[0]))
