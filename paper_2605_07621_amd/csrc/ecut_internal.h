@@ -421,7 +421,7 @@ struct ecut_sectors {
     std::vector<double> h6_pval;
     bool h6_uniform = false;              // every hop of either spin has the value h6_hop
     double h6_hop = 0.0;
-    int32_t h6_maxq = 0;                  // bond slots of the down-spin table
+    int32_t h6_maxq = 0;                  // pair slots of the down-spin table
     std::vector<int32_t> h6_col;
     std::vector<double> h6_val;
     ecut::HubUArgs h6u{};
