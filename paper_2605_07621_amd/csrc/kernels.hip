@@ -2050,7 +2050,7 @@ size_t hub_lds_bytes(const ecut_sectors *s) {
     b += al((size_t)nlo * 4) * 2 + al((size_t)nlo * H.lo_stride * 4);
     b += al((size_t)nhi * 4) * 2 + al((size_t)nhi * H.hi_stride * 4);
     b += al((size_t)(H.n_coef > 0 ? H.n_coef : 1) * 8);
-    if (!H.uniform_u) b += 3 * 256 * 8;
+    if (!H.uniform_u || !H.uniform_t) b += 3 * 256 * 8;   // one U, uneven hops: the general kernel, which keeps a U table
     return b;
 }
 

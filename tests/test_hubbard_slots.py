@@ -176,3 +176,27 @@ def test_repeated_pairs_vs_oracle(dev):
     E.apply_batch(S, xs, out)
     for a, b in zip(ys, out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,a,b", [(7, 5, 6), (8, 4, 1), (10, 2, 8), (11, 5, 5), (12, 3, 6)])
+def test_one_u_with_uneven_hops_vs_oracle(dev, n, a, b):
+    """One U on every site and hops of several values, by every variant: the
+    whole-row kernel of uneven models keeps a table of U by byte of the word
+    even where one U would do (relative L2 1e-12)."""
+    torch = pytest.importorskip("torch")
+    import oracle as O
+    t = np.random.default_rng(n).normal(size=n)
+    p = I.Problem(_model(n, [(i, (i + 1) % n) for i in range(n)], t), I.Cut("updn"), a, b)
+    s = E.Sectors.from_problem(p)
+    psi = I.psi(3300 + n, s.dim)
+    x = s.import_(torch.from_numpy(psi).to(dev))
+    ref = O.Sector(p.model, a, b).apply(psi)
+    for v in (0, 1, 2, 4, 6):
+        for kw in (dict(n_xcd=8), dict(n_xcd=1, grid=4, row_order=1)):
+            try:
+                s.set_tuning(variant=v, **kw)
+            except E.EcutError:
+                continue
+            got = s.export(s.apply(x)).cpu().numpy()
+            assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref), (v, kw)
